@@ -164,22 +164,6 @@ __device__ __forceinline__ bool slab(float lx, float ly, float lz, float hx, flo
     return tn <= tf * 1.0000005f + 1e-30f;
 }
 
-// The same test with each plane's entry depth as one fused multiply-add,
-// l inv + (-o inv), noi = -o inv formed once per node: within an ulp of the
-// subtract-then-multiply form, far inside the boxes' 1e-5 padding and the
-// test's relative slack, so it still never rejects a box the ray enters.
-__device__ __forceinline__ bool slab_fma(float lx, float ly, float lz, float hx, float hy, float hz, const float3 inv,
-                                         const float3 noi, float t0, float t1, float &tnear)
-{
-    float ax = fmaf(lx, inv.x, noi.x), bx = fmaf(hx, inv.x, noi.x);
-    float ay = fmaf(ly, inv.y, noi.y), by = fmaf(hy, inv.y, noi.y);
-    float az = fmaf(lz, inv.z, noi.z), bz = fmaf(hz, inv.z, noi.z);
-    float tn = fmaxf(fmaxf(fminf(ax, bx), fminf(ay, by)), fmaxf(fminf(az, bz), t0));
-    float tf = fminf(fminf(fmaxf(ax, bx), fmaxf(ay, by)), fminf(fmaxf(az, bz), t1));
-    tnear = tn;
-    return tn <= tf * 1.0000005f + 1e-30f;
-}
-
 // order-preserving float <-> int maps (atomic min/max of floats)
 __device__ __forceinline__ int f2o(float f)
 {
@@ -202,9 +186,33 @@ __device__ __forceinline__ float fast_inv(float d)
     return __builtin_amdgcn_rcpf(fabsf(d) > 1e-30f ? d : copysignf(1e-30f, d));
 }
 
-__device__ __forceinline__ uint64_t make_key(float tau, uint32_t id)
+// The sort key of a hit, (bits(tau), id), held as the double with those bits:
+// a non-negative depth's bits order as its value does, tau is finite, so the
+// key is a finite non-negative double, and doubles of one sign order as their
+// bits do.  v_min_f64 / v_max_f64 then order keys at one instruction each.
+__device__ __forceinline__ double make_key(float tau, uint32_t id)
 {
-    return ((uint64_t)__float_as_uint(tau) << 32) | (uint64_t)id;
+    return __hiloint2double(__float_as_int(tau), (int)id);
+}
+__device__ __forceinline__ float key_tau(double k) { return __int_as_float(__double2hiint(k)); }
+
+// An empty slot of the k-buffer: +infinity, above every key; its depth word
+// reads as a quiet NaN, which fminf passes over.
+__device__ __forceinline__ double empty_key() { return __hiloint2double(0x7ff00000, 0); }
+
+// min / max of keys (never NaN), as the bare instructions: fmin and fmax put a
+// canonicalizing instruction before each operand.
+__device__ __forceinline__ double key_min(double a, double b)
+{
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ double key_max(double a, double b)
+{
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
 }
 
 // ---------------------------------------------------------------------------
@@ -224,21 +232,29 @@ __device__ __forceinline__ uint64_t make_key(float tau, uint32_t id)
 // unique, so hits of equal depth are neither lost nor repeated, and results
 // do not depend on K.
 //
-// The walk stack and the deferred list share one private array, growing from
-// opposite ends; their roles swap every round.  If they would collide, the
-// deferred list is dropped and the next round restarts from the root, which
-// re-finds every hit beyond the last composited key.
+// If the deferred list grows too long it is dropped and the next round
+// restarts from the root, which re-finds every hit beyond the last composited
+// key.
+//
+// What bounds the walk is VALU issue: lanes of a wavefront take the node
+// step, the leaf test and the visitor in turns (22 of 64 lanes active per
+// VALU instruction), at 72-79% of the issue peak.  So each of these blocks is
+// kept short: pushes without branches into ring windows, one merged push for
+// kept and deferred children, keys moved by min and max.  Node step 430 to
+// 230 VALU instructions, insertion at K = 16 121 to 81; room of 1M surfels:
+// forward K = 16 (512 x 512, 32 spp) 53.0 to 43.7 ms, backward K = 13
+// (1024 x 1024, 16 spp) 122.8 to 115.5 ms, relighting K = 12 31.9 to 28.1 ms.
 //
 // advance() does one node or one hit, so a wavefront can hold rays at
 // different rounds and refill lanes whose ray has finished (run_persistent).
 // ---------------------------------------------------------------------------
 // ---------------------------------------------------------------------------
-// A lane's stack: the top kLdsDepth entries live in LDS (lane-interleaved, so
-// a wavefront's accesses are conflict-free), deeper ones spill to a private
-// array.  Position p sits in LDS slot p % kLdsDepth; a push that reuses the
-// slot of position p - kLdsDepth first copies that entry out (entries never
-// change once pushed), and a pop reads the private copy for positions below
-// `spilled`.  Positions [0, spilled) always have valid private copies.
+// A lane's two stacks (walk and deferred): the newest entries of each are a
+// window in LDS, a ring of D slots (lane-interleaved, so a wavefront's
+// accesses are conflict-free); older ones lie in a private array.  Room is
+// made once per walking step (the oldest 8 entries of a window that the step
+// could fill move out, and 8 come back when a pop finds its window empty), so
+// pushing is one LDS store and a wrapped increment, without branches.
 // ---------------------------------------------------------------------------
 #ifndef GRT_LDS_DEPTH
 #define GRT_LDS_DEPTH 24
@@ -266,71 +282,141 @@ constexpr int kBwdSiteShare8 = GRT_BWD_SITE_SHARE8;
 #define GRT_SURFEL_SHARE4 2
 #endif
 constexpr int kSurfelShare4 = GRT_SURFEL_SHARE4;
-constexpr int kStackCap = 384;  // logical capacity of a stack
+constexpr int kStackCap = 384;  // private entries of a stack
+constexpr int kSpill = 8;       // entries moved between a window and the private array at a time
 constexpr int kNone = 0x7fffffff;
 
-template <int D>
-struct SpillStack {
-    int sp, spilled;
-
-    __device__ __forceinline__ void reset() { sp = 0; spilled = 0; }
-
-    // lds: this lane's slot 0 of the stack (slot i at lds[64 * i]); mem:
-    // its private overflow array [kStackCap]
-    __device__ __forceinline__ void push(int x, int *lds, int *mem)
-    {
-        const int slot = sp % D;
-        if (sp >= D && sp - D >= spilled) {
-            mem[sp - D] = lds[64 * slot];
-            spilled = sp - D + 1;
-        }
-        lds[64 * slot] = x;
-        ++sp;
-    }
-
-    __device__ __forceinline__ int pop(int *lds, int *mem)
-    {
-        --sp;
-        if (sp < spilled) {
-            spilled = sp;
-            return mem[sp];
-        }
-        return lds[64 * (sp % D)];
-    }
-};
-
-// The walk stack and the deferred list of a lane; their roles swap each
-// round (the deferred list becomes the next round's walk stack).  A round's
-// stack starts with at most kMaxDeferred items; below them, a node step pops
-// one item and pushes at most three, so the stack holds at most three
-// siblings for each 4-wide level of the current path.  The 4-wide tree is no
-// deeper than the binary LBVH (each of its edges spans at least one binary
-// edge), whose depth is at most 63 (30-bit codes, then the position breaking
-// ties), so the stack stays within kMaxDeferred + 3 * 63 <= kStackCap.
+// The roles of the two stacks swap each round (the deferred list becomes the
+// next round's walk stack).  A round's stack starts with at most kMaxDeferred
+// items; below them, a node step pops one item and pushes at most three, so
+// the stack holds at most three siblings for each 4-wide level of the current
+// path.  The 4-wide tree is no deeper than the binary LBVH (each of its edges
+// spans at least one binary edge), whose depth is at most 63 (30-bit codes,
+// then the position breaking ties), so the stack stays within
+// kMaxDeferred + 3 * 63 <= kStackCap.
 constexpr int kMaxDeferred = 192;
 static_assert(kMaxDeferred + 3 * 63 <= kStackCap, "walk stack bound");
 
+typedef __attribute__((address_space(3))) int LdsInt;
+__device__ __forceinline__ uint32_t lds_addr(const int *p) { return (uint32_t)(uintptr_t)(LdsInt *)p; }
+__device__ __forceinline__ int lds_load(uint32_t a) { return *(const LdsInt *)(uintptr_t)a; }
+__device__ __forceinline__ void lds_store(uint32_t a, int x) { *(LdsInt *)(uintptr_t)a = x; }
+
 template <int D>
 struct Frontier {
-    SpillStack<D> walk;  // the current round's walk stack
-    SpillStack<D> def;   // deferrals for the next round
-    int *lds;            // this lane's slot 0 of stack 0; stack 1 starts D slots on
-    int *mem0, *mem1;    // the two stacks' private overflow arrays
-    int role;            // the stack that holds the walk (the other one defers)
+    static constexpr uint32_t kStride = 256;            // a slot of the wavefront: 64 lanes x 4 bytes
+    static constexpr uint32_t kWindow = D * kStride;
+    static_assert(D >= kSpill + 5, "a spill leaves the entries that a step may add");
+    uint32_t base;        // LDS address of this lane's slot 0 of window 0; window 1 follows
+    uint32_t woff;        // the window that holds the walk: 0 or kWindow (the other one defers)
+    uint32_t wtop, dtop;  // LDS address of the next free slot of the walk / deferred window
+    int wn, dn;           // entries in the windows
+    int wold, dold;       // entries in the private arrays, below the windows'
+    int *mem;             // [2][kStackCap] private arrays
 
-    __device__ __forceinline__ int *lds_of(int which) const { return lds + 64 * D * which; }
-    __device__ __forceinline__ int *mem_of(int which) const { return which ? mem1 : mem0; }
-    __device__ __forceinline__ void push_walk(int x) { walk.push(x, lds_of(role), mem_of(role)); }
-    __device__ __forceinline__ int pop_walk() { return walk.pop(lds_of(role), mem_of(role)); }
-    __device__ __forceinline__ void push_def(int x) { def.push(x, lds_of(role ^ 1), mem_of(role ^ 1)); }
+    __device__ __forceinline__ uint32_t wlo() const { return base + woff; }
+    __device__ __forceinline__ uint32_t dlo() const { return base + (kWindow - woff); }
+    __device__ __forceinline__ int *mem_of(uint32_t off) const { return mem + (off ? kStackCap : 0); }
+    static __device__ __forceinline__ uint32_t next(uint32_t a, uint32_t lo)
+    {
+        a += kStride;
+        return a == lo + kWindow ? lo : a;
+    }
 
-    // the deferred list becomes the walk stack (positions swapped, no copy)
+    __device__ __forceinline__ void clear_def()
+    {
+        dtop = dlo();
+        dn = 0;
+        dold = 0;
+    }
+    __device__ __forceinline__ void reset()
+    {
+        wtop = wlo();
+        wn = 0;
+        wold = 0;
+        clear_def();
+    }
+
+    static __device__ __forceinline__ void spill(uint32_t top, uint32_t lo, int &n, int &old, int *m)
+    {
+        uint32_t b = top - kStride * (uint32_t)n;  // the oldest entry of the window
+        b = (int)(b - lo) < 0 ? b + kWindow : b;
+#pragma unroll
+        for (int j = 0; j < kSpill; ++j) {
+            m[old + j] = lds_load(b);
+            b = next(b, lo);
+        }
+        n -= kSpill;
+        old += kSpill;
+    }
+
+    // Before a walking step, which pushes at most 3 items on the walk stack
+    // and 4 on the deferred list, and a leaf test after it that defers one
+    // more.  A deferred list too long is dropped (lost); while it is, what is
+    // pushed on it goes the same way.
+    __device__ __forceinline__ void make_room(bool &lost)
+    {
+        if (wn <= D - 3 && dn <= D - 5) return;
+        if (wn > D - 3) spill(wtop, wlo(), wn, wold, mem_of(woff));
+        if (dn > D - 5) {
+            if (lost || dold + kSpill > kMaxDeferred - D) {
+                lost = true;
+                clear_def();
+            } else {
+                spill(dtop, dlo(), dn, dold, mem_of(kWindow - woff));
+            }
+        }
+    }
+
+    __device__ __forceinline__ bool walk_empty() const { return (wn | wold) == 0; }
+
+    // the walk stack is not empty
+    __device__ __forceinline__ int pop_walk()
+    {
+        const uint32_t lo = wlo();
+        if (wn == 0) {
+            const int *m = mem_of(woff) + (wold - kSpill);
+#pragma unroll
+            for (int j = 0; j < kSpill; ++j) {
+                lds_store(wtop, m[j]);
+                wtop = next(wtop, lo);
+            }
+            wn = kSpill;
+            wold -= kSpill;
+        }
+        wtop = (wtop == lo ? lo + kWindow : wtop) - kStride;
+        --wn;
+        return lds_load(wtop);
+    }
+
+    __device__ __forceinline__ void push_def(int x)
+    {
+        lds_store(dtop, x);
+        dtop = next(dtop, dlo());
+        ++dn;
+    }
+
+    // x goes on the walk stack (w), on the deferred list (d) or nowhere; the
+    // store is unconditional, since the slot it hits is free
+    __device__ __forceinline__ void push(int x, bool w, bool d)
+    {
+        const uint32_t a = w ? wtop : dtop;
+        lds_store(a, x);
+        const uint32_t n = next(a, w ? wlo() : dlo());
+        wtop = w ? n : wtop;
+        dtop = d ? n : dtop;
+        wn += (int)w;
+        dn += (int)d;
+    }
+
+    // the deferred list becomes the walk stack, which is empty
     __device__ __forceinline__ void swap_roles()
     {
-        const SpillStack<D> t = walk;
-        walk = def;
-        def = t;
-        role ^= 1;
+        wtop = dtop;
+        wn = dn;
+        wold = dold;
+        woff = kWindow - woff;
+        clear_def();
     }
 };
 
@@ -349,8 +435,8 @@ struct Walker {
     static constexpr int kDepth = D;  // LDS entries per lane and stack
     float3 o, d;
     float tmin, tmax;
-    uint64_t last;        // start key of the round; while compositing, the last composited hit
-    uint64_t key[K];
+    double last;          // start key of the round; while compositing, the last composited hit
+    double key[K];
     uint32_t pos[K];
     int cnt;
     int cur;              // item in hand: node >= 0, leaf -(pos+1), or kNone
@@ -365,22 +451,16 @@ struct Walker {
     __device__ __forceinline__ void clear_buffer()
     {
 #pragma unroll
-        for (int i = 0; i < K; ++i) { key[i] = ~0ull; pos[i] = 0; }
+        for (int i = 0; i < K; ++i) { key[i] = empty_key(); pos[i] = 0; }
         cnt = 0;
     }
 
     // The round's walk covers [lo_bound, hi_bound]: from the last composited
     // key's depth (tmin in the first round) to the full buffer's largest
-    // depth (tmax while it is not full).  Derived when needed rather than
-    // held, to keep two registers free.
-    __device__ __forceinline__ float lo_bound() const
-    {
-        return fmaxf(tmin, __uint_as_float((uint32_t)(last >> 32)));
-    }
-    __device__ __forceinline__ float hi_bound() const
-    {
-        return cnt >= K ? __uint_as_float((uint32_t)(key[K - 1] >> 32)) : tmax;
-    }
+    // depth (tmax while it is not full: the empty key's depth word is a NaN).
+    // Derived when needed rather than held, to keep two registers free.
+    __device__ __forceinline__ float lo_bound() const { return fmaxf(tmin, key_tau(last)); }
+    __device__ __forceinline__ float hi_bound() const { return fminf(tmax, key_tau(key[K - 1])); }
 
     __device__ __forceinline__ void start(const SceneDev &S, float3 o_, float3 d_, float tmin_, float tmax_)
     {
@@ -388,31 +468,16 @@ struct Walker {
         d = d_;
         tmin = tmin_;
         tmax = tmax_;
-        last = 0;
+        last = 0.0;
         ncomp = 0;
         pend = kNone;
-        F.walk.reset();
-        F.def.reset();
+        F.reset();
         lost = false;
         cur = S.n == 1 ? -1 : 0;
         clear_buffer();
 #ifdef GRT_STATS
         st_nodes = st_leaves = st_comps = st_lost = st_deferred = 0;
         st_rounds = 1;
-#endif
-    }
-
-    __device__ __forceinline__ void defer(int x)
-    {
-        if (lost) return;
-        if (F.def.sp >= kMaxDeferred) {  // too many: drop the list, restart the next round at the root
-            lost = true;
-            F.def.reset();
-            return;
-        }
-        F.push_def(x);
-#ifdef GRT_STATS
-        ++st_deferred;
 #endif
     }
 
@@ -425,101 +490,60 @@ struct Walker {
         ++st_leaves;
 #endif
         if (fabsf(den) < kGrazing || !(tau > tmin && tau <= tmax) || !(rho2 <= r2max)) return;
-        uint64_t k = make_key(tau, __float_as_uint(idbits));
+        const double k = make_key(tau, __float_as_uint(idbits));
         if (k <= last) return;
-        if (k >= key[K - 1]) {  // beyond the full buffer: next round
-            defer(-(int)p - 1);
-            return;
+        // beyond a full buffer, or the largest key drops out of it: to the next round
+        const bool beyond = k >= key[K - 1];
+        if (cnt >= K) {
+            F.push_def(-(int)(beyond ? p : pos[K - 1]) - 1);
+#ifdef GRT_STATS
+            if (!lost) ++st_deferred;
+#endif
         }
-        if (cnt >= K) defer(-(int)pos[K - 1] - 1);  // evicted
-        // sorted insertion, the largest key drops out
-        bool placed = false;
+        if (beyond) return;
+        // Sorted insertion: slot i takes the middle of (slot i - 1, k, itself),
+        // which for keys is a min and a max, and for positions two selects.
+        bool above = key[K - 1] > k;
 #pragma unroll
         for (int i = K - 1; i > 0; --i) {
-            bool shift = key[i - 1] > k;
-            uint64_t nk = shift ? key[i - 1] : (placed ? key[i] : k);
-            uint32_t np = shift ? pos[i - 1] : (placed ? pos[i] : p);
-            placed = placed || !shift;
-            key[i] = nk;
-            pos[i] = np;
+            const bool below = key[i - 1] > k;  // slot i - 1 moves up
+            pos[i] = above ? (below ? pos[i - 1] : p) : pos[i];
+            key[i] = key_max(key[i - 1], key_min(key[i], k));
+            above = below;
         }
-        if (!placed) { key[0] = k; pos[0] = p; }
+        pos[0] = above ? p : pos[0];
+        key[0] = key_min(key[0], k);
         ++cnt;
     }
 
-    // A child box met by the ray in [tlo, tmax]: process now if it starts
-    // within thi, else defer it.
-    __device__ __forceinline__ bool keep_child(int c, bool hit, float tn, float thi)
-    {
-        if (!hit) return false;
-        if (tn > thi) {
-            defer(c);
-            return false;
-        }
-        return true;
-    }
-
-    // One item of the current round; true when the round's walk is complete.
-    // One item of the current round's walk; `leaf` receives at most one leaf
-    // to test.  True when the round's walk is complete.
-    __device__ __forceinline__ bool step(const SceneDev &S, int &leaf)
-    {
-        if (cur == kNone) {
-            if (F.walk.sp == 0) return true;
-            cur = F.pop_walk();
-        }
-        if (cur < 0) {
-            leaf = cur;
-            cur = kNone;
-        } else {
-            walk_node(S, leaf);
-        }
-        return false;
-    }
-
     // Test the children of 4-wide node `cur`; sets the next item and at most
-    // one leaf to test.  Kept children (met within thi) are taken nearest
-    // entry first: a leaf among them goes to the single surfel site in
-    // advance() (a wavefront then runs it once per step however its lanes'
-    // children are mixed), the nearest other child becomes the item in hand,
-    // and the rest go on the walk stack, farthest first.
+    // one leaf to test.  The children met in [tlo, tmax] are sorted by entry
+    // depth; those entered beyond thi (the full buffer's largest depth) are
+    // deferred to the next round.  Of the others the nearest becomes the item
+    // in hand, except that a leaf among the first two goes to the single
+    // surfel site in advance() (a wavefront then runs it once per step however
+    // its lanes' children are mixed); the rest go on the walk stack, farthest
+    // first.  All of it is selects: with branches per child, lanes that defer,
+    // push and skip took turns.
     __device__ __forceinline__ void walk_node(const SceneDev &S, int &leaf)
     {
 #ifdef GRT_STATS
         ++st_nodes;
 #endif
         const Node4 *nd = S.nodes4 + cur;
-        const float tlo = lo_bound(), thi = hi_bound();
-        const float3 inv = make_float3(fast_inv(d.x), fast_inv(d.y), fast_inv(d.z));
         const float4 lx = nd->lx, ly = nd->ly, lz = nd->lz, hx = nd->hx, hy = nd->hy, hz = nd->hz;
         const int4 ch = nd->ch;
-        // all four boxes tested without branches (an unused slot's zero box
-        // is masked by its reference)
+        const float tlo = lo_bound(), thi = fminf(hi_bound(), 3.402823466e+38f);
+        const float3 inv = make_float3(fast_inv(d.x), fast_inv(d.y), fast_inv(d.z));
+        // an unused slot's zero box is masked by its reference
         float t0, t1, t2, t3;
-#ifdef GRT_SLAB_FMA
-        const float3 noi = make_float3(-o.x * inv.x, -o.y * inv.y, -o.z * inv.z);
-        bool k0 = slab_fma(lx.x, ly.x, lz.x, hx.x, hy.x, hz.x, inv, noi, tlo, tmax, t0);
-        bool k1 = slab_fma(lx.y, ly.y, lz.y, hx.y, hy.y, hz.y, inv, noi, tlo, tmax, t1);
-        bool k2 = slab_fma(lx.z, ly.z, lz.z, hx.z, hy.z, hz.z, inv, noi, tlo, tmax, t2);
-        bool k3 = slab_fma(lx.w, ly.w, lz.w, hx.w, hy.w, hz.w, inv, noi, tlo, tmax, t3);
-#else
-        bool k0 = slab(lx.x, ly.x, lz.x, hx.x, hy.x, hz.x, o, inv, tlo, tmax, t0);
-        bool k1 = slab(lx.y, ly.y, lz.y, hx.y, hy.y, hz.y, o, inv, tlo, tmax, t1);
-        bool k2 = slab(lx.z, ly.z, lz.z, hx.z, hy.z, hz.z, o, inv, tlo, tmax, t2);
-        bool k3 = slab(lx.w, ly.w, lz.w, hx.w, hy.w, hz.w, o, inv, tlo, tmax, t3);
-#endif
-        k0 = k0 & (ch.x != kNoChild);
-        k1 = k1 & (ch.y != kNoChild);
-        k2 = k2 & (ch.z != kNoChild);
-        k3 = k3 & (ch.w != kNoChild);
-        k0 = keep_child(ch.x, k0, t0, thi);
-        k1 = keep_child(ch.y, k1, t1, thi);
-        k2 = keep_child(ch.z, k2, t2, thi);
-        k3 = keep_child(ch.w, k3, t3, thi);
-        const int m = (int)k0 + (int)k1 + (int)k2 + (int)k3;
-        // kept children first, by entry depth (a five-exchange sorting network)
+        const bool k0 = slab(lx.x, ly.x, lz.x, hx.x, hy.x, hz.x, o, inv, tlo, tmax, t0) & (ch.x != kNoChild);
+        const bool k1 = slab(lx.y, ly.y, lz.y, hx.y, hy.y, hz.y, o, inv, tlo, tmax, t1) & (ch.y != kNoChild);
+        const bool k2 = slab(lx.z, ly.z, lz.z, hx.z, hy.z, hz.z, o, inv, tlo, tmax, t2) & (ch.z != kNoChild);
+        const bool k3 = slab(lx.w, ly.w, lz.w, hx.w, hy.w, hz.w, o, inv, tlo, tmax, t3) & (ch.w != kNoChild);
+        // by entry depth, missed children last (a five-exchange sorting network)
         float s0 = k0 ? t0 : INFINITY, s1 = k1 ? t1 : INFINITY, s2 = k2 ? t2 : INFINITY, s3 = k3 ? t3 : INFINITY;
-        int c0 = k0 ? ch.x : kNone, c1 = k1 ? ch.y : kNone, c2 = k2 ? ch.z : kNone, c3 = k3 ? ch.w : kNone;
+        int c0 = ch.x, c1 = ch.y, c2 = ch.z, c3 = ch.w;
         auto xch = [](float &sa, int &ca, float &sb, int &cb) {
             const bool sw = sb < sa;
             const float ts = sw ? sb : sa;
@@ -534,20 +558,18 @@ struct Walker {
         xch(s0, c0, s2, c2);
         xch(s1, c1, s3, c3);
         xch(s1, c1, s2, c2);
-        // the nearest kept leaf, if any, is the step's leaf; the others in order
-        const int li = (m > 0 && c0 < 0) ? 0 : (m > 1 && c1 < 0) ? 1 : (m > 2 && c2 < 0) ? 2 : (m > 3 && c3 < 0) ? 3 : -1;
-        int o0 = c0, o1 = c1, o2 = c2, o3 = c3, no = m;
-        if (li >= 0) {
-            leaf = li == 0 ? c0 : li == 1 ? c1 : li == 2 ? c2 : c3;
-            o0 = li == 0 ? c1 : c0;
-            o1 = li <= 1 ? c2 : c1;
-            o2 = li <= 2 ? c3 : c2;
-            no = m - 1;
-        }
-        cur = no >= 1 ? o0 : kNone;
-        if (no >= 4) F.push_walk(o3);
-        if (no >= 3) F.push_walk(o2);
-        if (no >= 2) F.push_walk(o1);
+        const bool n0 = s0 <= thi, n1 = s1 <= thi, n2 = s2 <= thi, n3 = s3 <= thi;  // kept in this round
+        const bool h0 = s0 < INFINITY, h1 = s1 < INFINITY, h2 = s2 < INFINITY, h3 = s3 < INFINITY;
+#ifdef GRT_STATS
+        if (!lost) st_deferred += (int)(h0 & !n0) + (int)(h1 & !n1) + (int)(h2 & !n2) + (int)(h3 & !n3);
+#endif
+        const bool f0 = n0 & (c0 < 0), f1 = n1 & !f0 & (c1 < 0);
+        F.push(c3, n3, h3 & !n3);
+        F.push(c2, n2, h2 & !n2);
+        F.push(c1, n1 & !f0 & !f1, h1 & !n1);
+        F.push(c0, false, h0 & !n0);
+        leaf = f0 ? c0 : f1 ? c1 : kNone;
+        cur = f0 ? (n1 ? c1 : kNone) : n0 ? c0 : kNone;
     }
 
     // Set up the next round from the deferred frontier (or the root).  A next
@@ -564,9 +586,8 @@ struct Walker {
         ++st_rounds;
         st_lost += lost ? 1 : 0;
 #endif
-        F.walk.reset();  // empty: the walk is complete
         if (lost) {
-            F.def.reset();
+            F.clear_def();
             lost = false;
             cur = S.n == 1 ? -1 : 0;
         } else {
@@ -577,11 +598,11 @@ struct Walker {
 
     // Depth of the last composited hit once the ray is finished (0 when none
     // was): a re-traversal bounded there meets the same composited hits.
-    __device__ __forceinline__ float stop_depth() const { return __uint_as_float((uint32_t)(last >> 32)); }
+    __device__ __forceinline__ float stop_depth() const { return key_tau(last); }
 
     __device__ __forceinline__ bool deferred_empty() const
     {
-        return !lost && F.def.sp == 0;
+        return !lost && (F.dn | F.dold) == 0;
     }
 
     // One unit of work: an item of the walk, or, once the round's walk is
@@ -602,13 +623,17 @@ struct Walker {
     __device__ __forceinline__ bool advance(const SceneDev &S, Visit &visit)
     {
         if (ncomp == 0 && pend == kNone) {
-            int leaf = kNone;
-            if (step(S, leaf)) {  // the round's walk is complete
+            F.make_room(lost);
+            if (cur == kNone && F.walk_empty()) {  // the round's walk is complete
                 const int m = cnt < K ? cnt : K;
                 if (m == 0) return true;
                 ncomp = m;
-            } else if (leaf != kNone) {
-                pend = -leaf - 1;
+            } else {
+                if (cur == kNone) cur = F.pop_walk();
+                int leaf = cur;
+                if (cur < 0) cur = kNone;
+                else walk_node(S, leaf);
+                if (leaf != kNone) pend = -leaf - 1;
             }
         }
         const bool wl = pend != kNone, wc = ncomp > 0;
@@ -642,15 +667,14 @@ struct Walker {
             pend = kNone;
             return false;
         }
-        const bool stop = visit(sp, (uint32_t)(key[0] & 0xffffffffu), __uint_as_float((uint32_t)(key[0] >> 32)), r0,
-                                r1, r2, r3, rho2, o, d);
+        const bool stop = visit(sp, (uint32_t)__double2loint(key[0]), key_tau(key[0]), r0, r1, r2, r3, rho2, o, d);
 #ifdef GRT_STATS
         ++st_comps;
 #endif
         last = key[0];  // the last composited hit (next_round resets it)
 #pragma unroll
         for (int i = 0; i < K - 1; ++i) { key[i] = key[i + 1]; pos[i] = pos[i + 1]; }
-        key[K - 1] = ~0ull;
+        key[K - 1] = empty_key();
         --ncomp;
         if (stop) return true;
         if (ncomp == 0) {
@@ -759,16 +783,14 @@ __device__ __forceinline__ void run_persistent(Job &job, unsigned long long *cou
     using WalkerT = typename std::remove_reference<decltype(job.walker())>::type;
     constexpr int D = WalkerT::kDepth;
     __shared__ int lds_stacks[4][2][D][64];  // [wave][stack][slot][lane]
-    int spill0[kStackCap], spill1[kStackCap];
+    int overflow[2 * kStackCap];
     const int wave = (threadIdx.x >> 6) & 3;
     {
         auto &F = job.walker().F;
-        F.lds = &lds_stacks[wave][0][0][lane];
-        F.mem0 = spill0;
-        F.mem1 = spill1;
-        F.role = 0;
-        F.walk.reset();
-        F.def.reset();
+        F.base = lds_addr(&lds_stacks[wave][0][0][lane]);
+        F.woff = 0;
+        F.mem = overflow;
+        F.reset();
     }
 #ifdef GRT_STATS
     uint32_t tally[kNumWalkStats] = {};
