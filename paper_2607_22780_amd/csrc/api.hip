@@ -92,7 +92,7 @@ grt::SceneDev scene_dev(const grt_scene *s)
     d.col = s->w.col;
     d.nodes = s->w.nodes;
     d.quat = s->w.quat;
-    d.nodes4 = s->w.nodes4;
+    d.nodesq = s->w.nodesq;
     d.n = (int32_t)s->s.n;
     return d;
 }

@@ -15,8 +15,10 @@
 //   node4 [<= n-1] Node4 the same hierarchy collapsed to 4 children per
 //                        node (boxes as structure of arrays, references as
 //                        above, >= 0 now a 4-wide node)           (128 B)
-// The traversal walks the 4-wide nodes: half the node steps of the binary
-// tree, each testing up to four boxes from one 128-byte line.
+//   nodeq [<= n-1] NodeQ the 4-wide nodes with their child boxes in 8 bits a
+//                        plane, rounded outward                    (64 B)
+// The traversal walks the NodeQ: half the node steps of the binary tree, each
+// testing up to four boxes from one 64-byte line.
 #pragma once
 
 #include <type_traits>
@@ -57,12 +59,26 @@ struct alignas(16) Node4 {
     int4 pad;
 };
 
+// The node a walk loads: child j spans org + scale * [lo_j, hi_j] on each
+// axis, with byte j of the axis' lo and hi words (conservative, see
+// quantize_node).  The vector L1 bounds the walk as much as VALU issue does (a
+// divergent load is one tag access per lane and 16 bytes: 97% of its cycles
+// were busy or stalled with the seven loads of a 128-byte node), so a node is
+// four loads.
+struct alignas(16) NodeQ {
+    float org[3];
+    float scale[3];
+    uint32_t lo[3], hi[3];
+    int4 ch;  // child references (kNoChild: unused slot)
+};
+static_assert(sizeof(NodeQ) == 64, "four 16-byte loads");
+
 struct SceneDev {
     const float4 *rec;
     const float4 *col;
     const Node *nodes;
     const float4 *quat;  // stored quaternions in record order
-    const Node4 *nodes4;
+    const NodeQ *nodesq;
     int32_t n;
 };
 
@@ -180,10 +196,36 @@ __device__ __forceinline__ float safe_inv(float d)
 // The walk's inverse direction, formed at each node step rather than held (3
 // registers): the hardware reciprocal (1 ulp) is far inside the slab test's
 // slack and the boxes' padding, so the test still rejects no box the ray
-// enters.
+// enters.  Components below 1e-18 are taken as that, so that plane * inverse
+// stays finite; the sign is kept.
 __device__ __forceinline__ float fast_inv(float d)
 {
-    return __builtin_amdgcn_rcpf(fabsf(d) > 1e-30f ? d : copysignf(1e-30f, d));
+    return __builtin_amdgcn_rcpf(fabsf(d) > 1e-18f ? d : copysignf(1e-18f, d));
+}
+
+// Byte j of a word as a float (one instruction).
+template <int j>
+__device__ __forceinline__ float byte_f(uint32_t w)
+{
+    return (float)((w >> (8 * j)) & 255u);
+}
+
+// Child j of a node from the words of its near and far planes (chosen by the
+// sign of the direction): the depth of plane q of an axis is q * step + start,
+// one fused multiply-add, with no min or max of the pair.  Rounding moves a
+// plane by less than the margin the node was quantized with, plus a relative
+// part that the comparison allows for; a NaN keeps the child.
+template <int j>
+__device__ __forceinline__ bool slab_q(uint32_t nx, uint32_t ny, uint32_t nz, uint32_t fx, uint32_t fy, uint32_t fz,
+                                       const float3 step, const float3 start, float t0, float &tnear)
+{
+    const float ax = fmaf(byte_f<j>(nx), step.x, start.x), bx = fmaf(byte_f<j>(fx), step.x, start.x);
+    const float ay = fmaf(byte_f<j>(ny), step.y, start.y), by = fmaf(byte_f<j>(fy), step.y, start.y);
+    const float az = fmaf(byte_f<j>(nz), step.z, start.z), bz = fmaf(byte_f<j>(fz), step.z, start.z);
+    const float tn = fmaxf(fmaxf(ax, ay), fmaxf(az, t0));
+    const float tf = fminf(fminf(bx, by), bz);
+    tnear = tn;
+    return !(tn > tf * 1.0000005f + 1e-30f);
 }
 
 // The sort key of a hit, (bits(tau), id), held as the double with those bits:
@@ -257,7 +299,7 @@ __device__ __forceinline__ double key_max(double a, double b)
 // pushing is one LDS store and a wrapped increment, without branches.
 // ---------------------------------------------------------------------------
 #ifndef GRT_LDS_DEPTH
-#define GRT_LDS_DEPTH 24
+#define GRT_LDS_DEPTH 26
 #endif
 constexpr int kLdsDepth = GRT_LDS_DEPTH;  // LDS entries per lane and stack
 #ifndef GRT_BWD_LDS_DEPTH
@@ -473,7 +515,7 @@ struct Walker {
         pend = kNone;
         F.reset();
         lost = false;
-        cur = S.n == 1 ? -1 : 0;
+        cur = S.n > 1 ? 0 : S.n == 1 ? -1 : kNone;  // no surfels: the first step ends the ray
         clear_buffer();
 #ifdef GRT_STATS
         st_nodes = st_leaves = st_comps = st_lost = st_deferred = 0;
@@ -530,17 +572,27 @@ struct Walker {
 #ifdef GRT_STATS
         ++st_nodes;
 #endif
-        const Node4 *nd = S.nodes4 + cur;
-        const float4 lx = nd->lx, ly = nd->ly, lz = nd->lz, hx = nd->hx, hy = nd->hy, hz = nd->hz;
-        const int4 ch = nd->ch;
-        const float tlo = lo_bound(), thi = fminf(hi_bound(), 3.402823466e+38f);
+        const float4 *nd = reinterpret_cast<const float4 *>(S.nodesq + cur);
+        const float4 w0 = nd[0], w1 = nd[1], w2 = nd[2];
+        const int4 ch = *reinterpret_cast<const int4 *>(nd + 3);
+        const float tlo = lo_bound();
+        const float thi = fminf(hi_bound() * 1.0000005f, 3.402823466e+38f);
+        const float tend = fminf(tmax * 1.0000005f + 1e-30f, 3.402823466e+38f);
         const float3 inv = make_float3(fast_inv(d.x), fast_inv(d.y), fast_inv(d.z));
-        // an unused slot's zero box is masked by its reference
+        const float3 start = make_float3((w0.x - o.x) * inv.x, (w0.y - o.y) * inv.y, (w0.z - o.z) * inv.z);
+        const float3 step = make_float3(w0.w * inv.x, w1.x * inv.y, w1.y * inv.z);
+        const uint32_t lx = __float_as_uint(w1.z), ly = __float_as_uint(w1.w), lz = __float_as_uint(w2.x);
+        const uint32_t hx = __float_as_uint(w2.y), hy = __float_as_uint(w2.z), hz = __float_as_uint(w2.w);
+        const bool gx = __float_as_int(d.x) < 0, gy = __float_as_int(d.y) < 0, gz = __float_as_int(d.z) < 0;
+        const uint32_t nx = gx ? hx : lx, fx = gx ? lx : hx;
+        const uint32_t ny = gy ? hy : ly, fy = gy ? ly : hy;
+        const uint32_t nz = gz ? hz : lz, fz = gz ? lz : hz;
+        // an unused slot is masked by its reference
         float t0, t1, t2, t3;
-        const bool k0 = slab(lx.x, ly.x, lz.x, hx.x, hy.x, hz.x, o, inv, tlo, tmax, t0) & (ch.x != kNoChild);
-        const bool k1 = slab(lx.y, ly.y, lz.y, hx.y, hy.y, hz.y, o, inv, tlo, tmax, t1) & (ch.y != kNoChild);
-        const bool k2 = slab(lx.z, ly.z, lz.z, hx.z, hy.z, hz.z, o, inv, tlo, tmax, t2) & (ch.z != kNoChild);
-        const bool k3 = slab(lx.w, ly.w, lz.w, hx.w, hy.w, hz.w, o, inv, tlo, tmax, t3) & (ch.w != kNoChild);
+        const bool k0 = slab_q<0>(nx, ny, nz, fx, fy, fz, step, start, tlo, t0) & (ch.x != kNoChild);
+        const bool k1 = slab_q<1>(nx, ny, nz, fx, fy, fz, step, start, tlo, t1) & (ch.y != kNoChild);
+        const bool k2 = slab_q<2>(nx, ny, nz, fx, fy, fz, step, start, tlo, t2) & (ch.z != kNoChild);
+        const bool k3 = slab_q<3>(nx, ny, nz, fx, fy, fz, step, start, tlo, t3) & (ch.w != kNoChild);
         // by entry depth, missed children last (a five-exchange sorting network)
         float s0 = k0 ? t0 : INFINITY, s1 = k1 ? t1 : INFINITY, s2 = k2 ? t2 : INFINITY, s3 = k3 ? t3 : INFINITY;
         int c0 = ch.x, c1 = ch.y, c2 = ch.z, c3 = ch.w;
@@ -559,7 +611,7 @@ struct Walker {
         xch(s1, c1, s3, c3);
         xch(s1, c1, s2, c2);
         const bool n0 = s0 <= thi, n1 = s1 <= thi, n2 = s2 <= thi, n3 = s3 <= thi;  // kept in this round
-        const bool h0 = s0 < INFINITY, h1 = s1 < INFINITY, h2 = s2 < INFINITY, h3 = s3 < INFINITY;
+        const bool h0 = s0 <= tend, h1 = s1 <= tend, h2 = s2 <= tend, h3 = s3 <= tend;         // met by the ray
 #ifdef GRT_STATS
         if (!lost) st_deferred += (int)(h0 & !n0) + (int)(h1 & !n1) + (int)(h2 & !n2) + (int)(h3 & !n3);
 #endif

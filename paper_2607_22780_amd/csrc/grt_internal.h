@@ -52,6 +52,7 @@ struct SceneWS {
     float *acc;            // [n,16] gradient lines of the backward passes
     float4 *quat;          // [n] stored quaternions in record order
     Node4 *nodes4;         // [n-1] the 4-wide hierarchy (node 0 the root)
+    NodeQ *nodesq;         // [n-1] the same nodes as the traversal loads them
     int32_t *f4;           // [n-1] binary node each 4-wide node was collapsed from
     int32_t *ctl4;         // [4] collapse state: level range [lo, hi), node count
     size_t bytes;
@@ -85,6 +86,7 @@ inline SceneWS carve_scene(void *base, int64_t n)
     w.acc = (float *)take(64 * nn);
     w.quat = (float4 *)take(16 * nn);
     w.nodes4 = (Node4 *)take(sizeof(Node4) * ni);
+    w.nodesq = (NodeQ *)take(sizeof(NodeQ) * ni);
     w.f4 = (int32_t *)take(4 * ni);
     w.ctl4 = (int32_t *)take(16);
     w.bytes = off;

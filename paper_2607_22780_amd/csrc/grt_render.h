@@ -486,7 +486,7 @@ struct ShadeTrace {
             return false;
         }
         const int spp = a.nc + a.ng + a.ne;
-        const int64_t p = r / spp;
+        const int64_t p = (uint32_t)r / (uint32_t)spp;  // fewer than 2^31 samples
         if (kHitList && a.hits) {
             const int64_t nray = (int64_t)a.H * a.W * spp;
             v.hl = a.hits + nray + r * a.hcap;
@@ -497,10 +497,6 @@ struct ShadeTrace {
         if constexpr (kPerRayArgs) bind(a, S);
         v.reset();
         w.start(S, x, d, a.tmin, INFINITY);
-        if (S.n <= 0) {
-            finish(a, r);
-            return false;
-        }
         return true;
     }
 
@@ -553,16 +549,12 @@ struct RelightTrace {
             a.contrib[r] = make_float4(0.f, 0.f, 0.f, 0.f);
             return false;
         }
-        const int64_t p = r / (a.nc + a.ng + a.ne);
+        const int64_t p = (uint32_t)r / (uint32_t)(a.nc + a.ng + a.ne);  // fewer than 2^31 samples
         const float3 x = make_float3(a.x[3 * p], a.x[3 * p + 1], a.x[3 * p + 2]);
         const float3 d = make_float3(r0.x, r0.y, r0.z);
         if constexpr (kPerRayArgs) bind(a, S);
         v.reset();
         w.start(S, x, d, a.tmin, INFINITY);
-        if (S.n <= 0) {
-            finish(a, r);
-            return false;
-        }
         return true;
     }
 

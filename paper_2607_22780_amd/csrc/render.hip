@@ -303,7 +303,7 @@ struct RenderBwdJob {
         const float4 r0 = a.rays[3 * r];
         if (r0.w == 0.0f) return skip(r);
         if (a.hits && a.hits[r] <= (uint32_t)a.hcap) return false;  // done from its stored list
-        const int64_t p = r / spp;
+        const int64_t p = (uint32_t)r / (uint32_t)spp;  // fewer than 2^31 samples
         const float inv = 1.0f / (float)spp;
         const float3 gp = make_float3(a.grad[3 * p] * inv, a.grad[3 * p + 1] * inv, a.grad[3 * p + 2] * inv);
         if (gp.x == 0.0f && gp.y == 0.0f && gp.z == 0.0f) return skip(r);

@@ -369,6 +369,51 @@ __device__ __forceinline__ float box_area(const float *b)
     return dx * dy + dy * dz + dz * dx;
 }
 
+// The NodeQ of m child boxes (lo xyz, hi xyz).  Per axis, a grid of 256 planes
+// over the children's union; each child takes the grid planes just outside
+// its own, at least `margin` (2^-20 of the union's extent) away: the walk
+// computes a plane's depth with an error below 2^-22 of that extent when the
+// ray starts inside it, and below 2^-22 of the depth otherwise.  Checked
+// against the arithmetic of the walk, so rounding here cannot shrink a box.
+__device__ __forceinline__ NodeQ quantize_node(const float (&box)[4][6], const int (&ref)[4], int m)
+{
+    NodeQ q;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        float lo = box[0][a], hi = box[0][3 + a];
+#pragma unroll
+        for (int j = 1; j < 4; ++j)
+            if (j < m) {
+                lo = fminf(lo, box[j][a]);
+                hi = fmaxf(hi, box[j][3 + a]);
+            }
+        const float margin = (hi - lo) * 9.5367431640625e-07f;
+        const float org = lo - 2.0f * margin;
+        float scale = (hi + 2.0f * margin - org) * (1.0f / 255.0f) * 1.000001f;
+        if (fmaf(255.0f, scale, org) < hi + margin) scale *= 1.00001f;
+        q.org[a] = org;
+        q.scale[a] = scale;
+        uint32_t wl = 0, wh = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (j >= m) continue;
+            const float l = box[j][a] - margin, h = box[j][3 + a] + margin;
+            // (a NaN plane, of a surfel with NaN parameters, keeps the whole span)
+            int ql = (int)fminf(fmaxf(floorf((l - org) / scale), 0.0f), 255.0f);
+            int qh = (int)fminf(fmaxf(ceilf((h - org) / scale), 0.0f), 255.0f);
+            if (ql > 0 && !(fmaf((float)ql, scale, org) <= l)) --ql;
+            if (qh < 255 && !(fmaf((float)qh, scale, org) >= h)) ++qh;
+            if (!(scale > 0.0f && l <= h)) { ql = 0; qh = 255; }
+            wl |= (uint32_t)ql << (8 * j);
+            wh |= (uint32_t)qh << (8 * j);
+        }
+        q.lo[a] = wl;
+        q.hi[a] = wh;
+    }
+    q.ch = make_int4(ref[0], ref[1], ref[2], ref[3]);
+    return q;
+}
+
 __global__ void k_collapse_init(int32_t *__restrict__ ctl, int32_t *__restrict__ f4)
 {
     if (threadIdx.x == 0) {
@@ -388,7 +433,7 @@ __global__ void k_collapse_next(int32_t *__restrict__ ctl)
 }
 
 __global__ void __launch_bounds__(256) k_collapse(const Node *__restrict__ bin, Node4 *__restrict__ out,
-                                                   int32_t *__restrict__ f4, int32_t *ctl)
+                                                   NodeQ *__restrict__ outq, int32_t *__restrict__ f4, int32_t *ctl)
 {
     const int lo = ctl[0], hi = ctl[1];
     for (int i = lo + (int)(blockIdx.x * blockDim.x + threadIdx.x); i < hi; i += (int)(gridDim.x * blockDim.x)) {
@@ -433,21 +478,24 @@ __global__ void __launch_bounds__(256) k_collapse(const Node *__restrict__ bin, 
                 }
             }
             ch[j] = r;
+            ref[j] = r;
 #pragma unroll
             for (int a = 0; a < 6; ++a) lo4[4 * a + j] = j < m ? box[j][a] : 0.0f;
         }
         o.pad = make_int4(m, 0, 0, 0);
         out[i] = o;
+        outq[i] = quantize_node(box, ref, m);
     }
 }
 
-hipError_t launch_collapse4(int n, const Node *nodes, Node4 *nodes4, int32_t *f4, int32_t *ctl, hipStream_t st)
+hipError_t launch_collapse4(int n, const Node *nodes, Node4 *nodes4, NodeQ *nodesq, int32_t *f4, int32_t *ctl,
+                            hipStream_t st)
 {
     if (n <= 1) return hipSuccess;
     const int blocks = (int)std::min<int64_t>(1024, ((int64_t)n / 2 + 255) / 256);
     hipLaunchKernelGGL(k_collapse_init, dim3(1), dim3(64), 0, st, ctl, f4);
     for (int l = 0; l < kCollapseLevels; ++l) {
-        hipLaunchKernelGGL(k_collapse, dim3(blocks), dim3(256), 0, st, nodes, nodes4, f4, ctl);
+        hipLaunchKernelGGL(k_collapse, dim3(blocks), dim3(256), 0, st, nodes, nodes4, nodesq, f4, ctl);
         hipLaunchKernelGGL(k_collapse_next, dim3(1), dim3(64), 0, st, ctl);
     }
     return hipGetLastError();
@@ -526,7 +574,7 @@ hipError_t launch_scene_build(const grt_surfels &s, float alpha_min, const Scene
                            w.flags);
         hipLaunchKernelGGL(k_refit, dim3(gb), dim3(tb), 0, st, n, w.leaf_box, w.nodes, w.parent_int, w.parent_leaf,
                            w.flags);
-        return launch_collapse4(n, w.nodes, w.nodes4, w.f4, w.ctl4, st);
+        return launch_collapse4(n, w.nodes, w.nodes4, w.nodesq, w.f4, w.ctl4, st);
     }
     return hipGetLastError();
 }

@@ -54,10 +54,6 @@ struct TraceJob {
         v.reset();
         if (a.dump_id) { v.did = a.dump_id + r * a.cap; v.dtau = a.dump_tau + r * a.cap; v.cap = a.cap; }
         w.start(S, o, d, tmin, tmax);
-        if (S.n <= 0) {
-            finish(r);
-            return false;
-        }
         return true;
     }
 
@@ -150,10 +146,6 @@ struct TraceAttrJob {
         const float tmax = a.f.tmax_a ? a.f.tmax_a[r] : a.f.tmax;
         v.reset();
         w.start(S, o, d, tmin, tmax);
-        if (S.n <= 0) {
-            finish(r);
-            return false;
-        }
         return true;
     }
 
@@ -193,10 +185,6 @@ struct TraceGBufJob {
         const float tmax = a.f.tmax_a ? a.f.tmax_a[r] : a.f.tmax;
         v.reset();
         w.start(S, o, d, tmin, tmax);
-        if (S.n <= 0) {
-            finish(r);
-            return false;
-        }
         return true;
     }
 
