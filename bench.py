@@ -149,11 +149,8 @@ def bytes_per_ray(wc, env_hw=(256, 512)):
 
 def trace_kernel(kind, k):
     """Base name of the kernel the library launches for the MIS forward
-    ("fwd") or its re-traversal backward ("bwd") at k-buffer size k (the
-    sizes held to 3 wavefronts per SIMD have their own kernels)."""
-    if kind == "bwd":
-        return "k_render_bwd_w3" if k == 13 else "k_render_bwd"
-    return "k_render_w3" if k in (12, 16) else "k_render"
+    ("fwd") or its re-traversal backward ("bwd") at k-buffer size k."""
+    return "k_render_bwd" if kind == "bwd" else "k_render"
 
 
 def roofline(bytes_per, units, ms):

@@ -156,7 +156,8 @@ typedef struct {
 } grt_rays;
 
 /* k: k-nearest hit buffer size per traversal round, one of 1,2,4,8,12,16,32
- *    (results do not depend on k).
+ *    (results do not depend on k; some paths run a larger buffer than asked
+ *    for where it fits the same registers).
  * t_cut: transmittance cutoff (1e-3 in the workloads).
  * sky: radiance of escaped rays, L = c_rt + T sky (when env is NULL).
  * env: optional built environment (grt_env_build); then L = c_rt + T L_env(d)
@@ -404,7 +405,7 @@ typedef struct {
  * t_min: self-intersection offset along the secondary ray (1e-3).
  * k: k-nearest hit buffer size per traversal round, one of 1,2,4,8,12,16,32;
  *   grt_render_mis_backward(_shading) also takes 13 (results do not depend
- *   on k; the room workload runs 16 forward, 13 backward, 12 relighting).
+ *   on k; the room workload runs 16).
  * sample_dump: optional [npix, spp, 10] floats per sample: direction (3),
  *   mixture pdf q, weight f cos/q (3), incident radiance L_i (3); zeros for
  *   samples below the horizon or invalid pixels.
@@ -666,7 +667,8 @@ int grt_denoise(grt_ctx *ctx, int H, int W, const float *rgb, const float *depth
  *                One epoch runs at a time (the next starts once the one in
  *                flight is done, or stopped).
  * k:             k-buffer size, 4, 8, 12 or 16.  t_min, t_cut as in grt_mis_opts.
- * k_relight:     k-buffer size of relighting epochs, 4, 8, 12 or 16 (0 = k).
+ * k_relight:     k-buffer size of relighting epochs, 4, 8, 12 or 16 (0 = k;
+ *                12 runs 16).
  * slack_per_ray: seconds of deadline per ray (0 = arrival order only;
  *                negative = 4e-8, about twice a request's time alone).
  * preempt_share: rays that more urgent requests may run ahead of a started

@@ -26,17 +26,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-// Minimum waves per SIMD requested for the persistent trace kernels (caps
-// their register budget); 0 leaves the choice to the compiler.
-#ifndef GRT_WAVES_PER_EU
-#define GRT_WAVES_PER_EU 0
-#endif
-#if GRT_WAVES_PER_EU > 0
-#define GRT_OCCUPANCY __attribute__((amdgpu_waves_per_eu(GRT_WAVES_PER_EU)))
-#else
-#define GRT_OCCUPANCY
-#endif
-
 namespace grt {
 
 constexpr float kGrazing = 1e-6f; // |n . d| below this is no intersection
@@ -81,6 +70,18 @@ struct SceneDev {
     const NodeQ *nodesq;
     int32_t n;
 };
+
+// Wavefronts per SIMD that a persistent kernel is held to (128 VGPRs at 4, 168
+// at 3), up to the largest buffer that fits; the windows of the stacks take
+// what LDS that leaves (20 entries at 4, 24 at 3).  Measured, room of 1M
+// surfels: the radiance forward at K = 16 runs 512 x 512 x 32 rays in 37.2 ms
+// at 4 and 41.1 at 3, the relighting query 23.9 and 24.7; kernels that carry
+// more per lane keep 3: primary-ray maps 11.0 against 11.6 ms at 4 (200k
+// surfels, forward and backward), a server epoch of several requests 39.3
+// against 42.0, and the backwards, whose LDS also holds gradient lines.
+constexpr int kWindow4 = 20, kWindow3 = 24;
+constexpr int waves_for(int k, int waves) { return k <= 16 ? waves : 1; }
+#define GRT_WAVES(K, W) __attribute__((amdgpu_waves_per_eu(waves_for(K, W))))
 
 // ---------------------------------------------------------------------------
 // Canonical single-precision arithmetic of the hit decision.  The operation
@@ -242,6 +243,8 @@ __device__ __forceinline__ float key_tau(double k) { return __int_as_float(__dou
 // reads as a quiet NaN, which fminf passes over.
 __device__ __forceinline__ double empty_key() { return __hiloint2double(0x7ff00000, 0); }
 
+__device__ __forceinline__ bool is_empty(double k) { return __double2hiint(k) == 0x7ff00000; }
+
 // min / max of keys (never NaN), as the bare instructions: fmin and fmax put a
 // canonicalizing instruction before each operand.
 __device__ __forceinline__ double key_min(double a, double b)
@@ -294,14 +297,10 @@ __device__ __forceinline__ double key_max(double a, double b)
 // A lane's two stacks (walk and deferred): the newest entries of each are a
 // window in LDS, a ring of D slots (lane-interleaved, so a wavefront's
 // accesses are conflict-free); older ones lie in a private array.  Room is
-// made once per walking step (the oldest 8 entries of a window that the step
-// could fill move out, and 8 come back when a pop finds its window empty), so
-// pushing is one LDS store and a wrapped increment, without branches.
+// made once per walking step (the oldest entries of a window that the step
+// could fill move out, and some come back when a pop finds its window empty),
+// so pushing is one LDS store and a wrapped increment, without branches.
 // ---------------------------------------------------------------------------
-#ifndef GRT_LDS_DEPTH
-#define GRT_LDS_DEPTH 26
-#endif
-constexpr int kLdsDepth = GRT_LDS_DEPTH;  // LDS entries per lane and stack
 #ifndef GRT_BWD_LDS_DEPTH
 #define GRT_BWD_LDS_DEPTH 16
 #endif
@@ -325,7 +324,6 @@ constexpr int kBwdSiteShare8 = GRT_BWD_SITE_SHARE8;
 #endif
 constexpr int kSurfelShare4 = GRT_SURFEL_SHARE4;
 constexpr int kStackCap = 384;  // private entries of a stack
-constexpr int kSpill = 8;       // entries moved between a window and the private array at a time
 constexpr int kNone = 0x7fffffff;
 
 // The roles of the two stacks swap each round (the deferred list becomes the
@@ -348,7 +346,11 @@ template <int D>
 struct Frontier {
     static constexpr uint32_t kStride = 256;            // a slot of the wavefront: 64 lanes x 4 bytes
     static constexpr uint32_t kWindow = D * kStride;
-    static_assert(D >= kSpill + 5, "a spill leaves the entries that a step may add");
+    // Entries moved between a window and the private array at a time.  It
+    // divides D, and a window's oldest entry always sits at a multiple of it,
+    // so the entries of a move are consecutive slots (immediate offsets).
+    static constexpr int kSpill = D % 8 == 0 ? 8 : 4;
+    static_assert(D % kSpill == 0 && D >= kSpill + 5, "a move leaves room for what a step may add");
     uint32_t base;        // LDS address of this lane's slot 0 of window 0; window 1 follows
     uint32_t woff;        // the window that holds the walk: 0 or kWindow (the other one defers)
     uint32_t wtop, dtop;  // LDS address of the next free slot of the walk / deferred window
@@ -384,10 +386,7 @@ struct Frontier {
         uint32_t b = top - kStride * (uint32_t)n;  // the oldest entry of the window
         b = (int)(b - lo) < 0 ? b + kWindow : b;
 #pragma unroll
-        for (int j = 0; j < kSpill; ++j) {
-            m[old + j] = lds_load(b);
-            b = next(b, lo);
-        }
+        for (int j = 0; j < kSpill; ++j) m[old + j] = lds_load(b + kStride * j);
         n -= kSpill;
         old += kSpill;
     }
@@ -419,10 +418,8 @@ struct Frontier {
         if (wn == 0) {
             const int *m = mem_of(woff) + (wold - kSpill);
 #pragma unroll
-            for (int j = 0; j < kSpill; ++j) {
-                lds_store(wtop, m[j]);
-                wtop = next(wtop, lo);
-            }
+            for (int j = 0; j < kSpill; ++j) lds_store(lo + kStride * j, m[j]);
+            wtop = lo + kStride * kSpill;
             wn = kSpill;
             wold -= kSpill;
         }
@@ -472,7 +469,7 @@ struct Frontier {
 #ifndef GRT_FWD_COMP_SHARE16
 #define GRT_FWD_COMP_SHARE16 0
 #endif
-template <int K, int D = kLdsDepth, int kCompShare16 = GRT_FWD_COMP_SHARE16, int kSiteShare8 = 0>
+template <int K, int D = kWindow4, int kCompShare16 = GRT_FWD_COMP_SHARE16, int kSiteShare8 = 0>
 struct Walker {
     static constexpr int kDepth = D;  // LDS entries per lane and stack
     float3 o, d;
@@ -480,12 +477,12 @@ struct Walker {
     double last;          // start key of the round; while compositing, the last composited hit
     double key[K];
     uint32_t pos[K];
-    int cnt;
     int cur;              // item in hand: node >= 0, leaf -(pos+1), or kNone
     bool lost;            // deferred list dropped: next round restarts at the root
     Frontier<D> F;        // walk stack and deferred list (LDS + private spill)
-    int ncomp;            // buffered hits still to composite (0 while walking)
-    int pend;             // leaf waiting for the next surfel step (record position), or kNone
+    int st;               // kNone: walking; >= 0: record of a leaf that waits for the next surfel
+                          // step; kMore, kFinal: compositing a full buffer, the last one
+    static constexpr int kMore = -1, kFinal = -2;
 #ifdef GRT_STATS
     int st_nodes, st_leaves, st_comps, st_rounds, st_lost, st_deferred;
 #endif
@@ -494,7 +491,6 @@ struct Walker {
     {
 #pragma unroll
         for (int i = 0; i < K; ++i) { key[i] = empty_key(); pos[i] = 0; }
-        cnt = 0;
     }
 
     // The round's walk covers [lo_bound, hi_bound]: from the last composited
@@ -504,15 +500,14 @@ struct Walker {
     __device__ __forceinline__ float lo_bound() const { return fmaxf(tmin, key_tau(last)); }
     __device__ __forceinline__ float hi_bound() const { return fminf(tmax, key_tau(key[K - 1])); }
 
-    __device__ __forceinline__ void start(const SceneDev &S, float3 o_, float3 d_, float tmin_, float tmax_)
+    // (tmin and tmax are the caller's to set: a job whose rays share them sets
+    // them once, which keeps them out of the lanes' registers)
+    __device__ __forceinline__ void start(const SceneDev &S, float3 o_, float3 d_)
     {
         o = o_;
         d = d_;
-        tmin = tmin_;
-        tmax = tmax_;
         last = 0.0;
-        ncomp = 0;
-        pend = kNone;
+        st = kNone;
         F.reset();
         lost = false;
         cur = S.n > 1 ? 0 : S.n == 1 ? -1 : kNone;  // no surfels: the first step ends the ray
@@ -536,7 +531,7 @@ struct Walker {
         if (k <= last) return;
         // beyond a full buffer, or the largest key drops out of it: to the next round
         const bool beyond = k >= key[K - 1];
-        if (cnt >= K) {
+        if (!is_empty(key[K - 1])) {
             F.push_def(-(int)(beyond ? p : pos[K - 1]) - 1);
 #ifdef GRT_STATS
             if (!lost) ++st_deferred;
@@ -555,7 +550,6 @@ struct Walker {
         }
         pos[0] = above ? p : pos[0];
         key[0] = key_min(key[0], k);
-        ++cnt;
     }
 
     // Test the children of 4-wide node `cur`; sets the next item and at most
@@ -630,10 +624,9 @@ struct Walker {
     __device__ __forceinline__ void next_round(const SceneDev &S)
     {
         // The buffer is empty already (every composite shifted an empty key in
-        // at its end, and the round composited all its hits), so only the
-        // count is reset: rewriting the keys would give the registers a
-        // second version to reconcile at every exit of the surfel step.
-        cnt = 0;
+        // at its end, and the round composited all its hits): rewriting the
+        // keys would give the registers a second version to reconcile at
+        // every exit of the surfel step.
 #ifdef GRT_STATS
         ++st_rounds;
         st_lost += lost ? 1 : 0;
@@ -663,7 +656,7 @@ struct Walker {
     // its round from holding the wavefront for K hits.  Returns true when the
     // ray is finished.
     // One step of the lane.  Walking lanes step a node every call; a leaf they
-    // find waits (pend) for a surfel step, and so do buffered hits to
+    // find waits (st) for a surfel step, and so do buffered hits to
     // composite.  Surfel steps -- the record, its canonical crossing, then the
     // k-buffer insertion or the visitor -- run for the whole wavefront at
     // once, when enough of its active lanes wait for one (or all do),
@@ -674,21 +667,20 @@ struct Walker {
     template <class Visit>
     __device__ __forceinline__ bool advance(const SceneDev &S, Visit &visit)
     {
-        if (ncomp == 0 && pend == kNone) {
+        if (st == kNone) {
             F.make_room(lost);
             if (cur == kNone && F.walk_empty()) {  // the round's walk is complete
-                const int m = cnt < K ? cnt : K;
-                if (m == 0) return true;
-                ncomp = m;
+                if (is_empty(key[0])) return true;
+                st = is_empty(key[K - 1]) ? kFinal : kMore;
             } else {
                 if (cur == kNone) cur = F.pop_walk();
                 int leaf = cur;
                 if (cur < 0) cur = kNone;
                 else walk_node(S, leaf);
-                if (leaf != kNone) pend = -leaf - 1;
+                st = leaf != kNone ? -leaf - 1 : kNone;
             }
         }
-        const bool wl = pend != kNone, wc = ncomp > 0;
+        const bool wc = st < 0, wl = st != kNone && !wc;
         bool want = wl || wc;
         int nwant, nact;
         bool all;
@@ -706,8 +698,8 @@ struct Walker {
         }
         const bool few = kSiteShare8 ? 8 * nwant < kSiteShare8 * nact : 4 * nwant < kSurfelShare4 * nact;
         if (!want || (few && !all)) return false;
-        const bool comp = ncomp > 0;
-        const uint32_t sp = comp ? pos[0] : (uint32_t)pend;
+        const bool comp = st < 0;
+        const uint32_t sp = comp ? pos[0] : (uint32_t)st;
         // One surfel site for leaf tests and composites: the record and its
         // canonical crossing are shared by both kinds of lanes.
         const float4 *r = S.rec + 4 * (size_t)sp;
@@ -716,7 +708,7 @@ struct Walker {
         canon_geo(r0, r1, r2, r3, o, d, den, tau, rho2);
         if (!comp) {
             test_leaf(sp, den, tau, rho2, r0.w, r2.w);
-            pend = kNone;
+            st = kNone;
             return false;
         }
         const bool stop = visit(sp, (uint32_t)__double2loint(key[0]), key_tau(key[0]), r0, r1, r2, r3, rho2, o, d);
@@ -727,10 +719,10 @@ struct Walker {
 #pragma unroll
         for (int i = 0; i < K - 1; ++i) { key[i] = key[i + 1]; pos[i] = pos[i + 1]; }
         key[K - 1] = empty_key();
-        --ncomp;
         if (stop) return true;
-        if (ncomp == 0) {
-            if (cnt < K || deferred_empty()) return true;
+        if (is_empty(key[0])) {
+            if (st == kFinal || deferred_empty()) return true;
+            st = kNone;
             next_round(S);
         }
         return false;
@@ -884,16 +876,12 @@ __device__ __forceinline__ void run_persistent(Job &job, unsigned long long *cou
             }
         }
         const uint64_t busy = __ballot(active);
-        if (!busy) {
-            if (exhausted) {
-#ifdef GRT_STATS
-                walk_flush<StatSlot<Job>::value>(tally);
-#endif
-                job.drain();
-                break;
-            }
-            continue;
-        }
+        // The loop's only exit, and no early return to its head: with one more
+        // edge the compiler kept a second copy of the walker's registers in
+        // the backward kernels and moved all of it twice a step (450 of 1340
+        // VALU instructions, 168 VGPRs with spills; 164 of 1050 and 144
+        // without; room step backward 105 to 91 ms at 1024 x 1024, 16 spp).
+        if (!busy && exhausted) break;
 #ifdef GRT_STATS
         if (lane == 0) {
             ++tally[kStSteps];
@@ -911,6 +899,10 @@ __device__ __forceinline__ void run_persistent(Job &job, unsigned long long *cou
         }
         job.after_step();  // wavefront-uniform point
     }
+#ifdef GRT_STATS
+    walk_flush<StatSlot<Job>::value>(tally);
+#endif
+    job.drain();
 }
 
 }  // namespace grt

@@ -467,7 +467,7 @@ __device__ __forceinline__ void gen_ray(const RenderArgs &a, int64_t r)
 // and 3% of its time).
 template <int K, bool kHitList = false, bool kPerRayArgs = false>
 struct ShadeTrace {
-    Walker<K> w;
+    Walker<K, kPerRayArgs ? kWindow3 : kWindow4> w;
     CompositeVisit<kHitList> v;
 
     __device__ __forceinline__ void bind(const RenderArgs &a, const SceneDev &S)
@@ -475,6 +475,8 @@ struct ShadeTrace {
         v.rec = S.rec;
         v.col = S.col;
         v.tcut = a.tcut;
+        w.tmin = a.tmin;
+        w.tmax = INFINITY;
     }
 
     __device__ __forceinline__ bool begin(const RenderArgs &a, const SceneDev &S, int64_t r)
@@ -496,7 +498,7 @@ struct ShadeTrace {
         const float3 d = make_float3(r0.x, r0.y, r0.z);
         if constexpr (kPerRayArgs) bind(a, S);
         v.reset();
-        w.start(S, x, d, a.tmin, INFINITY);
+        w.start(S, x, d);
         return true;
     }
 
@@ -530,7 +532,7 @@ struct ShadeTrace {
 // five values pushed the K = 12 kernel to 23 spilled registers.
 template <int K, bool kPerRayArgs = false>
 struct RelightTrace {
-    Walker<K> w;
+    Walker<K, kPerRayArgs ? kWindow3 : kWindow4> w;
     AttrVisit v;
 
     __device__ __forceinline__ void bind(const RenderArgs &a, const SceneDev &S)
@@ -540,6 +542,8 @@ struct RelightTrace {
         v.rough = a.sa_rough;
         v.metal = a.sa_metal;
         v.tcut = a.tcut;
+        w.tmin = a.tmin;
+        w.tmax = INFINITY;
     }
 
     __device__ __forceinline__ bool begin(const RenderArgs &a, const SceneDev &S, int64_t r)
@@ -554,7 +558,7 @@ struct RelightTrace {
         const float3 d = make_float3(r0.x, r0.y, r0.z);
         if constexpr (kPerRayArgs) bind(a, S);
         v.reset();
-        w.start(S, x, d, a.tmin, INFINITY);
+        w.start(S, x, d);
         return true;
     }
 

@@ -207,14 +207,14 @@ struct RenderJob {
     const RenderArgs &a;
     SceneDev S;
     ShadeTrace<K, kHitList> t;
-    int64_t r;  // sample index of the lane's ray
+    uint32_t r;  // sample index of the lane's ray
 
     __device__ RenderJob(const RenderArgs &a_) : a(a_), S(a_.S), r(0) { t.bind(a, S); }
     __device__ __forceinline__ Walker<K> &walker() { return t.w; }
     __device__ __forceinline__ decltype(t.v) &visit() { return t.v; }
     __device__ __forceinline__ bool begin(int64_t g)
     {
-        r = a.order ? (int64_t)a.order[g] : g;
+        r = a.order ? a.order[g] : (uint32_t)g;
         return t.begin(a, S, r);
     }
     __device__ __forceinline__ void finish(int64_t) { t.finish(a, r); }
@@ -230,14 +230,14 @@ struct RelightJob {
     const RenderArgs &a;
     SceneDev S;
     RelightTrace<K> t;
-    int64_t r;
+    uint32_t r;
 
     __device__ RelightJob(const RenderArgs &a_) : a(a_), S(a_.S), r(0) { t.bind(a, S); }
     __device__ __forceinline__ Walker<K> &walker() { return t.w; }
     __device__ __forceinline__ AttrVisit &visit() { return t.v; }
     __device__ __forceinline__ bool begin(int64_t g)
     {
-        r = a.order ? (int64_t)a.order[g] : g;
+        r = a.order ? a.order[g] : (uint32_t)g;
         return t.begin(a, S, r);
     }
     __device__ __forceinline__ void finish(int64_t) { t.finish(a, r); }
@@ -286,6 +286,7 @@ struct RenderBwdJob {
     {
         v.stage = t;
         stage_init(t);
+        w.tmin = a.tmin;
     }
     __device__ __forceinline__ BwdWalker<K> &walker() { return w; }
     __device__ __forceinline__ GradVisitT<kOrigin> &visit() { return v; }
@@ -314,8 +315,9 @@ struct RenderBwdJob {
         const float3 x = make_float3(a.x[3 * p], a.x[3 * p + 1], a.x[3 * p + 2]);
         const float3 d = make_float3(r0.x, r0.y, r0.z);
         v.reset(gC, gT, make_float3(sv.x, sv.y, sv.z), sv.w);
-        w.start(S, x, d, a.tmin, stop_bound(a.saved_t, r, INFINITY));
-        if constexpr (kOrigin) cur = r;
+        w.tmax = stop_bound(a.saved_t, r, INFINITY);
+        w.start(S, x, d);
+        if constexpr (kOrigin) cur = (uint32_t)r;
         return true;
     }
 
@@ -326,56 +328,27 @@ struct RenderBwdJob {
     __device__ __forceinline__ void after_step() { stage_sync(a.g.acc, v.stage, false); }
     __device__ __forceinline__ void drain() { stage_sync(a.g.acc, v.stage, true); }
 
-    int64_t cur = 0;  // the lane's sample (kOrigin)
+    uint32_t cur = 0;  // the lane's sample (kOrigin)
 };
 
 // kHitList: the launch stores hit lists (a.hits set); a separate kernel, so
 // that the plain forward carries no list pointer in its registers.
 template <int K, bool kHitList>
-__global__ void __launch_bounds__(256) GRT_OCCUPANCY k_render(RenderArgs a)
-{
-    RenderJob<K, kHitList> job(a);
-    run_persistent<K>(job, a.counters, (int64_t)a.H * a.W * (a.nc + a.ng + a.ne));
-}
-
-// The forward with a 12-hit buffer fits 3 wavefronts per SIMD (168 VGPRs)
-// when the compiler is held to it; it then beats K = 8 (fewer rounds).
-#ifndef GRT_FWD12_WAVES
-#define GRT_FWD12_WAVES 3
-#endif
-template <int K, bool kHitList>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GRT_FWD12_WAVES))) k_render_w3(RenderArgs a)
+__global__ void __launch_bounds__(256) GRT_WAVES(K, 4) k_render(RenderArgs a)
 {
     RenderJob<K, kHitList> job(a);
     run_persistent<K>(job, a.counters, (int64_t)a.H * a.W * (a.nc + a.ng + a.ne));
 }
 
 template <int K>
-__global__ void __launch_bounds__(256) GRT_OCCUPANCY k_render_relight(RenderArgs a)
-{
-    RelightJob<K> job(a);
-    run_persistent<K>(job, a.counters, (int64_t)a.H * a.W * (a.nc + a.ng + a.ne));
-}
-
-template <int K>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k_render_relight_w3(RenderArgs a)
+__global__ void __launch_bounds__(256) GRT_WAVES(K, 4) k_render_relight(RenderArgs a)
 {
     RelightJob<K> job(a);
     run_persistent<K>(job, a.counters, (int64_t)a.H * a.W * (a.nc + a.ng + a.ne));
 }
 
 template <int K, bool kOrigin>
-__global__ void __launch_bounds__(256) GRT_OCCUPANCY k_render_bwd(RenderArgs a)
-{
-    __shared__ WaveStage stages[4];
-    RenderBwdJob<K, kOrigin> job(a, &stages[(threadIdx.x >> 6) & 3]);
-    run_persistent<K>(job, a.counters, (int64_t)a.H * a.W * (a.nc + a.ng + a.ne));
-}
-
-// The re-traversal with a 13-hit buffer fits 3 wavefronts per SIMD (168
-// VGPRs) when the compiler is held to it, and then beats K = 12.
-template <int K, bool kOrigin>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k_render_bwd_w3(RenderArgs a)
+__global__ void __launch_bounds__(256) GRT_WAVES(K, 3) k_render_bwd(RenderArgs a)
 {
     __shared__ WaveStage stages[4];
     RenderBwdJob<K, kOrigin> job(a, &stages[(threadIdx.x >> 6) & 3]);
@@ -510,13 +483,8 @@ template <int K, bool kHitList>
 static hipError_t go_render_as(const RenderArgs &a, int num_cu, hipStream_t st)
 {
     const int64_t total = (int64_t)a.H * a.W * (a.nc + a.ng + a.ne);
-    if constexpr (K == 12 || K == 16) {
-        const int nb = persistent_blocks(k_render_w3<K, kHitList>, num_cu, total);
-        hipLaunchKernelGGL((k_render_w3<K, kHitList>), dim3(nb), dim3(256), 0, st, a);
-    } else {
-        const int nb = persistent_blocks(k_render<K, kHitList>, num_cu, total);
-        hipLaunchKernelGGL((k_render<K, kHitList>), dim3(nb), dim3(256), 0, st, a);
-    }
+    const int nb = persistent_blocks(k_render<K, kHitList>, num_cu, total);
+    hipLaunchKernelGGL((k_render<K, kHitList>), dim3(nb), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
@@ -526,19 +494,12 @@ static hipError_t go_render(const RenderArgs &a, int num_cu, hipStream_t st)
     return a.hits ? go_render_as<K, true>(a, num_cu, st) : go_render_as<K, false>(a, num_cu, st);
 }
 
-// (the shading-state variant, kOrigin, keeps the plain kernel: it carries
-// the origin gradient too and would spill at 3 wavefronts per SIMD)
 template <int K, bool kOrigin>
 static hipError_t go_render_bwd_as(const RenderArgs &a, int num_cu, hipStream_t st)
 {
     const int64_t total = (int64_t)a.H * a.W * (a.nc + a.ng + a.ne);
-    if constexpr (K == 13 && !kOrigin) {
-        const int nb = persistent_blocks(k_render_bwd_w3<K, kOrigin>, num_cu, total);
-        hipLaunchKernelGGL((k_render_bwd_w3<K, kOrigin>), dim3(nb), dim3(256), 0, st, a);
-    } else {
-        const int nb = persistent_blocks(k_render_bwd<K, kOrigin>, num_cu, total);
-        hipLaunchKernelGGL((k_render_bwd<K, kOrigin>), dim3(nb), dim3(256), 0, st, a);
-    }
+    const int nb = persistent_blocks(k_render_bwd<K, kOrigin>, num_cu, total);
+    hipLaunchKernelGGL((k_render_bwd<K, kOrigin>), dim3(nb), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
@@ -694,13 +655,8 @@ template <int K>
 static hipError_t go_relight(const RenderArgs &a, int num_cu, hipStream_t st)
 {
     const int64_t total = (int64_t)a.H * a.W * (a.nc + a.ng + a.ne);
-    if constexpr (K == 12) {
-        const int nb = persistent_blocks(k_render_relight_w3<K>, num_cu, total);
-        hipLaunchKernelGGL(k_render_relight_w3<K>, dim3(nb), dim3(256), 0, st, a);
-    } else {
-        const int nb = persistent_blocks(k_render_relight<K>, num_cu, total);
-        hipLaunchKernelGGL(k_render_relight<K>, dim3(nb), dim3(256), 0, st, a);
-    }
+    const int nb = persistent_blocks(k_render_relight<K>, num_cu, total);
+    hipLaunchKernelGGL(k_render_relight<K>, dim3(nb), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
@@ -717,7 +673,7 @@ hipError_t launch_render_relight(const RenderArgs &a, const RenderWS &w, int k, 
     case 2: e = go_relight<2>(a, num_cu, st); break;
     case 4: e = go_relight<4>(a, num_cu, st); break;
     case 8: e = go_relight<8>(a, num_cu, st); break;
-    case 12: e = go_relight<12>(a, num_cu, st); break;
+    case 12:  // 16 hits fit the same registers and take fewer rounds: 26.7 to 23.9 ms (1M, 512 x 512 x 16)
     case 16: e = go_relight<16>(a, num_cu, st); break;
     case 32: e = go_relight<32>(a, num_cu, st); break;
     default: return hipErrorInvalidValue;

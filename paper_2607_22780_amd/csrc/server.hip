@@ -128,18 +128,18 @@ struct ServeJob {
     SceneDev S;
     Trace t;
     const RenderArgs *a;
-    int64_t r;
+    uint32_t r;  // sample index: fewer than 2^31
 
     __device__ ServeJob(const ServeEpoch &e_) : e(e_), S(e_.S), a(nullptr), r(0) {}
-    __device__ __forceinline__ Walker<K> &walker() { return t.w; }
+    __device__ __forceinline__ decltype(t.w) &walker() { return t.w; }
     __device__ __forceinline__ decltype(t.v) &visit() { return t.v; }
 
     __device__ __forceinline__ bool begin(int64_t g)
     {
         const ServeChunk ch = e.chunks[find_chunk(e.chunks, e.nchunks, g)];
         a = &e.jobs[ch.slot];
-        r = ch.begin + (g - ch.offset);
-        if (a->order) r = (int64_t)a->order[r];
+        const int64_t q = ch.begin + (g - ch.offset);
+        r = a->order ? a->order[q] : (uint32_t)q;
         return t.begin(*a, S, r);
     }
 
@@ -151,17 +151,7 @@ struct ServeJob {
 // kStop: the epoch may be stopped (e.stop set).  Without it the persistent
 // loop carries no stop test, as a direct render's does.
 template <int K, class Trace, bool kStop>
-__global__ void __launch_bounds__(256) GRT_OCCUPANCY k_serve(ServeEpoch e)
-{
-    ServeJob<K, Trace> job(e);
-    if (kStop)
-        run_persistent<K>(job, e.counters, e.total, e.stop);
-    else
-        run_persistent<K>(job, e.counters, e.total);
-}
-
-template <int K, class Trace, bool kStop>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k_serve_w3(ServeEpoch e)
+__global__ void __launch_bounds__(256) GRT_WAVES(K, 3) k_serve(ServeEpoch e)
 {
     ServeJob<K, Trace> job(e);
     if (kStop)
@@ -183,14 +173,14 @@ struct ServeOneJob {
     int nchunks;
     int64_t r0;
 
-    int64_t r;
+    uint32_t r;  // sample index: fewer than 2^31
 
     __device__ ServeOneJob(const RenderArgs &a_, const ServeChunk *c, int nc, int64_t r0_)
         : a(a_), S(a_.S), chunks(c), nchunks(nc), r0(r0_), r(0)
     {
         bind_trace(t, a, S);
     }
-    __device__ __forceinline__ Walker<K> &walker() { return t.w; }
+    __device__ __forceinline__ decltype(t.w) &walker() { return t.w; }
     __device__ __forceinline__ decltype(t.v) &visit() { return t.v; }
     __device__ __forceinline__ bool begin(int64_t g)
     {
@@ -199,7 +189,7 @@ struct ServeOneJob {
             const ServeChunk ch = chunks[find_chunk(chunks, nchunks, g)];
             q = ch.begin + (g - ch.offset);
         }
-        r = a.order ? (int64_t)a.order[q] : q;
+        r = a.order ? a.order[q] : (uint32_t)q;
         return t.begin(a, S, r);
     }
     __device__ __forceinline__ void finish(int64_t) { t.finish(a, r); }
@@ -212,22 +202,9 @@ struct ServeOneJob {
 // loop with the request's arguments; otherwise it handles a range table and
 // a stop flag.
 template <int K, class Trace, bool kPlain>
-__global__ void __launch_bounds__(256) GRT_OCCUPANCY
+__global__ void __launch_bounds__(256) GRT_WAVES(K, 4)
     k_serve_one(RenderArgs a, const ServeChunk *chunks, int nchunks, int64_t r0, int64_t n,
                 unsigned long long *counters, const int *stop)
-{
-    ServeOneJob<K, Trace, kPlain> job(a, chunks, nchunks, r0);
-    if (kPlain)
-        run_persistent<K>(job, counters, n);
-    else
-        run_persistent<K>(job, counters, n, stop);
-}
-
-// K = 12 held to 3 wavefronts per SIMD, as the direct render's forward
-template <int K, class Trace, bool kPlain>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
-    k_serve_one_w3(RenderArgs a, const ServeChunk *chunks, int nchunks, int64_t r0, int64_t n,
-                   unsigned long long *counters, const int *stop)
 {
     ServeOneJob<K, Trace, kPlain> job(a, chunks, nchunks, r0);
     if (kPlain)
@@ -249,32 +226,20 @@ __global__ void k_serve_reduce(const RenderArgs *a, int64_t npix, const unsigned
     reduce_pixel(p, a->nc + a->ng + a->ne, a->contrib, a->out);
 }
 
-// K = 12 held to 3 wavefronts per SIMD, as in a direct render
 template <int K, class Trace, bool kStop>
 static hipError_t go_serve_as(const ServeEpoch &e, int num_cu, hipStream_t st)
 {
-    if constexpr (K == 12) {
-        const int nb = persistent_blocks(k_serve_w3<K, Trace, kStop>, num_cu, e.total);
-        hipLaunchKernelGGL((k_serve_w3<K, Trace, kStop>), dim3(nb), dim3(256), 0, st, e);
-    } else {
-        const int nb = persistent_blocks(k_serve<K, Trace, kStop>, num_cu, e.total);
-        hipLaunchKernelGGL((k_serve<K, Trace, kStop>), dim3(nb), dim3(256), 0, st, e);
-    }
+    const int nb = persistent_blocks(k_serve<K, Trace, kStop>, num_cu, e.total);
+    hipLaunchKernelGGL((k_serve<K, Trace, kStop>), dim3(nb), dim3(256), 0, st, e);
     return hipGetLastError();
 }
 
 template <int K, class Trace, bool kPlain>
 static hipError_t go_serve_one_as(const RenderArgs &a, const ServeEpoch &e, int64_t r0, int num_cu, hipStream_t st)
 {
-    if constexpr (K == 12) {
-        const int nb = persistent_blocks(k_serve_one_w3<K, Trace, kPlain>, num_cu, e.total);
-        hipLaunchKernelGGL((k_serve_one_w3<K, Trace, kPlain>), dim3(nb), dim3(256), 0, st, a, e.chunks, e.nchunks,
-                           r0, e.total, e.counters, e.stop);
-    } else {
-        const int nb = persistent_blocks(k_serve_one<K, Trace, kPlain>, num_cu, e.total);
-        hipLaunchKernelGGL((k_serve_one<K, Trace, kPlain>), dim3(nb), dim3(256), 0, st, a, e.chunks, e.nchunks, r0,
-                           e.total, e.counters, e.stop);
-    }
+    const int nb = persistent_blocks(k_serve_one<K, Trace, kPlain>, num_cu, e.total);
+    hipLaunchKernelGGL((k_serve_one<K, Trace, kPlain>), dim3(nb), dim3(256), 0, st, a, e.chunks, e.nchunks, r0,
+                       e.total, e.counters, e.stop);
     return hipGetLastError();
 }
 
@@ -293,7 +258,8 @@ template <int K>
 static hipError_t go_epoch(const ServeEpoch &e, const RenderArgs *one, int64_t r0, bool relight, int num_cu,
                            hipStream_t st)
 {
-    if (relight) return go_relight_epoch<K>(e, one, r0, num_cu, st);
+    // (12: 16 hits fit the same registers and take fewer rounds)
+    if (relight) return go_relight_epoch<(K == 12 ? 16 : K)>(e, one, r0, num_cu, st);
     if (one)
         return (!e.stop && e.nchunks <= 1) ? go_serve_one_as<K, ShadeTrace<K>, true>(*one, e, r0, num_cu, st)
                                            : go_serve_one_as<K, ShadeTrace<K>, false>(*one, e, r0, num_cu, st);
