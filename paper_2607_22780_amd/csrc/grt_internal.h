@@ -42,19 +42,17 @@ struct SceneWS {
     float4 *col;
     Node *nodes;
     float *leaf_box;   // [n,6] sorted order
-    float *box_tmp;    // [n,6] surfel order
+    float *pyr;        // [< n + 32, 6] boxes of runs of 2, 4, 8, ... leaves
     uint32_t *keys0, *keys1, *vals0, *vals1;
-    int32_t *parent_int;   // [n-1]
-    int32_t *parent_leaf;  // [n]
-    uint32_t *flags;       // [n-1]
     uint32_t *hist;        // [256 * blocks]
     int32_t *bounds;       // [8]
     float *acc;            // [n,16] gradient lines of the backward passes
     float4 *quat;          // [n] stored quaternions in record order
     Node4 *nodes4;         // [n-1] the 4-wide hierarchy (node 0 the root)
     NodeQ *nodesq;         // [n-1] the same nodes as the traversal loads them
-    int32_t *f4;           // [n-1] binary node each 4-wide node was collapsed from
-    int32_t *ctl4;         // [4] collapse state: level range [lo, hi), node count
+    int32_t *queue;        // [n-1] collapse: binary nodes that 4-wide nodes start from
+    uint32_t *mark;        // [n] collapse: marks of those, then their numbers
+    int32_t *ctl4;         // [4] collapse: the level [lo, hi) the top left, node count
     size_t bytes;
 };
 
@@ -73,21 +71,19 @@ inline SceneWS carve_scene(void *base, int64_t n)
     w.col = (float4 *)take(16 * nn);
     w.nodes = (Node *)take(sizeof(Node) * ni);
     w.leaf_box = (float *)take(24 * nn);
-    w.box_tmp = (float *)take(24 * nn);
+    w.pyr = (float *)take(24 * (nn + 32));
     w.keys0 = (uint32_t *)take(4 * nn);
     w.keys1 = (uint32_t *)take(4 * nn);
     w.vals0 = (uint32_t *)take(4 * nn);
     w.vals1 = (uint32_t *)take(4 * nn);
-    w.parent_int = (int32_t *)take(4 * ni);
-    w.parent_leaf = (int32_t *)take(4 * nn);
-    w.flags = (uint32_t *)take(4 * ni);
     w.hist = (uint32_t *)take(4 * sort_hist_words(n));
     w.bounds = (int32_t *)take(4 * 8);
     w.acc = (float *)take(64 * nn);
     w.quat = (float4 *)take(16 * nn);
     w.nodes4 = (Node4 *)take(sizeof(Node4) * ni);
     w.nodesq = (NodeQ *)take(sizeof(NodeQ) * ni);
-    w.f4 = (int32_t *)take(4 * ni);
+    w.queue = (int32_t *)take(4 * ni);
+    w.mark = (uint32_t *)take(4 * nn);
     w.ctl4 = (int32_t *)take(16);
     w.bytes = off;
     return w;
@@ -228,8 +224,9 @@ hipError_t launch_env_build(const float *rgb, int H, int W, const EnvWS &w, hipS
 hipError_t launch_bounds_reset(int32_t *bounds, hipStream_t st);
 hipError_t launch_morton_sort(int n, const float *centres, const int32_t *bounds, uint32_t *keys0, uint32_t *vals0,
                               uint32_t *keys1, uint32_t *vals1, uint32_t *hist, hipStream_t st);
-hipError_t launch_hierarchy_refit(int n, const uint32_t *keys, const float *leaf_box, Node *nodes, int32_t *parent_int,
-                                  int32_t *parent_leaf, uint32_t *flags, hipStream_t st);
+// mark: [n] words cleared for the collapse to 4-wide nodes (null: none)
+hipError_t launch_hierarchy(int n, const uint32_t *keys, const float *leaf_box, float *pyr, Node *nodes, uint32_t *mark,
+                            hipStream_t st);
 
 // Triangle mesh for the mesh backend of the attribute query (mesh.hip):
 // records in Morton order, 48 B each: (v0, triangle id bits), (e1, 0), (e2, 0).
@@ -237,11 +234,10 @@ struct MeshWS {
     float4 *rec;
     Node *nodes;
     float *leaf_box;  // [nf,6] sorted order
-    float *box_tmp;   // [nf,6] triangle order
+    float *box_tmp;   // [nf,6] triangle order, then the boxes of runs of leaves [< nf + 32, 6]
     float *centre;    // [nf,3]
     uint32_t *keys0, *keys1, *vals0, *vals1;
-    int32_t *parent_int, *parent_leaf;
-    uint32_t *flags, *hist;
+    uint32_t *hist;
     int32_t *bounds;
     size_t bytes;
 };
@@ -259,15 +255,12 @@ inline MeshWS carve_mesh(void *base, int64_t nf)
     w.rec = (float4 *)take(48 * n);
     w.nodes = (Node *)take(sizeof(Node) * ni);
     w.leaf_box = (float *)take(24 * n);
-    w.box_tmp = (float *)take(24 * n);
+    w.box_tmp = (float *)take(24 * (n + 32));
     w.centre = (float *)take(12 * n);
     w.keys0 = (uint32_t *)take(4 * n);
     w.keys1 = (uint32_t *)take(4 * n);
     w.vals0 = (uint32_t *)take(4 * n);
     w.vals1 = (uint32_t *)take(4 * n);
-    w.parent_int = (int32_t *)take(4 * ni);
-    w.parent_leaf = (int32_t *)take(4 * n);
-    w.flags = (uint32_t *)take(4 * ni);
     w.hist = (uint32_t *)take(4 * sort_hist_words((int64_t)n));
     w.bounds = (int32_t *)take(4 * 8);
     w.bytes = off;

@@ -94,7 +94,7 @@ hipError_t launch_mesh_build(int nv, const float *verts, int nf, const int32_t *
         return e;
     hipLaunchKernelGGL(k_tri_records, dim3(gb), dim3(tb), 0, st, nv, verts, nf, tris, w.vals0, w.box_tmp, w.rec,
                        w.leaf_box);
-    return launch_hierarchy_refit(nf, w.keys0, w.leaf_box, w.nodes, w.parent_int, w.parent_leaf, w.flags, st);
+    return launch_hierarchy(nf, w.keys0, w.leaf_box, w.box_tmp, w.nodes, nullptr, st);
 }
 
 // Moller-Trumbore (two-sided) with a fixed operation order; true on a hit
