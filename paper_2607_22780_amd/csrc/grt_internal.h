@@ -100,6 +100,7 @@ struct EnvWS {
     float *marg;   // [H+1]
     float *cond;   // [H,W+1]
     double *rows;  // [H]
+    double *dirs;  // [3 H + 2 W] texel angles of the prefiltering, by row and column
     float *Ed;     // [kPfH, kPfW, 3]
     float *Es;     // [kPfL - 1, kPfH, kPfW, 3]
     float *lut;    // [kLutN, kLutN, 2]
@@ -118,6 +119,7 @@ inline EnvWS carve_env(void *base, int H, int W)
     w.marg = (float *)take(4 * (size_t)(H + 1));
     w.cond = (float *)take(4 * (size_t)H * (size_t)(W + 1));
     w.rows = (double *)take(8 * (size_t)H);
+    w.dirs = (double *)take(8 * (3 * (size_t)H + 2 * (size_t)W));
     w.Ed = (float *)take(4 * (size_t)kPfH * kPfW * 3);
     w.Es = (float *)take(4 * (size_t)(kPfL - 1) * kPfH * kPfW * 3);
     w.lut = (float *)take(4 * (size_t)kLutN * kLutN * 2);

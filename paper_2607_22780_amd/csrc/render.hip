@@ -23,51 +23,93 @@ constexpr float kPi = 3.14159265358979323846f;
 // Environment proposal tables: texel weight = luminance x sin(theta_centre);
 // cumulative sums in double, left to right, rounded to float at the end.
 // ---------------------------------------------------------------------------
-__global__ void k_env_rows(int H, int W, const float *__restrict__ rgb, float *__restrict__ cond,
-                           double *__restrict__ rows)
+// The sums are a serial chain by definition (left to right), so what surrounds
+// the chain is taken off it (93 to 7 us for 128 x 256 with a thread per row, the
+// marginal 21 to 4): a block loads and weights a chunk in parallel,
+// one thread adds it up in LDS, and the block divides and stores.  Rows longer
+// than a chunk go over it twice, since the quotients need the row's total.
+constexpr int kCdfChunk = 1024;
+
+// x[0..m) in LDS to its running sums, left to right, from acc on; returns the
+// last.  One thread; eight loads are in flight ahead of the additions.
+__device__ __forceinline__ double run_sums(double *x, int m, double acc)
 {
 #pragma clang fp contract(off)
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= H) return;
-    const double st = sin(3.14159265358979323846 * (i + 0.5) / H);
-    double acc = 0.0;
-    for (int j = 0; j < W; ++j) {
-        const float *p = rgb + ((size_t)i * W + j) * 3;
-        double lum = 0.2126 * (double)p[0] + 0.7152 * (double)p[1] + 0.0722 * (double)p[2];
-        acc += lum * st;
+    int j = 0;
+    for (; j + 8 <= m; j += 8) {
+        double v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = x[j + k];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            acc += v[k];
+            x[j + k] = acc;
+        }
     }
-    rows[i] = acc;
-    float *cr = cond + (size_t)i * (W + 1);
-    cr[0] = 0.0f;
-    double run = 0.0;
-    for (int j = 0; j < W; ++j) {
-        const float *p = rgb + ((size_t)i * W + j) * 3;
-        double lum = 0.2126 * (double)p[0] + 0.7152 * (double)p[1] + 0.0722 * (double)p[2];
-        run += lum * st;
-        cr[j + 1] = acc > 0.0 ? (float)(run / acc) : (float)((double)(j + 1) / W);
+    for (; j < m; ++j) {
+        acc += x[j];
+        x[j] = acc;
     }
-    cr[W] = 1.0f;
+    return acc;
 }
 
-__global__ void k_env_marginal(int H, const double *__restrict__ rows, float *__restrict__ marg)
+// cdf[1..n] = running sums of val over their total (uniform steps where that
+// is 0), cdf[0] = 0, cdf[n] = 1; returns the total.  A block of 256.
+template <class Val>
+__device__ __forceinline__ double block_cdf(int n, Val val, double *x, double *carry, float *__restrict__ cdf)
 {
 #pragma clang fp contract(off)
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double tot = 0.0;
-    for (int i = 0; i < H; ++i) tot += rows[i];
-    double acc = 0.0;
-    marg[0] = 0.0f;
-    for (int i = 0; i < H; ++i) {
-        acc += rows[i];
-        marg[i + 1] = tot > 0.0 ? (float)(acc / tot) : (float)((double)(i + 1) / H);
+    const bool once = n <= kCdfChunk;
+    double total = 0.0;
+    for (int pass = once ? 1 : 0; pass < 2; ++pass) {
+        if (threadIdx.x == 0) *carry = 0.0;
+        for (int base = 0; base < n; base += kCdfChunk) {
+            const int m = min(kCdfChunk, n - base);
+            for (int j = threadIdx.x; j < m; j += 256) x[j] = val(base + j);
+            __syncthreads();
+            if (threadIdx.x == 0) *carry = run_sums(x, m, *carry);
+            __syncthreads();
+            if (once) total = *carry;
+            if (pass == 1)
+                for (int j = threadIdx.x; j < m; j += 256)
+                    cdf[base + j + 1] = base + j + 1 == n ? 1.0f
+                                        : total > 0.0     ? (float)(x[j] / total)
+                                                          : (float)((double)(base + j + 1) / n);
+            __syncthreads();
+        }
+        total = *carry;
+        __syncthreads();
     }
-    marg[H] = 1.0f;
+    if (threadIdx.x == 0) cdf[0] = 0.0f;
+    return total;
+}
+
+__global__ void __launch_bounds__(256) k_env_rows(int H, int W, const float *__restrict__ rgb, float *__restrict__ cond,
+                                                  double *__restrict__ rows)
+{
+#pragma clang fp contract(off)
+    __shared__ double x[kCdfChunk], carry;
+    const int i = blockIdx.x;
+    const double st = sin(3.14159265358979323846 * (i + 0.5) / H);
+    const float *p = rgb + (size_t)i * W * 3;
+    auto val = [&](int j) {
+        const double lum = 0.2126 * (double)p[3 * j] + 0.7152 * (double)p[3 * j + 1] + 0.0722 * (double)p[3 * j + 2];
+        return lum * st;
+    };
+    const double total = block_cdf(W, val, x, &carry, cond + (size_t)i * (W + 1));
+    if (threadIdx.x == 0) rows[i] = total;
+}
+
+__global__ void __launch_bounds__(256) k_env_marginal(int H, const double *__restrict__ rows, float *__restrict__ marg)
+{
+    __shared__ double x[kCdfChunk], carry;
+    block_cdf(H, [&](int i) { return rows[i]; }, x, &carry, marg);
 }
 
 hipError_t launch_env_build(const float *rgb, int H, int W, const EnvWS &w, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_env_rows, dim3((H + 63) / 64), dim3(64), 0, st, H, W, rgb, w.cond, w.rows);
-    hipLaunchKernelGGL(k_env_marginal, dim3(1), dim3(64), 0, st, H, w.rows, w.marg);
+    hipLaunchKernelGGL(k_env_rows, dim3(H), dim3(256), 0, st, H, W, rgb, w.cond, w.rows);
+    hipLaunchKernelGGL(k_env_marginal, dim3(1), dim3(256), 0, st, H, w.rows, w.marg);
     return hipGetLastError();
 }
 
@@ -79,54 +121,91 @@ hipError_t launch_env_build(const float *rgb, int H, int W, const EnvWS &w, hipS
 //   E_d(n)    = sum L max(0, n.l) dW / sum max(0, n.l) dW
 //   E_s(R, r) = sum L D(h) max(0, R.l) dW / sum D(h) max(0, R.l) dW,
 //               h = normalize(R + l), GGX D with alpha = r^2.
-// One wavefront per table texel: lanes split the environment's texels, then
-// a fixed-order tree in LDS sums the lanes.
+// A ratio of sums does not see a common factor of its weights, and for unit
+// vectors (n.h)^2 = (1 + n.l) / 2, so a level's weight is max(0, R.l) dW / t^2
+// with t = (1 + n.l) / 2 (a2 - 1) + 1: no square root, and one reciprocal.
+// Bound by double-precision issue.  The texels' angles come from a table per
+// row and column (three trigonometric calls a texel and entry were most of the
+// time), and a block of four wavefronts shares a table texel: 512 wavefronts
+// left half of the chip's SIMDs idle.  128 x 256 map: 728 to 82 us.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(64) k_env_prefilter(int H, int W, const float *__restrict__ rgb,
-                                                      float *__restrict__ Ed, float *__restrict__ Es)
+// rows: sin and cos of the polar angle and the solid angle of a texel there;
+// columns: cos and sin of the azimuth (at texel centres).
+__global__ void __launch_bounds__(256) k_env_dirs(int H, int W, double *__restrict__ dirs)
 {
 #pragma clang fp contract(off)
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < H) {
+        const double th = kPiD * (i + 0.5) / H;
+        dirs[i] = sin(th);
+        dirs[H + i] = cos(th);
+        dirs[2 * (size_t)H + i] = 2.0 * kPiD / W * (cos(kPiD * i / H) - cos(kPiD * (i + 1) / H));
+    } else if (i - H < W) {
+        const double ph = 2.0 * kPiD * (i - H + 0.5) / W;
+        dirs[2 * (size_t)H + i] = cos(ph);
+        dirs[2 * (size_t)H + W + i] = sin(ph);
+    }
+}
+
+// 1 / x to the last bits: the hardware's estimate and two Newton steps.
+__device__ __forceinline__ double fast_recip(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+
+__global__ void __launch_bounds__(256) k_env_prefilter(int H, int W, const float *__restrict__ rgb,
+                                                       const double *__restrict__ dirs, float *__restrict__ Ed,
+                                                       float *__restrict__ Es)
+{
     constexpr int kAcc = 4 + 4 * (kPfL - 1);  // diffuse (L, weight), then each level
-    __shared__ double part[kAcc][64];
-    const int t = blockIdx.x, lane = threadIdx.x;
+    __shared__ double part[4][kAcc];
+    const int t = blockIdx.x;
     const double tth = kPiD * ((t / kPfW) + 0.5) / kPfH, tph = 2.0 * kPiD * ((t % kPfW) + 0.5) / kPfW;
     const V3 nt = v3(sin(tth) * cos(tph), cos(tth), sin(tth) * sin(tph));
     double acc[kAcc];
 #pragma unroll
     for (int q = 0; q < kAcc; ++q) acc[q] = 0.0;
-    for (int k = lane; k < H * W; k += 64) {
-        const int i = k / W, j = k - i * W;
-        const double th = kPiD * (i + 0.5) / H, ph = 2.0 * kPiD * (j + 0.5) / W;
-        const V3 l = v3(sin(th) * cos(ph), cos(th), sin(th) * sin(ph));
-        const double c = dot(nt, l);
-        if (!(c > 0.0)) continue;
-        const double om = 2.0 * kPiD / W * (cos(kPiD * i / H) - cos(kPiD * (i + 1) / H));
-        const float *L = rgb + (size_t)k * 3;
-        const double w = c * om;
-        acc[0] += w * L[0]; acc[1] += w * L[1]; acc[2] += w * L[2]; acc[3] += w;
-        const double ndh = dot(nt, normalized(v3(nt.x + l.x, nt.y + l.y, nt.z + l.z)));
+    const double *st = dirs, *ct = dirs + H, *om = dirs + 2 * (size_t)H, *cp = dirs + 3 * (size_t)H, *sp = cp + W;
+    const int total = H * W, rows = 256 / W, cols = 256 - rows * W;  // a step of 256 texels
+    int i = (int)threadIdx.x / W, j = (int)threadIdx.x - i * W;
+    for (int k = threadIdx.x; k < total; k += 256) {
+        const double c = nt.x * (st[i] * cp[j]) + nt.y * ct[i] + nt.z * (st[i] * sp[j]);
+        if (c > 0.0) {
+            const float *L = rgb + (size_t)k * 3;
+            const double Lx = L[0], Ly = L[1], Lz = L[2], w = c * om[i];
+            acc[0] += w * Lx; acc[1] += w * Ly; acc[2] += w * Lz; acc[3] += w;
+            const double nh2 = 0.5 + 0.5 * c;
 #pragma unroll
-        for (int lv = 1; lv < kPfL; ++lv) {
-            const double r = (double)lv / (kPfL - 1), al = r * r;
-            const double wl = ggx_D(ndh, al * al) * w;
-            double *s = acc + 4 * lv;
-            s[0] += wl * L[0]; s[1] += wl * L[1]; s[2] += wl * L[2]; s[3] += wl;
+            for (int lv = 1; lv < kPfL; ++lv) {
+                const double r = (double)lv / (kPfL - 1), a2 = r * r * r * r;
+                const double x = nh2 * (a2 - 1.0) + 1.0;
+                const double wl = w * fast_recip(x * x);
+                double *s = acc + 4 * lv;
+                s[0] += wl * Lx; s[1] += wl * Ly; s[2] += wl * Lz; s[3] += wl;
+            }
         }
+        i += rows;
+        j += cols;
+        if (j >= W) { j -= W; ++i; }
     }
 #pragma unroll
-    for (int q = 0; q < kAcc; ++q) part[q][lane] = acc[q];
+    for (int q = 0; q < kAcc; ++q) {
+        for (int m = 32; m >= 1; m >>= 1) acc[q] += __shfl_xor(acc[q], m, 64);
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6][q] = acc[q];
+    }
     __syncthreads();
-    for (int half = 32; half > 0; half >>= 1) {
-        if (lane < half)
-            for (int q = 0; q < kAcc; ++q) part[q][lane] += part[q][lane + half];
-        __syncthreads();
-    }
-    if (lane < 3) {
-        Ed[t * 3 + lane] = part[3][0] > 0.0 ? (float)(part[lane][0] / part[3][0]) : 0.0f;
-        for (int lv = 1; lv < kPfL; ++lv) {
-            const double wsum = part[4 * lv + 3][0];
-            Es[((size_t)(lv - 1) * kPfH * kPfW + t) * 3 + lane] = wsum > 0.0 ? (float)(part[4 * lv + lane][0] / wsum) : 0.0f;
+    if (threadIdx.x < 3 * kPfL) {
+        const int lv = threadIdx.x / 3, c = threadIdx.x - 3 * lv;
+        double s = 0.0, w = 0.0;
+        for (int k = 0; k < 4; ++k) {
+            s += part[k][4 * lv + c];
+            w += part[k][4 * lv + 3];
         }
+        const float v = w > 0.0 ? (float)(s / w) : 0.0f;
+        if (lv == 0) Ed[t * 3 + c] = v;
+        else Es[((size_t)(lv - 1) * kPfH * kPfW + t) * 3 + c] = v;
     }
 }
 
@@ -135,49 +214,56 @@ __global__ void __launch_bounds__(64) k_env_prefilter(int H, int W, const float 
 //   A = E[g (1 - (1 - v.h)^5)],  B = E[g (1 - v.h)^5],  g = G (v.h) / (mu n.h),
 // over half vectors h distributed as D(h) n.h (the inverse GGX distribution
 // on a kLutQ x kLutQ midpoint grid of (xi, azimuth)), l = reflect(v, h) above
-// the horizon.  One workgroup per cell, one azimuth row per thread, a
-// fixed-order tree over the rows.
+// the horizon.  v lies in the xz plane, so only the azimuth's cosine enters
+// and the two halves of the circle are equal: a thread takes one xi and the
+// 128 azimuths of one half, whose cosines the block keeps in LDS (a sine and a
+// cosine per node took most of 417 us; 57 now).  Bound by double-precision
+// issue.
 __global__ void __launch_bounds__(256) k_dfg_lut(float *__restrict__ lut)
 {
-#pragma clang fp contract(off)
-    static_assert(kLutQ == 256, "one thread per quadrature row");
-    __shared__ double pa[256], pb[256];
+    static_assert(kLutQ == 256, "one thread per xi");
+    __shared__ double cp[kLutQ / 2], part[4][2];
     const int cell = blockIdx.x, i = cell / kLutN, j = cell % kLutN, s = threadIdx.x;
+    if (s < kLutQ / 2) cp[s] = cos(2.0 * kPiD * (s + 0.5) / kLutQ);
+    __syncthreads();
     const double mu = (i + 0.5) / kLutN, r = (j + 0.5) / kLutN, al = r * r, a2 = al * al;
-    const V3 v = v3(sqrt(1.0 - mu * mu), 0.0, mu);
     const double xi = (s + 0.5) / kLutQ;
     const double c2 = (1.0 - xi) / (1.0 + (a2 - 1.0) * xi);
     const double ct = sqrt(c2), st = sqrt(1.0 - c2 > 0.0 ? 1.0 - c2 : 0.0);
-    const double g1v = smith_G1(mu, a2);
+    const double vx = sqrt(1.0 - mu * mu) * st, vz = mu * ct;
     double A = 0.0, B = 0.0;
-    for (int t = 0; t < kLutQ; ++t) {
-        const double ph = 2.0 * kPiD * (t + 0.5) / kLutQ;
-        const V3 h = v3(st * cos(ph), st * sin(ph), ct);
-        const double vh = dot(v, h);
-        if (!(vh > 0.0)) continue;
-        const double nl = 2.0 * vh * h.z - v.z;
-        if (!(nl > 0.0)) continue;
-        const double g = smith_G1(nl, a2) * g1v * vh / (mu * ct);
-        const double x = 1.0 - vh, fc = x * x * x * x * x;
-        A += g * (1.0 - fc);
-        B += g * fc;
+    for (int t = 0; t < kLutQ / 2; ++t) {
+        const double vh = vx * cp[t] + vz;
+        const double nl = 2.0 * vh * ct - mu;
+        if (vh > 0.0 && nl > 0.0) {
+            // G1(n.l) (v.h) / 2, the rest of g being constant in the azimuth
+            const double g = nl * vh * fast_recip(nl + sqrt(a2 + (1.0 - a2) * nl * nl));
+            const double x = 1.0 - vh, x2 = x * x, fc = x2 * x2 * x;
+            A += g * (1.0 - fc);
+            B += g * fc;
+        }
     }
-    pa[s] = A;
-    pb[s] = B;
+    const double f = 2.0 * smith_G1(mu, a2) / (mu * ct);
+    A *= f;
+    B *= f;
+    for (int m = 32; m >= 1; m >>= 1) {
+        A += __shfl_xor(A, m, 64);
+        B += __shfl_xor(B, m, 64);
+    }
+    if ((s & 63) == 0) {
+        part[s >> 6][0] = A;
+        part[s >> 6][1] = B;
+    }
     __syncthreads();
-    for (int half = 128; half > 0; half >>= 1) {
-        if (s < half) { pa[s] += pa[s + half]; pb[s] += pb[s + half]; }
-        __syncthreads();
-    }
-    if (s == 0) {
-        lut[2 * cell] = (float)(pa[0] / ((double)kLutQ * kLutQ));
-        lut[2 * cell + 1] = (float)(pb[0] / ((double)kLutQ * kLutQ));
-    }
+    if (s < 2)  // both halves of the circle
+        lut[2 * cell + s] = (float)(2.0 * ((part[0][s] + part[1][s]) + (part[2][s] + part[3][s])) /
+                                    ((double)kLutQ * kLutQ));
 }
 
 hipError_t launch_env_prefilter(const float *rgb, int H, int W, const EnvWS &w, hipStream_t st, bool lut)
 {
-    hipLaunchKernelGGL(k_env_prefilter, dim3(kPfH * kPfW), dim3(64), 0, st, H, W, rgb, w.Ed, w.Es);
+    hipLaunchKernelGGL(k_env_dirs, dim3((H + W + 255) / 256), dim3(256), 0, st, H, W, w.dirs);
+    hipLaunchKernelGGL(k_env_prefilter, dim3(kPfH * kPfW), dim3(256), 0, st, H, W, rgb, w.dirs, w.Ed, w.Es);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !lut) return e;
     return launch_dfg_lut(w.lut, st);
