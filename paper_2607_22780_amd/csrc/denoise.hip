@@ -13,12 +13,30 @@
 // Image-space stencil: a workgroup stages its 16x16 pixels and an R-pixel
 // halo (colour, depth, unit normal, validity) in LDS once, so each input is
 // read from HBM about (16+2R)^2/256 times instead of (2R+1)^2 times.
+//
+// Bound by VALU issue: (2R+1)^2 weights a pixel.  So a weight's three factors
+// are one exponential of a summed base-2 exponent, with a hardware reciprocal
+// in the depth term; the normal term's logarithm is a short series near 1,
+// where sigma_n multiplies its error (two expf, a powf and a division per
+// weight took 3.5 times as long).
 #include "grt_internal.h"
 
 namespace grt {
 
 constexpr int kDnTile = 16;
 constexpr int kDnSpan = kDnTile + 2 * kDenoiseMaxRadius;
+
+// log2 of the cosine between two unit normals (0 where it is not positive).
+// Near 1 the hardware logarithm's absolute error is about that of its result
+// at 2, and sigma_n multiplies it; there 2 atanh(s), s = (c - 1) / (c + 1),
+// with terms up to s^7 (|s| < 1/7: the next is below 2^-26 of the sum).
+__device__ __forceinline__ float log2_cos(float c)
+{
+    const float s = (c - 1.0f) * __builtin_amdgcn_rcpf(c + 1.0f), s2 = s * s;
+    const float near1 = s * fmaf(s2, fmaf(s2, fmaf(s2, 2.8853901f / 7.0f, 2.8853901f / 5.0f), 2.8853901f / 3.0f), 2.8853901f);
+    const float l = c >= 0.75f ? near1 : __builtin_amdgcn_logf(c);
+    return c > 0.0f ? l : 0.0f;
+}
 
 __global__ void __launch_bounds__(256) k_denoise(DenoiseArgs a)
 {
@@ -64,17 +82,22 @@ __global__ void __launch_bounds__(256) k_denoise(DenoiseArgs a)
         return 0.0f;
     };
     const float gx = grad(1, 0), gy = grad(0, 1);
-    const float inv2s2 = 1.0f / (2.0f * a.sigma_s * a.sigma_s);
+    constexpr float kLog2e = 1.44269504f;
+    const float inv2s2 = kLog2e / (2.0f * a.sigma_s * a.sigma_s);
     float sr = 0.0f, sg = 0.0f, sb = 0.0f, sw = 0.0f;
     for (int dy = -R; dy <= R; ++dy)
         for (int dx = -R; dx <= R; ++dx) {
-            const float4 qn = ln[(ly + dy) * span + lx + dx];
-            if (qn.w == 0.0f) continue;
-            const float4 qc = lc[(ly + dy) * span + lx + dx];
-            const float ws = expf(-(float)(dx * dx + dy * dy) * inv2s2);
-            const float wd = expf(-fabsf(cc.w - qc.w) / (a.sigma_d * fabsf(gx * (float)dx + gy * (float)dy) + a.eps_d));
-            const float c = fmaxf(0.0f, cn.x * qn.x + cn.y * qn.y + cn.z * qn.z);
-            const float B = ws * wd * powf(c, a.sigma_n);
+            const int q = (ly + dy) * span + lx + dx;
+            const float4 qn = ln[q], qc = lc[q];
+            const float c = cn.x * qn.x + cn.y * qn.y + cn.z * qn.z;
+            // (kept above what the reciprocal can take)
+            const float scale = fmaxf(a.sigma_d * fabsf(gx * (float)dx + gy * (float)dy) + a.eps_d, 1e-37f);
+            float x = -(float)(dx * dx + dy * dy) * inv2s2;
+            x = fmaf(-kLog2e * fabsf(cc.w - qc.w), __builtin_amdgcn_rcpf(scale), x);
+            x = fmaf(a.sigma_n, log2_cos(c), x);
+            // (a zero base to the power 0 is 1)
+            const bool on = qn.w != 0.0f && (c > 0.0f || a.sigma_n == 0.0f);
+            const float B = on ? __builtin_amdgcn_exp2f(x) : 0.0f;
             sr += B * qc.x; sg += B * qc.y; sb += B * qc.z; sw += B;
         }
     const float inv = sw > 0.0f ? 1.0f / sw : 1.0f;
