@@ -737,7 +737,7 @@ int grt_mesh_trace_attr(const grt_mesh *mesh, const grt_rays *rays, const grt_ve
     grt::MeshTraceArgs a;
     a.n = rays->n;
     a.nv = (int)mesh->m.nv; a.nf = (int)mesh->m.nf;
-    a.rec = mesh->w.rec; a.nodes = mesh->w.nodes; a.tris = mesh->m.tris;
+    a.rec = mesh->w.rec; a.nodes = mesh->w.nodesq; a.tris = mesh->m.tris;
     a.o = rays->origins; a.d = rays->dirs; a.tmin = rays->t_min_all; a.tmax = rays->t_max_all;
     a.albedo = attrs->albedo; a.rough = attrs->rough; a.metal = attrs->metal; a.vnormal = attrs->normal;
     a.out_V = out_V; a.out_albedo = out_albedo; a.out_rough = out_rough; a.out_metal = out_metal;
@@ -857,7 +857,7 @@ int grt_render_relight_mesh(const grt_mesh *mesh, const grt_env *env, const grt_
     a.rl_nz = reinterpret_cast<float *>(w.k1);
     grt::MeshTraceArgs m{};
     m.nv = (int)mesh->m.nv; m.nf = (int)mesh->m.nf;
-    m.rec = mesh->w.rec; m.nodes = mesh->w.nodes; m.tris = mesh->m.tris;
+    m.rec = mesh->w.rec; m.nodes = mesh->w.nodesq; m.tris = mesh->m.tris;
     m.albedo = attrs->albedo; m.rough = attrs->rough; m.metal = attrs->metal; m.vnormal = attrs->normal;
     if ((rc = set_device(mesh->ctx))) return rc;
     hipError_t e = grt::launch_render_relight_mesh(a, m, (hipStream_t)stream);

@@ -229,6 +229,18 @@ __device__ __forceinline__ bool slab_q(uint32_t nx, uint32_t ny, uint32_t nz, ui
     return !(tn > tf * 1.0000005f + 1e-30f);
 }
 
+// One exchange of a sorting network: (sa, ca) takes the nearer of two children.
+__device__ __forceinline__ void exchange(float &sa, int &ca, float &sb, int &cb)
+{
+    const bool sw = sb < sa;
+    const float ts = sw ? sb : sa;
+    const int tc = sw ? cb : ca;
+    sb = sw ? sa : sb;
+    cb = sw ? ca : cb;
+    sa = ts;
+    ca = tc;
+}
+
 // The sort key of a hit, (bits(tau), id), held as the double with those bits:
 // a non-negative depth's bits order as its value does, tau is finite, so the
 // key is a finite non-negative double, and doubles of one sign order as their
@@ -590,20 +602,11 @@ struct Walker {
         // by entry depth, missed children last (a five-exchange sorting network)
         float s0 = k0 ? t0 : INFINITY, s1 = k1 ? t1 : INFINITY, s2 = k2 ? t2 : INFINITY, s3 = k3 ? t3 : INFINITY;
         int c0 = ch.x, c1 = ch.y, c2 = ch.z, c3 = ch.w;
-        auto xch = [](float &sa, int &ca, float &sb, int &cb) {
-            const bool sw = sb < sa;
-            const float ts = sw ? sb : sa;
-            const int tc = sw ? cb : ca;
-            sb = sw ? sa : sb;
-            cb = sw ? ca : cb;
-            sa = ts;
-            ca = tc;
-        };
-        xch(s0, c0, s1, c1);
-        xch(s2, c2, s3, c3);
-        xch(s0, c0, s2, c2);
-        xch(s1, c1, s3, c3);
-        xch(s1, c1, s2, c2);
+        exchange(s0, c0, s1, c1);
+        exchange(s2, c2, s3, c3);
+        exchange(s0, c0, s2, c2);
+        exchange(s1, c1, s3, c3);
+        exchange(s1, c1, s2, c2);
         const bool n0 = s0 <= thi, n1 = s1 <= thi, n2 = s2 <= thi, n3 = s3 <= thi;  // kept in this round
         const bool h0 = s0 <= tend, h1 = s1 <= tend, h2 = s2 <= tend, h3 = s3 <= tend;         // met by the ray
 #ifdef GRT_STATS

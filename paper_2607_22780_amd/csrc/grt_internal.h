@@ -230,6 +230,11 @@ hipError_t launch_morton_sort(int n, const float *centres, const int32_t *bounds
 hipError_t launch_hierarchy(int n, const uint32_t *keys, const float *leaf_box, float *pyr, Node *nodes, uint32_t *mark,
                             hipStream_t st);
 
+// Collapse to 4-wide nodes.  nodes4: the full-precision copy (null: none);
+// queue [n-1], mark [n] (cleared by launch_hierarchy), part [n], sums [n / 4096 + 1]
+hipError_t launch_collapse4(int n, const Node *nodes, Node4 *nodes4, NodeQ *nodesq, int32_t *queue, uint32_t *mark,
+                            uint32_t *part, uint32_t *sums, int32_t *ctl, hipStream_t st);
+
 // Triangle mesh for the mesh backend of the attribute query (mesh.hip):
 // records in Morton order, 48 B each: (v0, triangle id bits), (e1, 0), (e2, 0).
 struct MeshWS {
@@ -241,6 +246,10 @@ struct MeshWS {
     uint32_t *keys0, *keys1, *vals0, *vals1;
     uint32_t *hist;
     int32_t *bounds;
+    NodeQ *nodesq;    // [nf-1] the 4-wide nodes the query walks
+    int32_t *queue;   // [nf-1] as in SceneWS
+    uint32_t *mark;   // [nf]
+    int32_t *ctl4;    // [4]
     size_t bytes;
 };
 
@@ -265,6 +274,10 @@ inline MeshWS carve_mesh(void *base, int64_t nf)
     w.vals1 = (uint32_t *)take(4 * n);
     w.hist = (uint32_t *)take(4 * sort_hist_words((int64_t)n));
     w.bounds = (int32_t *)take(4 * 8);
+    w.nodesq = (NodeQ *)take(sizeof(NodeQ) * ni);
+    w.queue = (int32_t *)take(4 * ni);
+    w.mark = (uint32_t *)take(4 * n);
+    w.ctl4 = (int32_t *)take(16);
     w.bytes = off;
     return w;
 }
@@ -273,7 +286,7 @@ struct MeshTraceArgs {
     int64_t n;                       // rays
     int nv, nf;
     const float4 *rec;
-    const Node *nodes;
+    const NodeQ *nodes;
     const int32_t *tris;             // [nf,3]
     const float *o, *d;
     float tmin, tmax;

@@ -6,8 +6,8 @@
 // with the hit's barycentric weights.
 //
 // MI355X has no ray-tracing units, so the query is software: an LBVH over the
-// triangles' boxes, built with the surfel scene's Morton / radix-sort /
-// Karras / refit kernels, and a closest-hit traversal, one thread per ray,
+// triangles' boxes, built and collapsed to 4-wide quantized nodes with the
+// surfel scene's kernels, and a closest-hit traversal, one thread per ray,
 // nearer child first, pruned by the closest hit so far.
 #include "grt_internal.h"
 
@@ -94,7 +94,9 @@ hipError_t launch_mesh_build(int nv, const float *verts, int nf, const int32_t *
         return e;
     hipLaunchKernelGGL(k_tri_records, dim3(gb), dim3(tb), 0, st, nv, verts, nf, tris, w.vals0, w.box_tmp, w.rec,
                        w.leaf_box);
-    return launch_hierarchy(nf, w.keys0, w.leaf_box, w.box_tmp, w.nodes, nullptr, st);
+    if ((e = launch_hierarchy(nf, w.keys0, w.leaf_box, w.box_tmp, w.nodes, w.mark, st)) != hipSuccess) return e;
+    // (the sort's other keys and its histogram are free again)
+    return launch_collapse4(nf, w.nodes, nullptr, w.nodesq, w.queue, w.mark, w.keys1, w.hist, w.ctl4, st);
 }
 
 // Moller-Trumbore (two-sided) with a fixed operation order; true on a hit
@@ -119,21 +121,53 @@ __device__ __forceinline__ bool tri_hit(const float4 r0, const float4 r1, const 
     return t < tbest || __float_as_uint(r0.w) < best_id;
 }
 
-constexpr int kMeshStack = 64;  // LBVH depth <= 63: one far child per level
+// A ray's stack: entries (4-wide node or leaf, entry depth), the first
+// kMeshLds in LDS (lane-interleaved), deeper ones in a private array.  A node
+// leaves at most three siblings behind, on at most 63 levels.
+constexpr int kMeshLds = 12, kMeshDeep = 3 * 63 - kMeshLds;
+
+struct MeshStack {
+    int2 *lds;  // the thread's slot 0; slot i at lds[256 * i]
+    int2 *deep;
+    int sp;
+
+    __device__ __forceinline__ void push(int ref, float t)
+    {
+        const int2 e = make_int2(ref, __float_as_int(t));
+        if (sp < kMeshLds) lds[256 * sp] = e;
+        else deep[sp - kMeshLds] = e;
+        ++sp;
+    }
+    // the topmost entry not beyond `best`; kNone when there is none
+    __device__ __forceinline__ int pop(float best)
+    {
+        while (sp > 0) {
+            --sp;
+            const int2 e = sp < kMeshLds ? lds[256 * sp] : deep[sp - kMeshLds];
+            if (__int_as_float(e.y) <= best) return e.x;
+        }
+        return kNone;
+    }
+};
 
 // Closest hit of one ray: triangle id (0xffffffff: miss) and barycentrics.
-__device__ __forceinline__ void mesh_closest(const float4 *__restrict__ rec, const Node *__restrict__ nodes, int nf,
-                                             float3 o, float3 d, float tmin, float tmax, uint32_t &bid, float &bu,
-                                             float &bv)
+// Bound by the vector L1 like the surfel walk (one tag access per lane and 16
+// bytes of a divergent load): a 4-wide quantized node is four loads, as a
+// binary one was, for half the node steps.
+__device__ __forceinline__ void mesh_closest(const float4 *__restrict__ rec, const NodeQ *__restrict__ nodes, int nf,
+                                             float3 o, float3 d, float tmin, float tmax, MeshStack &stack,
+                                             uint32_t &bid, float &bu, float &bv)
 {
-    const float3 inv = make_float3(safe_inv(d.x), safe_inv(d.y), safe_inv(d.z));
+    const float3 inv = make_float3(fast_inv(d.x), fast_inv(d.y), fast_inv(d.z));
+    const bool gx = __float_as_int(d.x) < 0, gy = __float_as_int(d.y) < 0, gz = __float_as_int(d.z) < 0;
     float best = tmax;
     bu = 0.0f; bv = 0.0f;
     bid = 0xffffffffu;
-    int stack[kMeshStack];
-    int sp = 0;
+    stack.sp = 0;
     int cur = nf <= 0 ? kNone : (nf == 1 ? -1 : 0);
     while (cur != kNone) {
+        // (entry depths carry rounding: prune with some slack)
+        const float bound = best * 1.0000005f;
         if (cur < 0) {  // leaf: triangle record -(cur + 1)
             const float4 *rr = rec + 3 * (size_t)(-cur - 1);
             const float4 r0 = rr[0], r1 = rr[1], r2 = rr[2];
@@ -141,24 +175,36 @@ __device__ __forceinline__ void mesh_closest(const float4 *__restrict__ rec, con
             if (tri_hit(r0, r1, r2, o, d, tmin, best, bid, t, u, v)) {
                 best = t; bu = u; bv = v; bid = __float_as_uint(r0.w);
             }
-            cur = sp > 0 ? stack[--sp] : kNone;
+            cur = stack.pop(best * 1.0000005f);
             continue;
         }
-        const Node nd = nodes[cur];
-        float tl, tr;
-        const bool hl = slab(nd.a.x, nd.a.y, nd.a.z, nd.a.w, nd.b.x, nd.b.y, o, inv, tmin, best, tl);
-        const bool hr = slab(nd.b.z, nd.b.w, nd.c.x, nd.c.y, nd.c.z, nd.c.w, o, inv, tmin, best, tr);
-        if (hl && hr) {
-            const bool lf = tl <= tr;
-            if (sp < kMeshStack) stack[sp++] = lf ? nd.d.y : nd.d.x;
-            cur = lf ? nd.d.x : nd.d.y;
-        } else if (hl) {
-            cur = nd.d.x;
-        } else if (hr) {
-            cur = nd.d.y;
-        } else {
-            cur = sp > 0 ? stack[--sp] : kNone;
-        }
+        const float4 *nd = reinterpret_cast<const float4 *>(nodes + cur);
+        const float4 w0 = nd[0], w1 = nd[1], w2 = nd[2];
+        const int4 ch = *reinterpret_cast<const int4 *>(nd + 3);
+        const float3 start = make_float3((w0.x - o.x) * inv.x, (w0.y - o.y) * inv.y, (w0.z - o.z) * inv.z);
+        const float3 step = make_float3(w0.w * inv.x, w1.x * inv.y, w1.y * inv.z);
+        const uint32_t lx = __float_as_uint(w1.z), ly = __float_as_uint(w1.w), lz = __float_as_uint(w2.x);
+        const uint32_t hx = __float_as_uint(w2.y), hy = __float_as_uint(w2.z), hz = __float_as_uint(w2.w);
+        const uint32_t nx = gx ? hx : lx, fx = gx ? lx : hx;
+        const uint32_t ny = gy ? hy : ly, fy = gy ? ly : hy;
+        const uint32_t nz = gz ? hz : lz, fz = gz ? lz : hz;
+        float t0, t1, t2, t3;
+        const bool k0 = slab_q<0>(nx, ny, nz, fx, fy, fz, step, start, tmin, t0) & (t0 <= bound) & (ch.x != kNoChild);
+        const bool k1 = slab_q<1>(nx, ny, nz, fx, fy, fz, step, start, tmin, t1) & (t1 <= bound) & (ch.y != kNoChild);
+        const bool k2 = slab_q<2>(nx, ny, nz, fx, fy, fz, step, start, tmin, t2) & (t2 <= bound) & (ch.z != kNoChild);
+        const bool k3 = slab_q<3>(nx, ny, nz, fx, fy, fz, step, start, tmin, t3) & (t3 <= bound) & (ch.w != kNoChild);
+        int m = (int)k0 + (int)k1 + (int)k2 + (int)k3;
+        float s0 = k0 ? t0 : INFINITY, s1 = k1 ? t1 : INFINITY, s2 = k2 ? t2 : INFINITY, s3 = k3 ? t3 : INFINITY;
+        int c0 = k0 ? ch.x : kNone, c1 = k1 ? ch.y : kNone, c2 = k2 ? ch.z : kNone, c3 = k3 ? ch.w : kNone;
+        exchange(s0, c0, s1, c1);
+        exchange(s2, c2, s3, c3);
+        exchange(s0, c0, s2, c2);
+        exchange(s1, c1, s3, c3);
+        exchange(s1, c1, s2, c2);
+        if (m > 3) stack.push(c3, s3);
+        if (m > 2) stack.push(c2, s2);
+        if (m > 1) stack.push(c1, s1);
+        cur = m > 0 ? c0 : stack.pop(bound);
     }
 }
 
@@ -192,13 +238,16 @@ __device__ __forceinline__ MeshHitAttrs mesh_attrs(const int32_t *__restrict__ t
 
 __global__ void __launch_bounds__(256) k_mesh_trace_attr(MeshTraceArgs a)
 {
+    __shared__ int2 top[kMeshLds][256];
+    int2 deep[kMeshDeep];
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= a.n) return;
     const float3 o = make_float3(a.o[3 * r], a.o[3 * r + 1], a.o[3 * r + 2]);
     const float3 d = make_float3(a.d[3 * r], a.d[3 * r + 1], a.d[3 * r + 2]);
+    MeshStack stack = {&top[0][threadIdx.x], deep, 0};
     uint32_t bid;
     float bu, bv;
-    mesh_closest(a.rec, a.nodes, a.nf, o, d, a.tmin, a.tmax, bid, bu, bv);
+    mesh_closest(a.rec, a.nodes, a.nf, o, d, a.tmin, a.tmax, stack, bid, bu, bv);
     const MeshHitAttrs h = mesh_attrs(a.tris, a.nf, a.albedo, a.rough, a.metal, a.vnormal, bid, bu, bv, d);
     a.out_V[r] = h.V;
 #pragma unroll
@@ -211,36 +260,105 @@ __global__ void __launch_bounds__(256) k_mesh_trace_attr(MeshTraceArgs a)
 // render's ray records, the mesh query parked for the shading pass as the
 // surfel relight parks it ((V, albedo) in the contribution slot, (r, m) in
 // the ray record's spare words, the normal in rl_n*).
+// A block takes the samples of neighbouring pixels, kMeshTile of them, and
+// traces them in the order of their directions' bins (a counting sort in LDS):
+// a pixel's samples leave in all directions, and 64 of them in index order
+// share few nodes.  Everything else stays within the tile's records, so no
+// global sort and no scattered writes are paid for it.
+constexpr int kMeshTile = 2048;
+constexpr int kMeshBins = 257;  // 16 x 16 directions, then the untraced
+
+// octahedral direction bin, 16 x 16, along a Morton curve
+__device__ __forceinline__ int dir_bin(float4 d)
+{
+    const float s = fabsf(d.x) + fabsf(d.y) + fabsf(d.z);
+    float u = d.x / s, v = d.z / s;
+    if (d.y < 0.0f) {
+        const float uu = (1.0f - fabsf(v)) * (u >= 0.0f ? 1.0f : -1.0f);
+        const float vv = (1.0f - fabsf(u)) * (v >= 0.0f ? 1.0f : -1.0f);
+        u = uu;
+        v = vv;
+    }
+    const int iu = (int)fminf(fmaxf((u * 0.5f + 0.5f) * 16.0f, 0.0f), 15.0f);
+    const int iv = (int)fminf(fmaxf((v * 0.5f + 0.5f) * 16.0f, 0.0f), 15.0f);
+    auto spread = [](int x) { x = (x | (x << 2)) & 0x33; return (x | (x << 1)) & 0x55; };
+    return spread(iu) | (spread(iv) << 1);
+}
+
 __global__ void __launch_bounds__(256) k_mesh_relight_query(RenderArgs a, MeshTraceArgs m, int64_t total)
 {
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= total) return;
-    const float4 r0 = a.rays[3 * r];
-    if (r0.w == 0.0f) {
-        a.contrib[r] = make_float4(0.f, 0.f, 0.f, 0.f);
-        return;
+    __shared__ int2 top[kMeshLds][256];
+    __shared__ uint16_t order[kMeshTile];
+    __shared__ int count[kMeshBins], sums[4];
+    int2 deep[kMeshDeep];
+    const int64_t base = (int64_t)blockIdx.x * kMeshTile;
+    const int tile = (int)(total - base < kMeshTile ? total - base : kMeshTile);
+    constexpr int kPer = kMeshTile / 256;
+    for (int b = threadIdx.x; b < kMeshBins; b += 256) count[b] = 0;
+    __syncthreads();
+    int bin[kPer], rank[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int i = k * 256 + threadIdx.x;
+        if (i < tile) {
+            const float4 r0 = a.rays[3 * (base + i)];
+            bin[k] = r0.w == 0.0f ? kMeshBins - 1 : dir_bin(r0);
+            rank[k] = atomicAdd(&count[bin[k]], 1);
+        }
     }
-    const int64_t p = r / (a.nc + a.ng + a.ne);
-    const float3 x = make_float3(a.x[3 * p], a.x[3 * p + 1], a.x[3 * p + 2]);
-    const float3 d = make_float3(r0.x, r0.y, r0.z);
-    uint32_t bid;
-    float bu, bv;
-    mesh_closest(m.rec, m.nodes, m.nf, x, d, a.tmin, INFINITY, bid, bu, bv);
-    const MeshHitAttrs h = mesh_attrs(m.tris, m.nf, m.albedo, m.rough, m.metal, m.vnormal, bid, bu, bv, d);
-    a.contrib[r] = make_float4(h.V, h.A[0], h.A[1], h.A[2]);
-    float4 *r2 = a.rays + 3 * r + 2;
-    r2->z = h.R;
-    r2->w = h.M;
-    a.rl_nx[r] = h.N[0];
-    a.rl_ny[r] = h.N[1];
-    a.rl_nz[r] = h.N[2];
+    __syncthreads();
+    {   // exclusive prefix sum of the first 256 bins; the untraced come last
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        const int own = count[threadIdx.x];
+        int x = own;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int y = __shfl_up(x, off, 64);
+            if (lane >= off) x += y;
+        }
+        if (lane == 63) sums[wave] = x;
+        __syncthreads();
+        int before = x - own;
+        for (int w = 0; w < wave; ++w) before += sums[w];
+        count[threadIdx.x] = before;
+        if (threadIdx.x == 255) count[256] = before + own;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kPer; ++k)
+        if (k * 256 + (int)threadIdx.x < tile) order[count[bin[k]] + rank[k]] = (uint16_t)(k * 256 + threadIdx.x);
+    __syncthreads();
+    MeshStack stack = {&top[0][threadIdx.x], deep, 0};
+    for (int i = threadIdx.x; i < tile; i += 256) {
+        const int64_t r = base + order[i];
+        const float4 r0 = a.rays[3 * r];
+        if (r0.w == 0.0f) {
+            a.contrib[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+            continue;
+        }
+        const int64_t p = (uint32_t)r / (uint32_t)(a.nc + a.ng + a.ne);  // fewer than 2^31 samples
+        const float3 x = make_float3(a.x[3 * p], a.x[3 * p + 1], a.x[3 * p + 2]);
+        const float3 d = make_float3(r0.x, r0.y, r0.z);
+        uint32_t bid;
+        float bu, bv;
+        mesh_closest(m.rec, m.nodes, m.nf, x, d, a.tmin, INFINITY, stack, bid, bu, bv);
+        const MeshHitAttrs h = mesh_attrs(m.tris, m.nf, m.albedo, m.rough, m.metal, m.vnormal, bid, bu, bv, d);
+        a.contrib[r] = make_float4(h.V, h.A[0], h.A[1], h.A[2]);
+        float4 *r2 = a.rays + 3 * r + 2;
+        r2->z = h.R;
+        r2->w = h.M;
+        a.rl_nx[r] = h.N[0];
+        a.rl_ny[r] = h.N[1];
+        a.rl_nz[r] = h.N[2];
+    }
 }
 
 hipError_t launch_mesh_relight_query(const RenderArgs &a, const MeshTraceArgs &m, hipStream_t st)
 {
     const int64_t total = (int64_t)a.H * a.W * (a.nc + a.ng + a.ne);
     if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mesh_relight_query, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, a, m, total);
+    hipLaunchKernelGGL(k_mesh_relight_query, dim3((unsigned)((total + kMeshTile - 1) / kMeshTile)), dim3(256), 0, st, a,
+                       m, total);
     return hipGetLastError();
 }
 

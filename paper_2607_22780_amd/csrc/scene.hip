@@ -561,7 +561,7 @@ __device__ __forceinline__ void queue_children(const Collapsed &c, int32_t *q, u
 // node i is marked where it steps up behind i.
 __global__ void __launch_bounds__(256) k_collapse_write(int n, const Node *__restrict__ bin,
                                                         const uint32_t *__restrict__ num, int32_t *__restrict__ ctl,
-                                                        Node4 *__restrict__ out, NodeQ *__restrict__ outq)
+                                                        Node4 *out, NodeQ *__restrict__ outq)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n - 1) return;
@@ -581,7 +581,7 @@ __global__ void __launch_bounds__(256) k_collapse_write(int n, const Node *__res
     o.hz = make_float4(c.box[0][5], c.box[1][5], c.box[2][5], c.box[3][5]);
     o.ch = make_int4(c.ref[0], c.ref[1], c.ref[2], c.ref[3]);
     o.pad = make_int4(c.m, 0, 0, 0);
-    out[at] = o;
+    if (out) out[at] = o;
     outq[at] = quantize_node(c.box, c.ref, c.m);
 }
 
@@ -716,7 +716,6 @@ static void launch_scan(int total, uint32_t *x, uint32_t *sums, hipStream_t st)
     }
 }
 
-// mark: [n] words that k_hierarchy cleared; part: [n] words; sums: n / 4096 + 1
 hipError_t launch_collapse4(int n, const Node *nodes, Node4 *nodes4, NodeQ *nodesq, int32_t *queue, uint32_t *mark,
                             uint32_t *part, uint32_t *sums, int32_t *ctl, hipStream_t st)
 {
