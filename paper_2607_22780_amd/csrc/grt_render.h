@@ -144,46 +144,64 @@ __device__ __forceinline__ V3 sample_env(const EnvDev &E, double u1, double u2)
     return v3(sin(th) * cos(ph), cos(th), sin(th) * sin(ph));
 }
 
-// nearest texel of a direction; sin(theta) for the pdf
-__device__ __forceinline__ void env_index(const EnvDev &E, V3 w, int &i, int &j, double &sin_t)
+// angles of a direction: polar from +y (cosine clamped), azimuth in [0, 2 pi)
+struct Angles {
+    double y, th, ph;
+};
+__device__ __forceinline__ Angles angles_of(V3 w)
 {
 #pragma clang fp contract(off)
-    double y = w.y < -1.0 ? -1.0 : (w.y > 1.0 ? 1.0 : w.y);
-    double th = acos(y);
-    double ph = atan2(w.z, w.x);
-    if (ph < 0.0) ph += 2.0 * kPiD;
-    int ii = (int)(th / kPiD * E.H), jj = (int)(ph / (2.0 * kPiD) * E.W);
-    i = ii < E.H - 1 ? ii : E.H - 1;
-    j = jj < E.W - 1 ? jj : E.W - 1;
-    if (i < 0) i = 0;
-    if (j < 0) j = 0;
-    sin_t = sqrt(1.0 - y * y > 0.0 ? 1.0 - y * y : 0.0);
+    Angles a;
+    a.y = w.y < -1.0 ? -1.0 : (w.y > 1.0 ? 1.0 : w.y);
+    a.th = acos(a.y);
+    a.ph = atan2(w.z, w.x);
+    if (a.ph < 0.0) a.ph += 2.0 * kPiD;
+    return a;
+}
+
+// nearest texel of a direction (its row and column, and the angles it came from)
+struct EnvTexel {
+    int i, j;
+    double y;
+};
+__device__ __forceinline__ EnvTexel env_texel(const EnvDev &E, const Angles &a)
+{
+#pragma clang fp contract(off)
+    EnvTexel t;
+    int ii = (int)(a.th / kPiD * E.H), jj = (int)(a.ph / (2.0 * kPiD) * E.W);
+    t.i = ii < E.H - 1 ? ii : E.H - 1;
+    t.j = jj < E.W - 1 ? jj : E.W - 1;
+    if (t.i < 0) t.i = 0;
+    if (t.j < 0) t.j = 0;
+    t.y = a.y;
+    return t;
+}
+
+__device__ __forceinline__ float3 texel_radiance(const EnvDev &E, const EnvTexel &t)
+{
+    const float *p = E.rgb + ((size_t)t.i * E.W + t.j) * 3;
+    return make_float3(p[0], p[1], p[2]);
 }
 
 __device__ __forceinline__ float3 env_radiance(const EnvDev &E, V3 w)
 {
-    int i, j;
-    double st;
-    env_index(E, w, i, j, st);
-    const float *p = E.rgb + ((size_t)i * E.W + j) * 3;
-    return make_float3(p[0], p[1], p[2]);
+    return texel_radiance(E, env_texel(E, angles_of(w)));
 }
 
-__device__ __forceinline__ double env_pdf(const EnvDev &E, V3 w)
+__device__ __forceinline__ double env_pdf(const EnvDev &E, const EnvTexel &t)
 {
 #pragma clang fp contract(off)
-    int i, j;
-    double st;
-    env_index(E, w, i, j, st);
+    const double st = sqrt(1.0 - t.y * t.y > 0.0 ? 1.0 - t.y * t.y : 0.0);
     if (st <= 0.0) return 0.0;
-    const float *cr = E.cond + (size_t)i * (E.W + 1);
-    double pij = ((double)E.marg[i + 1] - (double)E.marg[i]) * ((double)cr[j + 1] - (double)cr[j]);
+    const float *cr = E.cond + (size_t)t.i * (E.W + 1);
+    double pij = ((double)E.marg[t.i + 1] - (double)E.marg[t.i]) * ((double)cr[t.j + 1] - (double)cr[t.j]);
     return pij * E.H * E.W / (2.0 * kPiD * kPiD * st);
 }
 
 // q = (N_c p_c + N_g p_g + N_e p_e) / N_r (Sec. 3.4.1, deterministic mixture)
-__device__ __forceinline__ double mixture_pdf(const EnvDev &E, V3 n, V3 wo, double rough, V3 w, int nc, int ng,
-                                              int ne)
+// (t: the texel of w, read only with ne > 0)
+__device__ __forceinline__ double mixture_pdf(const EnvDev &E, V3 n, V3 wo, double rough, V3 w, const EnvTexel &t,
+                                              int nc, int ng, int ne)
 {
 #pragma clang fp contract(off)
     double ndi = dot(n, w), ndo = dot(n, wo);
@@ -199,7 +217,7 @@ __device__ __forceinline__ double mixture_pdf(const EnvDev &E, V3 n, V3 wo, doub
             pg = smith_G1(ndo, a2) * ggx_D(ndh, a2) / (4.0 * ndo);
         }
     }
-    double pe = ne > 0 ? env_pdf(E, w) : 0.0;
+    double pe = ne > 0 ? env_pdf(E, t) : 0.0;
     return ((double)nc * pc + (double)ng * pg + (double)ne * pe) / (double)(nc + ng + ne);
 }
 
@@ -301,30 +319,38 @@ __device__ __forceinline__ void brdf_cos_backward(V3 n, V3 wo, V3 wi, V3 alb, do
 // prefiltered tables and SplitSum(a, r, m, n, E) of a surface seen along -w.
 // ---------------------------------------------------------------------------
 // bilinear over texel centres; wraps in the azimuth, clamps in the polar angle
-__device__ __forceinline__ V3 table_lookup(const float *__restrict__ T, V3 w)
+struct TableAt {
+    int i0, j0, j1;
+    double fx, fy;
+};
+__device__ __forceinline__ TableAt table_at(const Angles &a)
 {
 #pragma clang fp contract(off)
-    double y = w.y < -1.0 ? -1.0 : (w.y > 1.0 ? 1.0 : w.y);
-    double th = acos(y), ph = atan2(w.z, w.x);
-    if (ph < 0.0) ph += 2.0 * kPiD;
+    TableAt t;
     // clamps written so that a NaN lands on the lower bound (indices stay in range)
-    double x = ph / (2.0 * kPiD) * kPfW - 0.5, v = th / kPiD * kPfH - 0.5;
+    double x = a.ph / (2.0 * kPiD) * kPfW - 0.5, v = a.th / kPiD * kPfH - 0.5;
     x = x > -1.0 ? (x < (double)kPfW ? x : (double)kPfW) : -1.0;
     double fx0 = floor(x);
-    double fx = x - fx0;
+    t.fx = x - fx0;
     int j0 = (int)fx0;
-    j0 = ((j0 % kPfW) + kPfW) % kPfW;
-    int j1 = (j0 + 1) % kPfW;
+    t.j0 = ((j0 % kPfW) + kPfW) % kPfW;
+    t.j1 = (t.j0 + 1) % kPfW;
     v = v > 0.0 ? (v < (double)(kPfH - 1) ? v : (double)(kPfH - 1)) : 0.0;
-    int i0 = (int)floor(v);
-    if (i0 > kPfH - 2) i0 = kPfH - 2;
-    double fy = v - i0;
+    t.i0 = (int)floor(v);
+    if (t.i0 > kPfH - 2) t.i0 = kPfH - 2;
+    t.fy = v - t.i0;
+    return t;
+}
+
+__device__ __forceinline__ V3 table_lookup(const float *__restrict__ T, const TableAt &at)
+{
+#pragma clang fp contract(off)
     double o[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        double a = T[(i0 * kPfW + j0) * 3 + k], b = T[(i0 * kPfW + j1) * 3 + k];
-        double c = T[((i0 + 1) * kPfW + j0) * 3 + k], d = T[((i0 + 1) * kPfW + j1) * 3 + k];
-        o[k] = (1.0 - fy) * ((1.0 - fx) * a + fx * b) + fy * ((1.0 - fx) * c + fx * d);
+        double a = T[(at.i0 * kPfW + at.j0) * 3 + k], b = T[(at.i0 * kPfW + at.j1) * 3 + k];
+        double c = T[((at.i0 + 1) * kPfW + at.j0) * 3 + k], d = T[((at.i0 + 1) * kPfW + at.j1) * 3 + k];
+        o[k] = (1.0 - at.fy) * ((1.0 - at.fx) * a + at.fx * b) + at.fy * ((1.0 - at.fx) * c + at.fx * d);
     }
     return v3(o[0], o[1], o[2]);
 }
@@ -341,19 +367,21 @@ __device__ __forceinline__ V3 split_sum(const EnvDev &E, V3 alb, double rough, d
     V3 R = v3(2.0 * ndv * n.x - v.x, 2.0 * ndv * n.y - v.y, 2.0 * ndv * n.z - v.z);
     double mu = ndv > 0.0 ? (ndv < 1.0 ? ndv : 1.0) : 0.0;
     double r = rough > 0.0 ? (rough < 1.0 ? rough : 1.0) : 0.0;
-    V3 Ld = table_lookup(E.Ed, n);
+    V3 Ld = table_lookup(E.Ed, table_at(angles_of(n)));
+    const Angles aR = angles_of(R);  // both levels, and the map itself, look along R
+    const TableAt tR = table_at(aR);
     double xl = r * (kPfL - 1);
     int l0 = (int)floor(xl);
     if (l0 > kPfL - 2) l0 = kPfL - 2;
     double tl = xl - l0;
     V3 L0;
     if (l0 == 0) {
-        float3 e = env_radiance(E, R);
+        float3 e = texel_radiance(E, env_texel(E, aR));
         L0 = v3(e.x, e.y, e.z);
     } else {
-        L0 = table_lookup(E.Es + (size_t)(l0 - 1) * kPfH * kPfW * 3, R);
+        L0 = table_lookup(E.Es + (size_t)(l0 - 1) * kPfH * kPfW * 3, tR);
     }
-    V3 L1 = table_lookup(E.Es + (size_t)l0 * kPfH * kPfW * 3, R);
+    V3 L1 = table_lookup(E.Es + (size_t)l0 * kPfH * kPfW * 3, tR);
     V3 Ls = v3((1.0 - tl) * L0.x + tl * L1.x, (1.0 - tl) * L0.y + tl * L1.y, (1.0 - tl) * L0.z + tl * L1.z);
     double xi = mu * kLutN - 0.5, yj = r * kLutN - 0.5;
     if (xi < 0.0) xi = 0.0;
@@ -401,9 +429,12 @@ __device__ __forceinline__ bool load_pixel(const RenderArgs &a, int64_t p, Shade
 }
 
 // Sample j of pixel p: direction w (double, and its single-precision ray
-// direction wf), mixture pdf q and weight f cos / q; false below the horizon.
+// direction wf), its environment texel, mixture pdf q and weight f cos / q;
+// false below the horizon.  kTexel: the caller reads the texel (otherwise it
+// is looked up only where the pdf needs it).
+template <bool kTexel>
 __device__ __forceinline__ bool draw(const RenderArgs &a, const Shade &s, int64_t p, int j, V3 &w, float3 &wf,
-                                     double &q, float3 &wt)
+                                     EnvTexel &t, double &q, float3 &wt)
 {
     uint32_t c0 = (uint32_t)p, c1 = (uint32_t)j;
     float u1f, u2f;
@@ -417,7 +448,8 @@ __device__ __forceinline__ bool draw(const RenderArgs &a, const Shade &s, int64_
     q = 0.0;
     wt = make_float3(0.f, 0.f, 0.f);
     if (!(ndi > 0.0)) return false;
-    q = mixture_pdf(a.E, s.n, s.wo, s.rough, w, a.nc, a.ng, a.ne);
+    if (kTexel || a.ne > 0) t = env_texel(a.E, angles_of(w));
+    q = mixture_pdf(a.E, s.n, s.wo, s.rough, w, t, a.nc, a.ng, a.ne);
     if (q > 0.0) {
         V3 f = brdf(s.n, s.wo, w, s.alb, s.rough, s.metal);
         wt = make_float3((float)(f.x * ndi / q), (float)(f.y * ndi / q), (float)(f.z * ndi / q));
@@ -431,19 +463,18 @@ __device__ __forceinline__ bool draw(const RenderArgs &a, const Shade &s, int64_
 // (L_env.y, L_env.z, -, -).  Samples below the horizon and invalid pixels are
 // flagged 0 and never traced.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void gen_ray(const RenderArgs &a, int64_t r)
+__device__ __forceinline__ void gen_ray(const RenderArgs &a, int64_t p, int j)
 {
-    const int spp = a.nc + a.ng + a.ne;
-    const int64_t p = r / spp;
-    const int j = (int)(r - p * spp);
+    const int64_t r = p * (a.nc + a.ng + a.ne) + j;
     Shade s;
+    EnvTexel tx = {0, 0, 0.0};
     float3 wf = make_float3(0.f, 0.f, 0.f), wt = wf, Le = wf;
     double q = 0.0;
     bool traced = false;
     if (load_pixel(a, p, s)) {
         V3 dir;
-        traced = draw(a, s, p, j, dir, wf, q, wt);
-        if (traced) Le = env_radiance(a.E, dir);
+        traced = draw<true>(a, s, p, j, dir, wf, tx, q, wt);
+        if (traced) Le = texel_radiance(a.E, tx);
     }
     float4 *rr = a.rays + 3 * r;
     rr[0] = make_float4(wf.x, wf.y, wf.z, traced ? 1.0f : 0.0f);
@@ -588,16 +619,41 @@ __device__ __forceinline__ void bind_trace(RelightTrace<K, false> &t, const Rend
     t.bind(a, S);
 }
 
-// c_pbr = (1/N_r) sum_j contrib[p, j], summed in sample order
-__device__ __forceinline__ void reduce_pixel(int64_t p, int spp, const float4 *__restrict__ contrib,
-                                             float *__restrict__ out)
+// c_pbr = (1/N_r) sum_j contrib[p, j], summed in sample order, for the pixels
+// of a block of 256 threads (every thread calls it).  A pixel's samples are
+// consecutive, so a thread that read its own pixel's would touch a line per
+// lane; a wavefront instead loads 8 samples of its 64 pixels at a time, 128
+// bytes a pixel, and each lane adds its own from LDS (bound by memory: 1024 x
+// 1024 x 32 samples 450 us before).
+constexpr int kReduceStep = 8;
+struct ReduceTile {
+    float4 v[4][64][kReduceStep + 1];
+};
+__device__ __forceinline__ void reduce_pixels(int64_t npix, int spp, const float4 *__restrict__ contrib,
+                                              float *__restrict__ out, ReduceTile &tile)
 {
-    const float4 *c = contrib + p * spp;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    float4(*v)[kReduceStep + 1] = tile.v[wave];
+    const int64_t p0 = (int64_t)blockIdx.x * 256 + wave * 64;
+    if (p0 >= npix) return;
+    const int64_t p = p0 + lane;
     float x = 0.f, y = 0.f, z = 0.f;
-    for (int j = 0; j < spp; ++j) {
-        const float4 v = c[j];
-        x += v.x; y += v.y; z += v.z;
+    for (int j0 = 0; j0 < spp; j0 += kReduceStep) {
+        const int m = spp - j0 < kReduceStep ? spp - j0 : kReduceStep;
+#pragma unroll
+        for (int k = 0; k < kReduceStep; ++k) {
+            const int q = k * (64 / kReduceStep) + lane / kReduceStep, s = lane % kReduceStep;
+            if (p0 + q < npix && s < m) v[q][s] = contrib[(p0 + q) * spp + j0 + s];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        if (p < npix)
+            for (int s = 0; s < m; ++s) {
+                const float4 c = v[lane][s];
+                x += c.x; y += c.y; z += c.z;
+            }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     }
+    if (p >= npix) return;
     const float inv = 1.0f / (float)spp;
     out[3 * p] = x * inv;
     out[3 * p + 1] = y * inv;

@@ -124,7 +124,7 @@ __device__ __forceinline__ bool tri_hit(const float4 r0, const float4 r1, const 
 // A ray's stack: entries (4-wide node or leaf, entry depth), the first
 // kMeshLds in LDS (lane-interleaved), deeper ones in a private array.  A node
 // leaves at most three siblings behind, on at most 63 levels.
-constexpr int kMeshLds = 12, kMeshDeep = 3 * 63 - kMeshLds;
+constexpr int kMeshLds = 8, kMeshDeep = 3 * 63 - kMeshLds;
 
 struct MeshStack {
     int2 *lds;  // the thread's slot 0; slot i at lds[256 * i]
@@ -167,7 +167,36 @@ __device__ __forceinline__ void mesh_closest(const float4 *__restrict__ rec, con
     int cur = nf <= 0 ? kNone : (nf == 1 ? -1 : 0);
     while (cur != kNone) {
         // (entry depths carry rounding: prune with some slack)
-        const float bound = best * 1.0000005f;
+        if (cur >= 0) {
+            const float bound = best * 1.0000005f;
+            const float4 *nd = reinterpret_cast<const float4 *>(nodes + cur);
+            const float4 w0 = nd[0], w1 = nd[1], w2 = nd[2];
+            const int4 ch = *reinterpret_cast<const int4 *>(nd + 3);
+            const float3 start = make_float3((w0.x - o.x) * inv.x, (w0.y - o.y) * inv.y, (w0.z - o.z) * inv.z);
+            const float3 step = make_float3(w0.w * inv.x, w1.x * inv.y, w1.y * inv.z);
+            const uint32_t lx = __float_as_uint(w1.z), ly = __float_as_uint(w1.w), lz = __float_as_uint(w2.x);
+            const uint32_t hx = __float_as_uint(w2.y), hy = __float_as_uint(w2.z), hz = __float_as_uint(w2.w);
+            const uint32_t nx = gx ? hx : lx, fx = gx ? lx : hx;
+            const uint32_t ny = gy ? hy : ly, fy = gy ? ly : hy;
+            const uint32_t nz = gz ? hz : lz, fz = gz ? lz : hz;
+            float t0, t1, t2, t3;
+            const bool k0 = slab_q<0>(nx, ny, nz, fx, fy, fz, step, start, tmin, t0) & (t0 <= bound) & (ch.x != kNoChild);
+            const bool k1 = slab_q<1>(nx, ny, nz, fx, fy, fz, step, start, tmin, t1) & (t1 <= bound) & (ch.y != kNoChild);
+            const bool k2 = slab_q<2>(nx, ny, nz, fx, fy, fz, step, start, tmin, t2) & (t2 <= bound) & (ch.z != kNoChild);
+            const bool k3 = slab_q<3>(nx, ny, nz, fx, fy, fz, step, start, tmin, t3) & (t3 <= bound) & (ch.w != kNoChild);
+            const int m = (int)k0 + (int)k1 + (int)k2 + (int)k3;
+            float s0 = k0 ? t0 : INFINITY, s1 = k1 ? t1 : INFINITY, s2 = k2 ? t2 : INFINITY, s3 = k3 ? t3 : INFINITY;
+            int c0 = ch.x, c1 = ch.y, c2 = ch.z, c3 = ch.w;
+            exchange(s0, c0, s1, c1);
+            exchange(s2, c2, s3, c3);
+            exchange(s0, c0, s2, c2);
+            exchange(s1, c1, s3, c3);
+            exchange(s1, c1, s2, c2);
+            if (m > 3) stack.push(c3, s3);
+            if (m > 2) stack.push(c2, s2);
+            if (m > 1) stack.push(c1, s1);
+            cur = m > 0 ? c0 : stack.pop(bound);
+        }
         if (cur < 0) {  // leaf: triangle record -(cur + 1)
             const float4 *rr = rec + 3 * (size_t)(-cur - 1);
             const float4 r0 = rr[0], r1 = rr[1], r2 = rr[2];
@@ -176,35 +205,7 @@ __device__ __forceinline__ void mesh_closest(const float4 *__restrict__ rec, con
                 best = t; bu = u; bv = v; bid = __float_as_uint(r0.w);
             }
             cur = stack.pop(best * 1.0000005f);
-            continue;
         }
-        const float4 *nd = reinterpret_cast<const float4 *>(nodes + cur);
-        const float4 w0 = nd[0], w1 = nd[1], w2 = nd[2];
-        const int4 ch = *reinterpret_cast<const int4 *>(nd + 3);
-        const float3 start = make_float3((w0.x - o.x) * inv.x, (w0.y - o.y) * inv.y, (w0.z - o.z) * inv.z);
-        const float3 step = make_float3(w0.w * inv.x, w1.x * inv.y, w1.y * inv.z);
-        const uint32_t lx = __float_as_uint(w1.z), ly = __float_as_uint(w1.w), lz = __float_as_uint(w2.x);
-        const uint32_t hx = __float_as_uint(w2.y), hy = __float_as_uint(w2.z), hz = __float_as_uint(w2.w);
-        const uint32_t nx = gx ? hx : lx, fx = gx ? lx : hx;
-        const uint32_t ny = gy ? hy : ly, fy = gy ? ly : hy;
-        const uint32_t nz = gz ? hz : lz, fz = gz ? lz : hz;
-        float t0, t1, t2, t3;
-        const bool k0 = slab_q<0>(nx, ny, nz, fx, fy, fz, step, start, tmin, t0) & (t0 <= bound) & (ch.x != kNoChild);
-        const bool k1 = slab_q<1>(nx, ny, nz, fx, fy, fz, step, start, tmin, t1) & (t1 <= bound) & (ch.y != kNoChild);
-        const bool k2 = slab_q<2>(nx, ny, nz, fx, fy, fz, step, start, tmin, t2) & (t2 <= bound) & (ch.z != kNoChild);
-        const bool k3 = slab_q<3>(nx, ny, nz, fx, fy, fz, step, start, tmin, t3) & (t3 <= bound) & (ch.w != kNoChild);
-        int m = (int)k0 + (int)k1 + (int)k2 + (int)k3;
-        float s0 = k0 ? t0 : INFINITY, s1 = k1 ? t1 : INFINITY, s2 = k2 ? t2 : INFINITY, s3 = k3 ? t3 : INFINITY;
-        int c0 = k0 ? ch.x : kNone, c1 = k1 ? ch.y : kNone, c2 = k2 ? ch.z : kNone, c3 = k3 ? ch.w : kNone;
-        exchange(s0, c0, s1, c1);
-        exchange(s2, c2, s3, c3);
-        exchange(s0, c0, s2, c2);
-        exchange(s1, c1, s3, c3);
-        exchange(s1, c1, s2, c2);
-        if (m > 3) stack.push(c3, s3);
-        if (m > 2) stack.push(c2, s2);
-        if (m > 1) stack.push(c1, s1);
-        cur = m > 0 ? c0 : stack.pop(bound);
     }
 }
 
@@ -264,8 +265,10 @@ __global__ void __launch_bounds__(256) k_mesh_trace_attr(MeshTraceArgs a)
 // traces them in the order of their directions' bins (a counting sort in LDS):
 // a pixel's samples leave in all directions, and 64 of them in index order
 // share few nodes.  Everything else stays within the tile's records, so no
-// global sort and no scattered writes are paid for it.
-constexpr int kMeshTile = 2048;
+// global sort and no scattered writes are paid for it.  (Relit frame of 1024 x
+// 1024 x 32 through 46k triangles: tiles of 1,024 11.0 ms, 2,048 11.3, 4,096
+// 11.8; 12 stack entries in LDS instead of 8, so fewer blocks, 12.0.)
+constexpr int kMeshTile = 1024;
 constexpr int kMeshBins = 257;  // 16 x 16 directions, then the untraced
 
 // octahedral direction bin, 16 x 16, along a Morton curve

@@ -275,12 +275,17 @@ hipError_t launch_dfg_lut(float *lut, hipStream_t st)
     return hipGetLastError();
 }
 
+// A wavefront draws one sample index of 64 neighbouring pixels, so that it
+// runs one proposal: with a pixel's samples side by side, every wavefront ran
+// all three in turns.  Bound by double-precision issue.
 __global__ void __launch_bounds__(256) k_render_gen(RenderArgs a)
 {
-    const int64_t total = (int64_t)a.H * a.W * (a.nc + a.ng + a.ne);
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= total) return;
-    gen_ray(a, r);
+    const int spp = a.nc + a.ng + a.ne;
+    const int64_t npix = (int64_t)a.H * a.W;
+    const uint32_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4u + (threadIdx.x >> 6));
+    const uint32_t group = w / (uint32_t)spp;
+    const int64_t p = 64 * (int64_t)group + (threadIdx.x & 63);
+    if (p < npix) gen_ray(a, p, (int)(w - group * (uint32_t)spp));
 }
 
 // ---------------------------------------------------------------------------
@@ -518,9 +523,10 @@ __global__ void __launch_bounds__(256) k_render_shade_grad(RenderArgs a, ShadeGr
             const float4 go = a.gorig[r];
             gx[0] += go.x; gx[1] += go.y; gx[2] += go.z;
             V3 w;
+            EnvTexel tx = {0, 0, 0.0};
             float3 wf, wt;
             double q;
-            draw(a, s, p, j, w, wf, q, wt);
+            draw<false>(a, s, p, j, w, wf, tx, q, wt);
             if (!(q > 0.0)) continue;
             const float4 sv = a.saved[r], r1 = a.rays[3 * r + 1], r2 = a.rays[3 * r + 2];
             const float Li[3] = {sv.x + sv.w * r1.w, sv.y + sv.w * r2.x, sv.z + sv.w * r2.y};
@@ -558,11 +564,11 @@ hipError_t launch_render_shade_grad(const RenderArgs &a, const ShadeGradOut &o, 
     return hipGetLastError();
 }
 
-__global__ void k_render_reduce(int64_t npix, int spp, const float4 *__restrict__ contrib, float *__restrict__ out)
+__global__ void __launch_bounds__(256) k_render_reduce(int64_t npix, int spp, const float4 *__restrict__ contrib,
+                                                       float *__restrict__ out)
 {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= npix) return;
-    reduce_pixel(p, spp, contrib, out);
+    __shared__ ReduceTile tile;
+    reduce_pixels(npix, spp, contrib, out, tile);
 }
 
 template <int K, bool kHitList>
@@ -635,8 +641,9 @@ hipError_t launch_render_backward_stored(const RenderArgs &a, const RenderWS &w,
 
 hipError_t launch_render_gen(const RenderArgs &a, hipStream_t st)
 {
-    const int64_t total = (int64_t)a.H * a.W * (a.nc + a.ng + a.ne);
-    hipLaunchKernelGGL(k_render_gen, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, a);
+    // (fewer than 2^31 samples: at most 2^25 + 65536 wavefronts)
+    const int64_t waves = ((int64_t)a.H * a.W + 63) / 64 * (a.nc + a.ng + a.ne);
+    hipLaunchKernelGGL(k_render_gen, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 

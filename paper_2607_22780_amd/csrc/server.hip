@@ -216,14 +216,14 @@ __global__ void __launch_bounds__(256) GRT_WAVES(K, 4)
 // counters/total: the claim counters of a preemptible epoch that held the
 // request's last rays; if the epoch was stopped before claiming them all, the
 // request is not complete and the reduction does nothing.
-__global__ void k_serve_reduce(const RenderArgs *a, int64_t npix, const unsigned long long *counters, int64_t total)
+__global__ void __launch_bounds__(256) k_serve_reduce(const RenderArgs *a, int64_t npix,
+                                                      const unsigned long long *counters, int64_t total)
 {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= npix) return;
+    __shared__ ReduceTile tile;
     if (counters)
         for (int q = 0; q < kParts; ++q)
             if ((int64_t)counters[q] < part_begin(total, q + 1) - part_begin(total, q)) return;
-    reduce_pixel(p, a->nc + a->ng + a->ne, a->contrib, a->out);
+    reduce_pixels(npix, a->nc + a->ng + a->ne, a->contrib, a->out, tile);
 }
 
 template <int K, class Trace, bool kStop>
