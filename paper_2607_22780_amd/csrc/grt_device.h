@@ -276,7 +276,7 @@ __device__ __forceinline__ double key_max(double a, double b)
 // Ordered traversal with a k-nearest hit buffer, in rounds that resume from a
 // deferred frontier, as a per-lane state machine.
 //
-// A round walks the LBVH keeping the K smallest keys (bits(tau), id) strictly
+// A round walks the BVH keeping the K smallest keys (bits(tau), id) strictly
 // greater than the last key composited in the previous round (registers,
 // sorted by unrolled insertion).  Once the buffer is full its largest depth
 // thi bounds the walk.  Everything the bound excludes is not dropped but
@@ -342,10 +342,9 @@ constexpr int kNone = 0x7fffffff;
 // next round's walk stack).  A round's stack starts with at most kMaxDeferred
 // items; below them, a node step pops one item and pushes at most three, so
 // the stack holds at most three siblings for each 4-wide level of the current
-// path.  The 4-wide tree is no deeper than the binary LBVH (each of its edges
-// spans at least one binary edge), whose depth is at most 63 (30-bit codes,
-// then the position breaking ties), so the stack stays within
-// kMaxDeferred + 3 * 63 <= kStackCap.
+// path.  The 4-wide tree is no deeper than the binary one (each of its edges
+// spans at least one binary edge), whose build keeps it within 63 levels, so
+// the stack stays within kMaxDeferred + 3 * 63 <= kStackCap.
 constexpr int kMaxDeferred = 192;
 static_assert(kMaxDeferred + 3 * 63 <= kStackCap, "walk stack bound");
 

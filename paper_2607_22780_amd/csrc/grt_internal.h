@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "grt.h"
 #include "grt_device.h"
 
@@ -36,13 +38,25 @@ inline size_t sort_hist_words(int64_t n)
     return total + (total + 4095) / 4096;
 }
 
+// Clusters of a block of the hierarchy's clustering, and the share of them
+// that a launch leaves.  The scratch of a hierarchy over n leaves: the lists
+// of the first and the second launch (33 bytes a cluster); the leaves of one
+// block need none.
+constexpr int kClusterBlock = 512, kClusterShrink = 8;
+inline size_t cluster_words(int64_t c) { return (size_t)((c + kClusterShrink - 1) / kClusterShrink); }
+inline size_t cluster_bytes(int64_t n)
+{
+    const size_t c1 = cluster_words(n);
+    return n <= kClusterBlock ? 0 : align256(33 * c1) + align256(33 * cluster_words((int64_t)c1));
+}
+
 // Carving of a scene workspace; the same function sizes and places.
 struct SceneWS {
     float4 *rec;
     float4 *col;
     Node *nodes;
     float *leaf_box;   // [n,6] sorted order
-    float *pyr;        // [< n + 32, 6] boxes of runs of 2, 4, 8, ... leaves
+    void *clusters;    // hierarchy: clusters between two launches (cluster_bytes)
     uint32_t *keys0, *keys1, *vals0, *vals1;
     uint32_t *hist;        // [256 * blocks]
     int32_t *bounds;       // [8]
@@ -71,7 +85,7 @@ inline SceneWS carve_scene(void *base, int64_t n)
     w.col = (float4 *)take(16 * nn);
     w.nodes = (Node *)take(sizeof(Node) * ni);
     w.leaf_box = (float *)take(24 * nn);
-    w.pyr = (float *)take(24 * (nn + 32));
+    w.clusters = take(cluster_bytes(n));
     w.keys0 = (uint32_t *)take(4 * nn);
     w.keys1 = (uint32_t *)take(4 * nn);
     w.vals0 = (uint32_t *)take(4 * nn);
@@ -222,13 +236,14 @@ struct EnvDev {
 };
 hipError_t launch_env_build(const float *rgb, int H, int W, const EnvWS &w, hipStream_t st);
 
-// LBVH pieces shared by the surfel scene and the triangle mesh (scene.hip)
+// BVH pieces shared by the surfel scene and the triangle mesh (scene.hip)
 hipError_t launch_bounds_reset(int32_t *bounds, hipStream_t st);
 hipError_t launch_morton_sort(int n, const float *centres, const int32_t *bounds, uint32_t *keys0, uint32_t *vals0,
                               uint32_t *keys1, uint32_t *vals1, uint32_t *hist, hipStream_t st);
-// mark: [n] words cleared for the collapse to 4-wide nodes (null: none)
-hipError_t launch_hierarchy(int n, const uint32_t *keys, const float *leaf_box, float *pyr, Node *nodes, uint32_t *mark,
-                            hipStream_t st);
+// Binary hierarchy over leaf boxes in sorted order.  scratch: cluster_bytes(n)
+// bytes (alignment 256); mark: [n] words cleared for the collapse to 4-wide
+// nodes (null: none)
+hipError_t launch_hierarchy(int n, const float *leaf_box, void *scratch, Node *nodes, uint32_t *mark, hipStream_t st);
 
 // Collapse to 4-wide nodes.  nodes4: the full-precision copy (null: none);
 // queue [n-1], mark [n] (cleared by launch_hierarchy), part [n], sums [n / 4096 + 1]
@@ -241,7 +256,7 @@ struct MeshWS {
     float4 *rec;
     Node *nodes;
     float *leaf_box;  // [nf,6] sorted order
-    float *box_tmp;   // [nf,6] triangle order, then the boxes of runs of leaves [< nf + 32, 6]
+    float *box_tmp;   // [nf,6] triangle order, then the clusters of the hierarchy
     float *centre;    // [nf,3]
     uint32_t *keys0, *keys1, *vals0, *vals1;
     uint32_t *hist;
@@ -266,7 +281,7 @@ inline MeshWS carve_mesh(void *base, int64_t nf)
     w.rec = (float4 *)take(48 * n);
     w.nodes = (Node *)take(sizeof(Node) * ni);
     w.leaf_box = (float *)take(24 * n);
-    w.box_tmp = (float *)take(24 * (n + 32));
+    w.box_tmp = (float *)take(std::max<size_t>(24 * n, cluster_bytes((int64_t)n)));
     w.centre = (float *)take(12 * n);
     w.keys0 = (uint32_t *)take(4 * n);
     w.keys1 = (uint32_t *)take(4 * n);

@@ -5,7 +5,7 @@
 // the environment); a hit sets V = 0 and interpolates the vertex attributes
 // with the hit's barycentric weights.
 //
-// MI355X has no ray-tracing units, so the query is software: an LBVH over the
+// MI355X has no ray-tracing units, so the query is software: a BVH over the
 // triangles' boxes, built and collapsed to 4-wide quantized nodes with the
 // surfel scene's kernels, and a closest-hit traversal, one thread per ray,
 // nearer child first, pruned by the closest hit so far.
@@ -94,7 +94,7 @@ hipError_t launch_mesh_build(int nv, const float *verts, int nf, const int32_t *
         return e;
     hipLaunchKernelGGL(k_tri_records, dim3(gb), dim3(tb), 0, st, nv, verts, nf, tris, w.vals0, w.box_tmp, w.rec,
                        w.leaf_box);
-    if ((e = launch_hierarchy(nf, w.keys0, w.leaf_box, w.box_tmp, w.nodes, w.mark, st)) != hipSuccess) return e;
+    if ((e = launch_hierarchy(nf, w.leaf_box, w.box_tmp, w.nodes, w.mark, st)) != hipSuccess) return e;
     // (the sort's other keys and its histogram are free again)
     return launch_collapse4(nf, w.nodes, nullptr, w.nodesq, w.queue, w.mark, w.keys1, w.hist, w.ctl4, st);
 }

@@ -1,15 +1,15 @@
-// scene.hip -- surfel records and LBVH construction on the GPU.
+// scene.hip -- surfel records and BVH construction on the GPU.
 //
 // The paper bounds each 2D Gaussian by an adaptive icosahedron whose radius
 // sqrt(2 ln(o / alpha_min)) shrinks with opacity, and indexes the proxies with
 // a BVH (Sec. 3.2, Eq. icosahedron_transform).  Here the proxy is the
 // axis-aligned box of the ellipse rho <= min(3, sqrt(2 ln(o / alpha_min))), and
-// the BVH is an LBVH built in five steps, all on the caller's stream:
+// the BVH is built over the Morton order in five steps, all on the caller's stream:
 //   1. scene bounds of the box centres         (k_bounds, ordered-int atomics)
 //   2. 30-bit Morton codes of the centres      (k_morton)
 //   3. stable LSD radix sort, 4 passes x 8 bit (k_radix_hist/scan/scatter)
 //   4. records and boxes in sorted order       (k_records)
-//   5. Karras hierarchy with its boxes         (k_pyramid, k_hierarchy)
+//   5. binary hierarchy by clustering          (k_cluster)
 // and collapsed to the 4-wide nodes the traversal walks (k_collapse_*).
 #include <algorithm>
 
@@ -293,133 +293,211 @@ __global__ void k_records(int n, const uint32_t *__restrict__ order, const float
     surfel_box(tu, tv, su, sv, r2, mu, leaf_box + 6 * (size_t)p);
 }
 
-// ---- Karras (HPG 2012) hierarchy ---------------------------------------------
+// ---- hierarchy ----------------------------------------------------------------
 
-// common prefix length of sorted keys i, j; equal codes continue into the
-// positions, so all keys are distinct
-__device__ __forceinline__ int prefix(const uint32_t *__restrict__ codes, int n, int i, int j)
+__device__ __forceinline__ float box_area(const float *b)
 {
-    if (j < 0 || j >= n) return -1;
-    uint32_t a = codes[i], b = codes[j];
-    if (a != b) return __clz(a ^ b);
-    return 32 + __clz((uint32_t)i ^ (uint32_t)j);
+    const float dx = b[3] - b[0], dy = b[4] - b[1], dz = b[5] - b[2];
+    return dx * dy + dy * dz + dz * dx;
 }
 
-// Boxes of aligned runs of 2, 4, 8, ... leaves: level k >= 1 holds
-// ceil(n / 2^k) boxes, the levels one after the other.  A block reduces 512
-// boxes of its input level through LDS and writes the next levels, up to 9 of
-// them.  A node's box is then the union of the few runs that make up its range
-// of leaves, so no node waits for another (a bottom-up climb over flags, with
-// a device-scope fence per step, took 6.4 ms at 1M surfels on the 8 XCDs).
-__device__ __forceinline__ void merge_box(float *b, const float *v)
-{
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        b[a] = fminf(b[a], v[a]);
-        b[3 + a] = fmaxf(b[3 + a], v[3 + a]);
-    }
-}
+// Binary hierarchy by parallel locally-ordered clustering (Meister and Bittner,
+// TVCG 2018): in the Morton order, each cluster names the neighbour within
+// kClusterRadius places with which it has the smallest common box, and pairs
+// that name each other become a node, which takes the place of the first.
+//
+// A block keeps kClusterBlock consecutive clusters in LDS and repeats that
+// until an eighth is left, so one launch takes the whole array three levels
+// up; the last launch, of one block, goes on to the root.  Clusters at a
+// block's edge find fewer partners, but an eighth of a block need find none:
+// counted on 1M surfels, rays visit as many nodes as with clustering over the
+// whole array.  A block's merges are as many as it has clusters to lose, so
+// the place of every node is known beforehand: nodes are numbered down from
+// n - 2 in the order they are made, and the root is 0.
+//
+// Height: the walks' stacks take 63 levels.  Free merges stay within `cap`;
+// when a pass made no merge, or after kClusterIters passes, each cluster is
+// joined with its neighbour, which halves their number: at most 3 such passes
+// (kClusterForced in the last launch), so the caps of the launches are 3 apart
+// and end at 63 - kClusterForced.  (A room of 1M surfels: 36 levels, about 13
+// passes a launch.)
+//
+// In that room a ray visits 28% fewer nodes than in the hierarchy of the
+// codes' common prefixes (164 -> 118; up to the stop depth 128 -> 92), with
+// which a training step of 16.8M rays took 170 ms and takes 157, a relit frame
+// of 4.2M 23.4 and 21.8, the mesh query of 33.5M 9.9 and 9.3; scattered
+// surfels gain nothing.  The build is 0.72 ms instead of 0.57.  Bound by the
+// latency of a pass (barriers, LDS): blocks of 1024 0.88, of 256 0.77; radius
+// 4 0.73 with 1-2% slower walks, 7 0.83 and 10 1.0 with none faster.
+constexpr int kClusterRadius = 5, kClusterIters = 40;
+constexpr int kClusterForced = 9;  // passes that halve the clusters of a block to one
+static_assert(kClusterShrink == 8 && (1 << kClusterForced) == kClusterBlock, "forced passes of a launch");
 
-constexpr int kPyramidStep = 9;
+// Clusters of one launch's input or output: the box and, after the first
+// launch, the node, its number of leaves and its height.
+struct ClusterList {
+    float *box;     // [6 c]
+    int2 *ref;      // [c] node, leaves (null: leaf i, 1 leaf)
+    uint8_t *high;  // [c]
+};
 
-__global__ void __launch_bounds__(256) k_pyramid(int cnt, const float *__restrict__ in, float *__restrict__ out)
+__global__ void __launch_bounds__(kClusterBlock) k_cluster(int n, int count, ClusterList in, ClusterList out, int cap,
+                                                           Node *__restrict__ nodes, uint32_t *__restrict__ mark)
 {
-    __shared__ float lds[6][256];
-    const int t = threadIdx.x;
-    const int i = blockIdx.x * 256 + t;  // pair index
-    int m = (cnt + 1) >> 1;              // boxes of the level written
-    float b[6];
-#pragma unroll
-    for (int a = 0; a < 6; ++a) b[a] = NAN;
-    if (i < m) {
-        merge_box(b, in + 6 * (size_t)(2 * i));
-        if (2 * i + 1 < cnt) merge_box(b, in + 6 * (size_t)(2 * i + 1));
-#pragma unroll
-        for (int a = 0; a < 6; ++a) out[6 * (size_t)i + a] = b[a];
+    __shared__ float4 box0[kClusterBlock];  // lo xyz, hi x
+    __shared__ float2 box1[kClusterBlock];  // hi yz
+    __shared__ int ref[kClusterBlock], leaves[kClusterBlock], high[kClusterBlock], near[kClusterBlock];
+    __shared__ uint32_t wsum[kClusterBlock / 64];
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const uint64_t below = lane ? ~0ull >> (64 - lane) : 0ull;
+    const int64_t at = (int64_t)blockIdx.x * kClusterBlock;
+    int m = (int)(count - at < kClusterBlock ? count - at : kClusterBlock);  // clusters left
+    const int target = count <= kClusterBlock ? 1 : (m + kClusterShrink - 1) / kClusterShrink;
+    // number of the block's first node: the merges of earlier launches, then of earlier blocks
+    int id = n - 2 - (n - count) - (int)blockIdx.x * (kClusterBlock - kClusterBlock / kClusterShrink);
+    if (t < m) {
+        const float *b = in.box + 6 * (at + t);
+        box0[t] = make_float4(b[0], b[1], b[2], b[3]);
+        box1[t] = make_float2(b[4], b[5]);
+        const int2 r = in.ref ? in.ref[at + t] : make_int2(-(int)(at + t) - 1, 1);
+        ref[t] = r.x;
+        leaves[t] = r.y;
+        high[t] = in.ref ? in.high[at + t] : 0;
     }
-    int first = blockIdx.x * 256, width = 256;
-    for (int l = 1; l < kPyramidStep && m > 1; ++l) {
+    __syncthreads();
+    bool stuck = false;
+    for (int pass = 0; m > target; ++pass) {
+        // a single wavefront's clusters need no barrier (the others wait below)
+        const bool alone = m <= 64;
+        if (alone && wave) break;
+        const auto sync = [&]() {
+            if (alone) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            else __syncthreads();
+        };
+        // number of the pairs and (upper half) of the merged clusters before
+        // this one, and in all
+        const auto before = [&](uint64_t pairs, uint64_t lost, uint32_t &all) {
+            if (lane == 0) wsum[wave] = __popcll(pairs) | __popcll(lost) << 16;
+            sync();
+            uint32_t x = __popcll(pairs & below) | __popcll(lost & below) << 16;
+            all = wsum[0];
+            if (alone) return x;
 #pragma unroll
-        for (int a = 0; a < 6; ++a)
-            if (t < width) lds[a][t] = b[a];
-        __syncthreads();
-        out += 6 * (size_t)m;
-        m = (m + 1) >> 1;
-        first >>= 1;
-        width >>= 1;
-        if (t < width) {
-            float u[6], v[6];
+            for (int w = 1; w < kClusterBlock / 64; ++w) {
+                x += wave >= w ? wsum[w - 1] : 0u;
+                all += wsum[w];
+            }
+            return x;
+        };
+        const bool force = stuck || pass >= kClusterIters;
+        const bool on = t < m;
+        int best = -1;
+        float4 b0 = make_float4(0.f, 0.f, 0.f, 0.f);
+        float2 b1 = make_float2(0.f, 0.f);
+        if (on) {
+            b0 = box0[t];
+            b1 = box1[t];
+            if (force) {
+                best = (t ^ 1) < m ? t ^ 1 : -1;
+            } else {
+                // equal areas go to the neighbour t ^ 1, then to the lowest: of
+                // the closest pairs of all, one is mutual
+                float least = INFINITY;
 #pragma unroll
-            for (int a = 0; a < 6; ++a) { u[a] = lds[a][2 * t]; v[a] = lds[a][2 * t + 1]; }
-#pragma unroll
-            for (int a = 0; a < 6; ++a) b[a] = u[a];
-            merge_box(b, v);
-            if (first + t < m)
-#pragma unroll
-                for (int a = 0; a < 6; ++a) out[6 * (size_t)(first + t) + a] = b[a];
+                for (int k = 0; k < 2 * kClusterRadius; ++k) {
+                    const int j = t + (k < kClusterRadius ? k - kClusterRadius : k - kClusterRadius + 1);
+                    const int jj = min(max(j, 0), m - 1);
+                    const float4 v0 = box0[jj];
+                    const float2 v1 = box1[jj];
+                    const float u[6] = {fminf(b0.x, v0.x), fminf(b0.y, v0.y), fminf(b0.z, v0.z),
+                                        fmaxf(b0.w, v0.w), fmaxf(b1.x, v1.x), fmaxf(b1.y, v1.y)};
+                    const float area = box_area(u);
+                    if (j == jj && (area < least || (area == least && j == (t ^ 1)))) {
+                        least = area;
+                        best = j;
+                    }
+                }
+            }
+            near[t] = best;
         }
-        __syncthreads();
+        sync();
+        int r = 0, l = 0, h = 0, pl = 0, pr = 0;
+        float4 v0 = b0;
+        float2 v1 = b1;
+        bool pair = false, gone = false;
+        if (on) {
+            r = ref[t];
+            l = leaves[t];
+            h = high[t];
+            if (best >= 0 && near[best] == t && (force || max(h, high[best]) < cap)) {
+                pair = best > t;
+                gone = !pair;
+                v0 = box0[best];
+                v1 = box1[best];
+                pr = ref[best];
+                pl = leaves[best];
+                h = max(h, high[best]) + 1;
+            }
+        }
+        uint32_t all;
+        uint32_t x = before(__ballot(pair), __ballot(gone), all);
+        const int npairs = (int)(all & 0xffffu), rank = (int)(x & 0xffffu), made = min(npairs, m - target);
+        if (made < npairs) {  // more pairs than the block may lose: the first of them
+            if (pair && rank >= made) {
+                near[best] = -2;
+                pair = false;
+                h = high[t];
+            }
+            sync();
+            if (gone && near[t] == -2) {
+                gone = false;
+                h = high[t];
+            }
+            x = before(0, __ballot(gone), all);
+        }
+        const int to = t - (int)(x >> 16);
+        if (pair) {
+            Node nd;
+            nd.a = make_float4(b0.x, b0.y, b0.z, b0.w);
+            nd.b = make_float4(b1.x, b1.y, v0.x, v0.y);
+            nd.c = make_float4(v0.z, v0.w, v1.x, v1.y);
+            l += pl;
+            nd.d = make_int4(r, pr, l, 0);
+            r = id - rank;
+            nodes[r] = nd;
+            if (mark) mark[r] = 0u;  // of the collapse to 4-wide nodes
+            b0 = make_float4(fminf(b0.x, v0.x), fminf(b0.y, v0.y), fminf(b0.z, v0.z), fmaxf(b0.w, v0.w));
+            b1 = make_float2(fmaxf(b1.x, v1.x), fmaxf(b1.y, v1.y));
+        }
+        if (on && !gone) {
+            box0[to] = b0;
+            box1[to] = b1;
+            ref[to] = r;
+            leaves[to] = l;
+            high[to] = h;
+        }
+        id -= made;
+        m -= made;
+        stuck = made == 0;
+        sync();
     }
-}
-
-// Union of the boxes of leaves a..b.
-__device__ __forceinline__ void range_box(int n, const float *__restrict__ leaf_box, const float *__restrict__ pyr, int a,
-                                          int b, float *box)
-{
+    __syncthreads();
+    if (count > kClusterBlock && t < target) {
+        const int64_t o = (int64_t)blockIdx.x * (kClusterBlock / kClusterShrink) + t;
+        const float4 b0 = box0[t];
+        const float2 b1 = box1[t];
+        const float b[6] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y};
 #pragma unroll
-    for (int k = 0; k < 6; ++k) box[k] = NAN;
-    const float *lv = leaf_box;
-    int cnt = n;
-    const float *up = pyr;
-    while (a <= b) {
-        if (a & 1) merge_box(box, lv + 6 * (size_t)a++);
-        if (!(b & 1)) merge_box(box, lv + 6 * (size_t)b--);
-        a >>= 1;
-        b >>= 1;  // (-1 stays -1)
-        lv = up;
-        cnt = (cnt + 1) >> 1;
-        up += 6 * (size_t)cnt;
+        for (int a = 0; a < 6; ++a) out.box[6 * o + a] = b[a];
+        out.ref[o] = make_int2(ref[t], leaves[t]);
+        out.high[o] = (uint8_t)high[t];
     }
-}
-
-__global__ void __launch_bounds__(256) k_hierarchy(int n, const uint32_t *__restrict__ codes,
-                                                   const float *__restrict__ leaf_box, const float *__restrict__ pyr,
-                                                   Node *__restrict__ nodes, uint32_t *__restrict__ mark)
-{
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (mark && i < n) mark[i] = 0u;  // of the collapse to 4-wide nodes
-    if (i >= n - 1) return;
-    int d = (prefix(codes, n, i, i + 1) - prefix(codes, n, i, i - 1)) > 0 ? 1 : -1;
-    int dmin = prefix(codes, n, i, i - d);
-    int lmax = 2;
-    while (prefix(codes, n, i, i + lmax * d) > dmin) lmax <<= 1;
-    int l = 0;
-    for (int t = lmax >> 1; t >= 1; t >>= 1)
-        if (prefix(codes, n, i, i + (l + t) * d) > dmin) l += t;
-    int j = i + l * d;
-    int dnode = prefix(codes, n, i, j);
-    int s = 0, t = l;
-    do {
-        t = (t + 1) >> 1;
-        if (prefix(codes, n, i, i + (s + t) * d) > dnode) s += t;
-    } while (t > 1);
-    int gamma = i + s * d + min(d, 0);
-    int lo = min(i, j), hi = max(i, j);
-    float L[6], R[6];
-    range_box(n, leaf_box, pyr, lo, gamma, L);
-    range_box(n, leaf_box, pyr, gamma + 1, hi, R);
-    Node nd;
-    nd.a = make_float4(L[0], L[1], L[2], L[3]);
-    nd.b = make_float4(L[4], L[5], R[0], R[1]);
-    nd.c = make_float4(R[2], R[3], R[4], R[5]);
-    nd.d = make_int4((lo == gamma) ? -(gamma + 1) : gamma, (hi == gamma + 1) ? -(gamma + 2) : gamma + 1,
-                     hi - lo + 1, 0);
-    nodes[i] = nd;
+    if (count <= kClusterBlock && t == 0 && mark) mark[n - 1] = 0u;  // the word past the nodes' (the scan takes n)
 }
 
 // ---------------------------------------------------------------------------
 // The 4-wide hierarchy the traversal walks, collapsed top down from the
-// binary LBVH.  A 4-wide node starts from a binary node's two children and
+// binary one.  A 4-wide node starts from a binary node's two children and
 // twice opens the internal child of largest surface area (replacing it by its
 // two children), so it has 2..4 children; its internal children are the binary
 // nodes that further 4-wide nodes start from.  Which binary nodes those are is
@@ -436,12 +514,6 @@ __global__ void __launch_bounds__(256) k_hierarchy(int n, const uint32_t *__rest
 constexpr int kCollapseTop = 1024;   // threads of the first launch
 constexpr int kCollapseWide = 2048;  // level width handed to the second
 constexpr int kCollapseWaves = 4096;
-
-__device__ __forceinline__ float box_area(const float *b)
-{
-    const float dx = b[3] - b[0], dy = b[4] - b[1], dz = b[5] - b[2];
-    return dx * dy + dy * dz + dz * dx;
-}
 
 // The NodeQ of m child boxes (lo xyz, hi xyz).  Per axis, a grid of 256 planes
 // over the children's union; each child takes the grid planes just outside
@@ -751,8 +823,8 @@ void launch_radix_sort(int n, int passes, uint32_t *k0, uint32_t *v0, uint32_t *
 
 // Pieces of the LBVH build shared with the triangle mesh: reset the centre
 // bounds; Morton codes of centres [n,3] within the bounds and their sort
-// (sorted codes / original indices back in keys0 / vals0); the hierarchy over
-// the sorted codes with its boxes, from leaf boxes in sorted order.
+// (sorted codes / original indices back in keys0 / vals0); the binary
+// hierarchy, from leaf boxes in sorted order.
 hipError_t launch_bounds_reset(int32_t *bounds, hipStream_t st)
 {
     hipLaunchKernelGGL(k_init, dim3(1), dim3(64), 0, st, bounds);
@@ -768,22 +840,31 @@ hipError_t launch_morton_sort(int n, const float *centres, const int32_t *bounds
     return hipGetLastError();
 }
 
-hipError_t launch_hierarchy(int n, const uint32_t *keys, const float *leaf_box, float *pyr, Node *nodes, uint32_t *mark,
-                            hipStream_t st)
+hipError_t launch_hierarchy(int n, const float *leaf_box, void *scratch, Node *nodes, uint32_t *mark, hipStream_t st)
 {
     if (n <= 1) return hipSuccess;
-    const float *in = leaf_box;
-    float *out = pyr;
-    for (int cnt = n; cnt > 1;) {
-        const int pairs = (cnt + 1) / 2;
-        hipLaunchKernelGGL(k_pyramid, dim3((pairs + 255) / 256), dim3(256), 0, st, cnt, in, out);
-        for (int l = 0; l < kPyramidStep && cnt > 1; ++l) {  // the levels written
-            cnt = (cnt + 1) / 2;
-            in = out;
-            out += 6 * (size_t)cnt;
-        }
+    const auto list = [](void *p, size_t c) {
+        ClusterList v;
+        v.ref = (int2 *)p;
+        v.box = (float *)(v.ref + c);
+        v.high = (uint8_t *)(v.box + 6 * c);
+        return v;
+    };
+    const auto blocks = [](int64_t c) { return (int)((c + kClusterBlock - 1) / kClusterBlock); };
+    int launches = 0;
+    for (int64_t c = n; c > kClusterBlock; c = (c + kClusterShrink - 1) / kClusterShrink) ++launches;
+    const size_t c1 = cluster_words(n), c2 = cluster_words((int64_t)c1);
+    const ClusterList lists[2] = {list(scratch, c1), list((char *)scratch + align256(33 * c1), c2)};
+    ClusterList in{const_cast<float *>(leaf_box), nullptr, nullptr};
+    int count = n;
+    for (int k = 0; k <= launches; ++k) {
+        const ClusterList out = lists[k & 1];
+        const int cap = 63 - kClusterForced - 3 * (launches - k);
+        hipLaunchKernelGGL(k_cluster, dim3(blocks(count)), dim3(kClusterBlock), 0, st, n, count, in, out, cap, nodes,
+                           mark);
+        count = (count + kClusterShrink - 1) / kClusterShrink;
+        in = out;
     }
-    hipLaunchKernelGGL(k_hierarchy, dim3((n + 255) / 256), dim3(256), 0, st, n, keys, leaf_box, pyr, nodes, mark);
     return hipGetLastError();
 }
 
@@ -801,7 +882,7 @@ hipError_t launch_scene_build(const grt_surfels &s, float alpha_min, const Scene
     hipLaunchKernelGGL(k_records, dim3(gb), dim3(tb), 0, st, n, w.vals0, s.means, s.scales, s.quats, s.opacity, s.rgb,
                        alpha_min, w.rec, w.col, w.leaf_box, w.quat);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = launch_hierarchy(n, w.keys0, w.leaf_box, w.pyr, w.nodes, w.mark, st)) != hipSuccess) return e;
+    if ((e = launch_hierarchy(n, w.leaf_box, w.clusters, w.nodes, w.mark, st)) != hipSuccess) return e;
     // (the sort's other keys and its histogram are free again)
     return launch_collapse4(n, w.nodes, w.nodes4, w.nodesq, w.queue, w.mark, w.keys1, w.hist, w.ctl4, st);
 }
