@@ -293,17 +293,17 @@ __device__ __forceinline__ double key_max(double a, double b)
 // restarts from the root, which re-finds every hit beyond the last composited
 // key.
 //
-// What bounds the walk is VALU issue: lanes of a wavefront take the node
-// step, the leaf test and the visitor in turns (22 of 64 lanes active per
-// VALU instruction), at 72-79% of the issue peak.  So each of these blocks is
-// kept short: pushes without branches into ring windows, one merged push for
-// kept and deferred children, keys moved by min and max.  Node step 430 to
-// 230 VALU instructions, insertion at K = 16 121 to 81; room of 1M surfels:
-// forward K = 16 (512 x 512, 32 spp) 53.0 to 43.7 ms, backward K = 13
-// (1024 x 1024, 16 spp) 122.8 to 115.5 ms, relighting K = 12 31.9 to 28.1 ms.
+// What bounds the walk is VALU issue: lanes of a wavefront take the node step
+// and the leaf test in turns (25 of 64 lanes active per VALU instruction), at
+// 88% of the issue peak.  So each of these blocks is kept short: pushes
+// without branches into ring windows, one merged push for kept and deferred
+// children, keys moved by min and max.  Node step 430 to 230 VALU
+// instructions, insertion at K = 16 121 to 81; room of 1M surfels: forward
+// K = 16 (512 x 512, 32 spp) 53.0 to 43.7 ms, backward K = 13 (1024 x 1024,
+// 16 spp) 122.8 to 115.5 ms, relighting K = 12 31.9 to 28.1 ms.
 //
-// advance() does one node or one hit, so a wavefront can hold rays at
-// different rounds and refill lanes whose ray has finished (run_persistent).
+// advance() does one node or one leaf and composite() a few hits, so a wavefront
+// can hold rays at different rounds and refill lanes whose ray has finished (run_persistent).
 // ---------------------------------------------------------------------------
 // ---------------------------------------------------------------------------
 // A lane's two stacks (walk and deferred): the newest entries of each are a
@@ -313,28 +313,16 @@ __device__ __forceinline__ double key_max(double a, double b)
 // could fill move out, and some come back when a pop finds its window empty),
 // so pushing is one LDS store and a wrapped increment, without branches.
 // ---------------------------------------------------------------------------
-#ifndef GRT_BWD_LDS_DEPTH
-#define GRT_BWD_LDS_DEPTH 16
-#endif
-constexpr int kBwdLdsDepth = GRT_BWD_LDS_DEPTH;  // backward kernels: their LDS also holds gradient tables
-// Backward kernels composite a hit (running the gradient chain) only in
-// surfel steps where at least kBwdCompShare16/16 of the wavefront's active
-// lanes have one to composite, or no lane is still walking, and run surfel
-// steps once kBwdSiteShare8/8 of the active lanes wait for one.
-#ifndef GRT_BWD_COMP_SHARE16
-#define GRT_BWD_COMP_SHARE16 3
-#endif
-#ifndef GRT_BWD_SITE_SHARE8
-#define GRT_BWD_SITE_SHARE8 3
-#endif
-constexpr int kBwdCompShare16 = GRT_BWD_COMP_SHARE16;
-constexpr int kBwdSiteShare8 = GRT_BWD_SITE_SHARE8;
-// Surfel steps run when at least kSurfelShare4 / 4 of a wavefront's active
-// lanes wait for one.
-#ifndef GRT_SURFEL_SHARE4
-#define GRT_SURFEL_SHARE4 2
-#endif
-constexpr int kSurfelShare4 = GRT_SURFEL_SHARE4;
+constexpr int kBwdLdsDepth = 16;  // backward kernels: their LDS also holds gradient tables
+// Surfel steps run when at least kSurfelShare8 / 8 of a wavefront's walking
+// lanes wait for one, and buffered hits are composited once kCompShare16 / 16
+// of the lanes with a ray have a round's buffer to composite: shares, so that
+// the last rays of a launch wait for few others (with 8 lanes as the rule,
+// primary-ray maps took 10.6 ms, with 3 / 16 9.2).  Training step of 16.8M
+// rays, 1M surfels: 1 / 16 154 ms, 2 142, 3 139, 4 142, 5 151; surfel shares
+// 2 / 8 to 5 / 8 lie within 1%, but 50k surfels' forward and backward within
+// 8% (3 / 8: 1.80 ms, 5 / 8: 1.96).
+constexpr int kSurfelShare8 = 3, kCompShare16 = 3;
 constexpr int kStackCap = 384;  // private entries of a stack
 constexpr int kNone = 0x7fffffff;
 
@@ -352,6 +340,12 @@ typedef __attribute__((address_space(3))) int LdsInt;
 __device__ __forceinline__ uint32_t lds_addr(const int *p) { return (uint32_t)(uintptr_t)(LdsInt *)p; }
 __device__ __forceinline__ int lds_load(uint32_t a) { return *(const LdsInt *)(uintptr_t)a; }
 __device__ __forceinline__ void lds_store(uint32_t a, int x) { *(LdsInt *)(uintptr_t)a = x; }
+
+// x of the lane at byte address 4 * lane (all lanes).
+__device__ __forceinline__ float lane_pull(int address, float x)
+{
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(address, __float_as_int(x)));
+}
 
 template <int D>
 struct Frontier {
@@ -470,17 +464,7 @@ struct Frontier {
     }
 };
 
-// kCompShare16 > 0: lanes with buffered hits join a surfel step only when at
-// least kCompShare16/16 of the active lanes have one, or when no lane is still
-// walking, so an expensive visitor runs with more lanes at once.  Each lane's
-// own sequence of steps is unchanged, and every call either walks some lane
-// or runs the step for all of them.  0: they join every surfel step.
-// kSiteShare8 > 0: surfel steps run once kSiteShare8/8 of the active lanes
-// wait for one (0: kSurfelShare4/4).
-#ifndef GRT_FWD_COMP_SHARE16
-#define GRT_FWD_COMP_SHARE16 0
-#endif
-template <int K, int D = kWindow4, int kCompShare16 = GRT_FWD_COMP_SHARE16, int kSiteShare8 = 0>
+template <int K, int D = kWindow4>
 struct Walker {
     static constexpr int kDepth = D;  // LDS entries per lane and stack
     float3 o, d;
@@ -652,22 +636,16 @@ struct Walker {
         return !lost && (F.dn | F.dold) == 0;
     }
 
-    // One unit of work: an item of the walk, or, once the round's walk is
-    // complete, one buffered hit handed to `visit` (front of the buffer, which
-    // then shifts down).  Compositing a hit per call keeps a lane that ends
-    // its round from holding the wavefront for K hits.  Returns true when the
-    // ray is finished.
-    // One step of the lane.  Walking lanes step a node every call; a leaf they
-    // find waits (st) for a surfel step, and so do buffered hits to
-    // composite.  Surfel steps -- the record, its canonical crossing, then the
-    // k-buffer insertion or the visitor -- run for the whole wavefront at
-    // once, when enough of its active lanes wait for one (or all do),
-    // so that block runs with many lanes (leaf tests postponed as in
-    // speculative while-while traversal).  Returns true when the ray is
-    // finished.  Every active lane of the wavefront calls it in the same step
-    // (the decision is a ballot over them).
-    template <class Visit>
-    __device__ __forceinline__ bool advance(const SceneDev &S, Visit &visit)
+    // A step of a walking lane (st >= 0): a node or a leaf of the walk.  A
+    // leaf that a node step finds waits (st) for a surfel step: the record,
+    // its canonical crossing and the k-buffer insertion run for the wavefront
+    // at once, when enough of its walking lanes wait for it, so that block
+    // runs with many lanes (leaf tests postponed as in speculative while-while
+    // traversal).  A lane whose round's walk is complete then waits for
+    // composite() (st < 0).  Returns true when the ray is finished.  Every
+    // walking lane of the wavefront calls it in the same step (the decision
+    // is a ballot over them).
+    __device__ __forceinline__ bool advance(const SceneDev &S)
     {
         if (st == kNone) {
             F.make_room(lost);
@@ -682,46 +660,135 @@ struct Walker {
                 st = leaf != kNone ? -leaf - 1 : kNone;
             }
         }
-        const bool wc = st < 0, wl = st != kNone && !wc;
-        bool want = wl || wc;
-        int nwant, nact;
-        bool all;
-        if (kCompShare16 == 0) {
-            nwant = __popcll(__ballot(want));
-            nact = __popcll(__ballot(1));
-            all = nwant == nact;
-        } else {
-            const int nl = __popcll(__ballot(wl)), nc = __popcll(__ballot(wc));
-            nact = __popcll(__ballot(1));
-            all = nl + nc == nact;
-            const bool comp_ok = 16 * nc >= kCompShare16 * nact || all;
-            want = wl || (wc && comp_ok);
-            nwant = nl + (comp_ok ? nc : 0);
-        }
-        const bool few = kSiteShare8 ? 8 * nwant < kSiteShare8 * nact : 4 * nwant < kSurfelShare4 * nact;
-        if (!want || (few && !all)) return false;
-        const bool comp = st < 0;
-        const uint32_t sp = comp ? pos[0] : (uint32_t)st;
-        // One surfel site for leaf tests and composites: the record and its
-        // canonical crossing are shared by both kinds of lanes.
-        const float4 *r = S.rec + 4 * (size_t)sp;
+        const bool want = st >= 0 && st != kNone;
+        const int nwant = __popcll(__ballot(want)), nwalk = __popcll(__ballot(st == kNone));
+        if (!want || 8 * nwant < kSurfelShare8 * (nwant + nwalk)) return false;
+        const float4 *r = S.rec + 4 * (size_t)(uint32_t)st;
         const float4 r0 = r[0], r1 = r[1], r2 = r[2], r3 = r[3];
         float den, tau, rho2;
         canon_geo(r0, r1, r2, r3, o, d, den, tau, rho2);
-        if (!comp) {
-            test_leaf(sp, den, tau, rho2, r0.w, r2.w);
-            st = kNone;
-            return false;
-        }
-        const bool stop = visit(sp, (uint32_t)__double2loint(key[0]), key_tau(key[0]), r0, r1, r2, r3, rho2, o, d);
-#ifdef GRT_STATS
-        ++st_comps;
-#endif
-        last = key[0];  // the last composited hit (next_round resets it)
+        test_leaf((uint32_t)st, den, tau, rho2, r0.w, r2.w);
+        st = kNone;
+        return false;
+    }
+
+    // Composite the next hits of lanes whose buffers wait (lanes of `comps`),
+    // at a wavefront-uniform point, all lanes.
+    //
+    // A hit's share of the work that does not depend on the hits before it --
+    // record, crossing, value geometry in double, alpha, and the gradient's
+    // chain rule behind the running sums -- is done by a helper lane,
+    // whichever ray the helper holds itself; the compositing lane then takes
+    // the results in order.  Up to 16 compositing lanes have 4 helpers (4
+    // hits) each, up to 32 two, more one.  Done by the compositing lane alone,
+    // a hit per step among the surfel steps, this block ran in nearly every
+    // step with 8 of 64 lanes: a quarter of the forward's VALU instructions
+    // and more of the backward's.  Values cross lanes through bpermute, which
+    // costs no VALU issue.  1M surfels, 16.8M rays: forward 66 to 59 ms,
+    // backward 87 to 79; 50k surfels, 32k rays, both: 1.97 to 1.80 ms.
+    static constexpr int kLogSlots = K < 2 ? 0 : K < 4 ? 1 : 2, kSlots = 1 << kLogSlots;
+
+    // the first n hits leave the buffer
+    template <int n>
+    __device__ __forceinline__ void shift()
+    {
 #pragma unroll
-        for (int i = 0; i < K - 1; ++i) { key[i] = key[i + 1]; pos[i] = pos[i + 1]; }
-        key[K - 1] = empty_key();
+        for (int i = 0; i < K - n; ++i) { key[i] = key[i + n]; pos[i] = pos[i + n]; }
+#pragma unroll
+        for (int i = K - n; i < K; ++i) key[i] = empty_key();
+    }
+
+    template <class Visit>
+    __device__ __forceinline__ bool composite(const SceneDev &S, Visit &visit, bool comp, uint64_t comps)
+    {
+        const int lane = (int)__lane_id();
+        const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(comps >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)comps, 0u));
+        const int n = __popcll(comps);
+        const int few = n > 32 ? 0 : n > 16 ? 1 : 2, l = min(few, kLogSlots), slots = 1 << l;
+        comp &= rank < 64 >> l;
+        int nv = 0;
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s) nv += (int)(s < slots && !is_empty(key[s]));
+        // the r-th compositing lane makes itself and its number of hits known
+        // to lane r (the others write to lane 63), and helpers read it there
+        const int named = __builtin_amdgcn_ds_permute(comp ? 4 * rank : 4 * 63, comp ? lane | nv << 8 : 0);
+        const int own = __builtin_amdgcn_ds_bpermute(lane >> l << 2, named);
+        const int from = (own & 63) << 2, slot = lane & (slots - 1), first = rank << l << 2;
+        const bool helps = slot < own >> 8;
+        uint32_t p = 0;
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s) {
+            const uint32_t x = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)pos[s]);
+            p = slot == s ? x : p;
+        }
+        const float3 ho = make_float3(lane_pull(from, o.x), lane_pull(from, o.y), lane_pull(from, o.z));
+        const float3 hd = make_float3(lane_pull(from, d.x), lane_pull(from, d.y), lane_pull(from, d.z));
+        const auto tables = visit.tables(from);
+        typename Visit::Item item;
+        float in[Visit::kIn];
+#pragma unroll
+        for (int j = 0; j < Visit::kIn; ++j) in[j] = 0.0f;
+        if (helps) {
+            const float4 *r = S.rec + 4 * (size_t)p;
+            const float4 r0 = r[0], r1 = r[1], r2 = r[2], r3 = r[3];
+            float den, tau, rho2;
+            canon_geo(r0, r1, r2, r3, ho, hd, den, tau, rho2);
+            Visit::item(S, tables, p, r0, r1, r2, r3, rho2, ho, hd, item, in);
+        }
+        bool stop = false;
+        int taken = 0;
+        float out[kSlots][Visit::kOut + 1];
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s) {
+#pragma unroll
+            for (int j = 0; j < Visit::kOut; ++j) out[s][j] = 0.0f;
+            if (s >= slots) continue;
+            float x[Visit::kIn];
+#pragma unroll
+            for (int j = 0; j < Visit::kIn; ++j) x[j] = lane_pull(first + 4 * s, in[j]);
+            if (comp && s < nv && !stop) {
+                stop = visit.step(x, pos[s], (uint32_t)__double2loint(key[s]), key_tau(key[s]), out[s]);
+                last = key[s];  // the last composited hit
+                ++taken;
+#ifdef GRT_STATS
+                ++st_comps;
+#endif
+            }
+        }
+        if constexpr (Visit::kOut > 0) {  // the rest of the hits' work, from the steps' results
+            const bool again = slot < __builtin_amdgcn_ds_bpermute(from, taken) && helps;
+            float back[Visit::kOut], ray[Visit::kRay], ret[Visit::kBack + 1];
+#pragma unroll
+            for (int j = 0; j < Visit::kOut; ++j) {
+                back[j] = 0.0f;
+#pragma unroll
+                for (int s = 0; s < kSlots; ++s) {
+                    const float x = lane_pull(from, out[s][j]);
+                    back[j] = slot == s ? x : back[j];
+                }
+            }
+            visit.ray_terms(ray);
+#pragma unroll
+            for (int j = 0; j < Visit::kRay; ++j) ray[j] = lane_pull(from, ray[j]);
+#pragma unroll
+            for (int j = 0; j < Visit::kBack; ++j) ret[j] = 0.0f;
+            if (again) visit.emit(S, item, back, ray, ret);
+            if constexpr (Visit::kBack > 0) {
+#pragma unroll
+                for (int s = 0; s < kSlots; ++s) {
+                    float x[Visit::kBack];
+#pragma unroll
+                    for (int j = 0; j < Visit::kBack; ++j) x[j] = lane_pull(first + 4 * s, ret[j]);
+                    if (comp && s < taken) visit.collect(x);
+                }
+            }
+        }
+        if (!comp) return false;
         if (stop) return true;
+        if (l == 0) shift<1>();
+        else if (l == 1) shift<2 <= kSlots ? 2 : 1>();
+        else shift<kSlots>();
         if (is_empty(key[0])) {
             if (st == kFinal || deferred_empty()) return true;
             st = kNone;
@@ -732,9 +799,9 @@ struct Walker {
 
 };
 
-// The walker of the backward kernels (see kBwdCompShare16, kBwdSiteShare8).
+// The walker of the backward kernels.
 template <int K>
-using BwdWalker = Walker<K, kBwdLdsDepth, kBwdCompShare16, kBwdSiteShare8>;
+using BwdWalker = Walker<K, kBwdLdsDepth>;
 
 // Upper end of a backward's re-traversal: the depth of the forward's last
 // composited hit when it was saved (every hit the backward composites lies at
@@ -758,7 +825,8 @@ __device__ __forceinline__ float stop_bound(const float *stop_depth, int64_t r, 
 // wavefront never waits for its slowest ray.  Every wavefront leaves the loop
 // once all partitions are drained and its lanes are idle.
 //
-// Job: bool begin(int64_t ray)  -- set up the ray; false if it needs no trace
+// Job: SceneDev S -- the scene of every ray
+//      bool begin(int64_t ray)  -- set up the ray; false if it needs no trace
 //      (then it must already have written its result)
 //      Walker<K, D> &walker(), Visit &visit(), void finish(int64_t ray),
 //      void after_step() and void drain() -- run by every lane of the
@@ -890,14 +958,20 @@ __device__ __forceinline__ void run_persistent(Job &job, unsigned long long *cou
             tally[kStActive] += (uint32_t)__popcll(busy);
         }
 #endif
-        if (active) {
-            if (job.walker().advance(job.S, job.visit())) {
+        auto &w = job.walker();
+        bool done = false;
+        if (active && w.st >= 0) done = w.advance(job.S);
+        const bool comp = active && w.st < 0;
+        const uint64_t comps = __ballot(comp);
+        const uint64_t walks = __ballot(active && !done && !comp);
+        if (comps && 16 * __popcll(comps) >= kCompShare16 * (__popcll(comps) + __popcll(walks)))
+            done |= w.composite(job.S, job.visit(), comp, comps);
+        if (done) {
 #ifdef GRT_STATS
-                walk_tally(tally, job.walker());
+            walk_tally(tally, w);
 #endif
-                job.finish(ray);
-                active = false;
-            }
+            job.finish(ray);
+            active = false;
         }
         job.after_step();  // wavefront-uniform point
     }

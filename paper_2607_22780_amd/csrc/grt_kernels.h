@@ -6,6 +6,21 @@
 
 namespace grt {
 
+// A visitor takes a ray's hits in order, each in parts (Walker::composite):
+//   item   what does not depend on the ray's other hits, by any lane: kIn
+//          values for the ray's own lane, and an Item that the lane keeps;
+//   step   the ray's own lane, in order: true when compositing stops after
+//          the hit, and kOut values for the lane that has the Item;
+//   emit   by that lane again, with those and the ray's kRay terms: what
+//          remains (a gradient's chain rule), and kBack values that
+//   collect, by the ray's lane, sums.
+struct NoTables {};
+struct VisitBase {
+    static constexpr int kOut = 0, kRay = 0, kBack = 0;
+    struct Item {};
+    static __device__ __forceinline__ NoTables tables(int) { return {}; }
+};
+
 // Forward compositing (Sec. 3.2, Eq. trace; Eq. alpha_blending along the ray).
 // Where to stop is decided on the transmittance of the canonical
 // single-precision alphas (Td); the composited values use alphas from the
@@ -13,9 +28,8 @@ namespace grt {
 // positions of the composited hits in the ray's stored hit list (hl); the
 // plain forward carries no list pointer at all.
 template <bool kHitList>
-struct CompositeVisit {
-    const float4 *rec;
-    const float4 *col;
+struct CompositeVisit : VisitBase {
+    static constexpr int kIn = 5;  // alpha, canonical alpha, colour
     float tcut;
     float3 C;
     float T, Td;
@@ -27,7 +41,7 @@ struct CompositeVisit {
     int hcap = 0;
 
     __device__ CompositeVisit() {}
-    __device__ CompositeVisit(const SceneDev &S, float t_cut) : rec(S.rec), col(S.col), tcut(t_cut) {}
+    __device__ explicit CompositeVisit(float t_cut) : tcut(t_cut) {}
 
     __device__ __forceinline__ void reset()
     {
@@ -37,23 +51,27 @@ struct CompositeVisit {
         cnt = 0;
     }
 
-    // Hit p (record r0..r3, canonical rho^2 crho2) of the ray, in order;
-    // true when compositing stops after it.
-    __device__ __forceinline__ bool operator()(uint32_t p, uint32_t id, float tau, const float4 r0, const float4 r1,
-                                               const float4 r2, const float4 r3, float crho2, const float3 o,
-                                               const float3 d)
+    static __device__ __forceinline__ void item(const SceneDev &S, NoTables, uint32_t p, const float4 r0,
+                                                const float4 r1, const float4 r2, const float4 r3, float crho2,
+                                                const float3 o, const float3 d, Item &, float (&in)[kIn])
     {
-        const float4 c = col[p];
+        const float4 c = S.col[p];
         HitGeo g;
         value_geo(r0, r1, r2, r3, o, d, g);
-        const float a = r1.w * expf(-0.5f * g.rho2);
-        const float w = T * a;
-        C.x += w * c.x; C.y += w * c.y; C.z += w * c.z;
+        in[0] = r1.w * expf(-0.5f * g.rho2);
+        in[1] = hit_alpha(r1.w, crho2);
+        in[2] = c.x; in[3] = c.y; in[4] = c.z;
+    }
+
+    __device__ __forceinline__ bool step(const float (&in)[kIn], uint32_t p, uint32_t id, float tau, float *)
+    {
+        const float a = in[0], w = T * a;
+        C.x += w * in[2]; C.y += w * in[3]; C.z += w * in[4];
         if (did && cnt < cap) { did[cnt] = (int32_t)id; dtau[cnt] = tau; }
         if (kHitList && hl && cnt < hcap) hl[cnt] = p;
         ++cnt;
         T = T * (1.0f - a);
-        Td = trans_step(Td, hit_alpha(r1.w, crho2));
+        Td = trans_step(Td, in[1]);
         return Td < tcut;
     }
 };
@@ -66,16 +84,40 @@ __device__ __forceinline__ float dot3(float3 a, float3 b) { return a.x * b.x + a
 // deferred_maps), each normal turned to face the ray origin; the caller
 // normalizes by the summed weight.  T ends as the visibility V of the
 // environment.
-struct AttrVisit {
-    const float4 *rec;
+//
+// kPerRayArgs: the attribute tables belong to the lane's ray, so a helper
+// takes them from the lane that it helps.
+struct AttrTables {
     const float *albedo, *rough, *metal;  // per surfel id
+};
+
+template <class P>
+__device__ __forceinline__ P *lane_pull_ptr(int address, P *x)
+{
+    const uint64_t v = (uint64_t)(uintptr_t)x;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(address, (int)(uint32_t)v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(address, (int)(uint32_t)(v >> 32));
+    return (P *)(uintptr_t)((uint64_t)hi << 32 | lo);
+}
+
+template <bool kPerRayArgs = false>
+struct AttrVisitT : VisitBase {
+    static constexpr int kIn = 10;  // alpha, canonical alpha, albedo, roughness, metallic, normal
+    AttrTables t;
     float tcut;
     float T, Td, W, R, M;
     float3 A, N;
 
-    __device__ AttrVisit() {}
-    __device__ AttrVisit(const SceneDev &S, float t_cut, const float *al, const float *ro, const float *me)
-        : rec(S.rec), albedo(al), rough(ro), metal(me), tcut(t_cut) {}
+    __device__ AttrVisitT() {}
+    __device__ AttrVisitT(float t_cut, const float *al, const float *ro, const float *me) : t{al, ro, me}, tcut(t_cut)
+    {
+    }
+
+    __device__ __forceinline__ AttrTables tables(int from) const
+    {
+        if (!kPerRayArgs) return t;
+        return {lane_pull_ptr(from, t.albedo), lane_pull_ptr(from, t.rough), lane_pull_ptr(from, t.metal)};
+    }
 
     __device__ __forceinline__ void reset()
     {
@@ -86,38 +128,52 @@ struct AttrVisit {
         N = make_float3(0.f, 0.f, 0.f);
     }
 
-    __device__ __forceinline__ bool operator()(uint32_t p, uint32_t id, float tau, const float4 r0, const float4 r1,
-                                               const float4 r2, const float4 r3, float crho2, const float3 o,
-                                               const float3 d)
+    static __device__ __forceinline__ void item(const SceneDev &, const AttrTables &t, uint32_t, const float4 r0,
+                                                const float4 r1, const float4 r2, const float4 r3, float crho2,
+                                                const float3 o, const float3 d, Item &, float *in)
     {
         HitGeo g;
         value_geo(r0, r1, r2, r3, o, d, g);
-        const float a = r1.w * expf(-0.5f * g.rho2);
-        const float w = T * a;
-        const float wn = g.den > 0.0f ? -w : w;  // normal toward the ray origin
-        const size_t i = id;
+        in[0] = r1.w * expf(-0.5f * g.rho2);
+        in[1] = hit_alpha(r1.w, crho2);
+        const bool away = g.den > 0.0f;  // normal toward the ray origin
+        in[7] = away ? -r1.x : r1.x; in[8] = away ? -r1.y : r1.y; in[9] = away ? -r1.z : r1.z;
+        // the record is done with before the attributes need registers
+        __builtin_amdgcn_sched_barrier(0);
+        const size_t i = __float_as_uint(r2.w);
+        in[2] = t.albedo[3 * i]; in[3] = t.albedo[3 * i + 1]; in[4] = t.albedo[3 * i + 2];
+        in[5] = t.rough[i];
+        in[6] = t.metal[i];
+    }
+
+    __device__ __forceinline__ bool step(const float *in, uint32_t, uint32_t, float, float *)
+    {
+        const float a = in[0], w = T * a;
         W += w;
-        A.x += w * albedo[3 * i]; A.y += w * albedo[3 * i + 1]; A.z += w * albedo[3 * i + 2];
-        R += w * rough[i];
-        M += w * metal[i];
-        N.x += wn * r1.x; N.y += wn * r1.y; N.z += wn * r1.z;
+        A.x += w * in[2]; A.y += w * in[3]; A.z += w * in[4];
+        R += w * in[5];
+        M += w * in[6];
+        N.x += w * in[7]; N.y += w * in[8]; N.z += w * in[9];
         T = T * (1.0f - a);
-        Td = trans_step(Td, hit_alpha(r1.w, crho2));
+        Td = trans_step(Td, in[1]);
         return Td < tcut;
     }
 };
+
+using AttrVisit = AttrVisitT<>;
 
 // Primary-ray G-buffer (Eq. deferred_maps on traced camera rays): the
 // attribute sums plus the depth tau and the colour of each composited hit,
 // with the same weights.
 struct GBufVisit : AttrVisit {
-    const float4 *col;
+    static constexpr int kIn = AttrVisit::kIn + 3;  // and the colour
     float Dsum;
     float3 Csum;
 
     __device__ GBufVisit() {}
-    __device__ GBufVisit(const SceneDev &S, float t_cut, const float *al, const float *ro, const float *me)
-        : AttrVisit(S, t_cut, al, ro, me), col(S.col) {}
+    __device__ GBufVisit(float t_cut, const float *al, const float *ro, const float *me) : AttrVisit(t_cut, al, ro, me)
+    {
+    }
 
     __device__ __forceinline__ void reset()
     {
@@ -126,18 +182,21 @@ struct GBufVisit : AttrVisit {
         Csum = make_float3(0.f, 0.f, 0.f);
     }
 
-    __device__ __forceinline__ bool operator()(uint32_t p, uint32_t id, float tau, const float4 r0, const float4 r1,
-                                               const float4 r2, const float4 r3, float crho2, const float3 o,
-                                               const float3 d)
+    static __device__ __forceinline__ void item(const SceneDev &S, const AttrTables &t, uint32_t p, const float4 r0,
+                                                const float4 r1, const float4 r2, const float4 r3, float crho2,
+                                                const float3 o, const float3 d, Item &it, float *in)
     {
-        HitGeo g;
-        value_geo(r0, r1, r2, r3, o, d, g);
-        const float a = r1.w * expf(-0.5f * g.rho2);
-        const float w = T * a;
-        const float4 c = col[p];
+        const float4 c = S.col[p];
+        AttrVisit::item(S, t, p, r0, r1, r2, r3, crho2, o, d, it, in);
+        in[10] = c.x; in[11] = c.y; in[12] = c.z;
+    }
+
+    __device__ __forceinline__ bool step(const float *in, uint32_t p, uint32_t id, float tau, float *out)
+    {
+        const float w = T * in[0];
         Dsum += w * tau;
-        Csum.x += w * c.x; Csum.y += w * c.y; Csum.z += w * c.z;
-        return AttrVisit::operator()(p, id, tau, r0, r1, r2, r3, crho2, o, d);
+        Csum.x += w * in[10]; Csum.y += w * in[11]; Csum.z += w * in[12];
+        return AttrVisit::step(in, p, id, tau, out);
     }
 };
 
@@ -160,10 +219,7 @@ struct WaveStageN {
 };
 // 80 entries of 64 bytes: with the backward's 16-deep stacks, 52 KB of LDS
 // per workgroup, three workgroups per CU
-#ifndef GRT_STAGE_CAP
-#define GRT_STAGE_CAP 80
-#endif
-using WaveStage = WaveStageN<GRT_STAGE_CAP>;
+using WaveStage = WaveStageN<80>;
 
 // Active lanes: stage one hit each (13 terms of surfel id).
 template <class Stage>
@@ -264,11 +320,19 @@ __device__ __forceinline__ void hit_param_grads(const HitGeo &hg, const float4 r
 // function of mu - o, so the loss's gradient with respect to the ray origin
 // is minus that sum (kept in `gmu`).
 template <bool kOrigin = false>
-struct GradVisitT {
-    const float4 *rec;
-    const float4 *col;
+struct GradVisitT : VisitBase {
+    static constexpr int kIn = 5;                   // alpha, canonical alpha, colour
+    static constexpr int kOut = 2;                  // w, dL/dalpha
+    static constexpr int kRay = 3;                  // gC
+    static constexpr int kBack = kOrigin ? 3 : 0;   // dL/dmu
+    struct Item {
+        HitGeo hg;
+        float4 r1, r2, r3;
+        float3 d;
+        float a, G, sv;
+        uint32_t p, id;
+    };
     float tcut;
-    GradPtrs g;
     WaveStage *stage = nullptr;  // the wavefront's staging list
     float3 gC;
     float3 R;     // colour still ahead: the saved c_rt minus the hits composited so far
@@ -277,9 +341,7 @@ struct GradVisitT {
     float3 gmu;
 
     __device__ GradVisitT() {}
-    const float4 *quat;
-    __device__ GradVisitT(const SceneDev &S, float t_cut, const GradPtrs &gp)
-        : rec(S.rec), col(S.col), tcut(t_cut), g(gp), quat(S.quat) {}
+    __device__ explicit GradVisitT(float t_cut) : tcut(t_cut) {}
 
     __device__ __forceinline__ void reset(float3 gC_, float gT_, float3 Cf_, float Tf_)
     {
@@ -291,37 +353,55 @@ struct GradVisitT {
         gmu = make_float3(0.f, 0.f, 0.f);
     }
 
-    __device__ __forceinline__ bool operator()(uint32_t p, uint32_t id, float tau, const float4 r0, const float4 r1,
-                                               const float4 r2, const float4 r3, float crho2, const float3 o,
-                                               const float3 d)
+    static __device__ __forceinline__ void item(const SceneDev &S, NoTables, uint32_t p, const float4 r0,
+                                                const float4 r1, const float4 r2, const float4 r3, float crho2,
+                                                const float3 o, const float3 d, Item &it, float *in)
     {
-        const float4 c = col[p];
-        const float op = r1.w;
-        HitGeo hg;
-        value_geo(r0, r1, r2, r3, o, d, hg);
-        const float G = expf(-0.5f * hg.rho2);
-        const float a = op * G;
-        const float w = T * a;
-        R.x -= w * c.x; R.y -= w * c.y; R.z -= w * c.z;
-        float dA = T * (gC.x * c.x + gC.y * c.y + gC.z * c.z);
+        const float4 c = S.col[p];
+        value_geo(r0, r1, r2, r3, o, d, it.hg);
+        it.G = expf(-0.5f * it.hg.rho2);
+        it.a = r1.w * it.G;
+        it.r1 = r1; it.r2 = r2; it.r3 = r3;
+        it.d = d;
+        it.sv = c.w;
+        it.p = p;
+        it.id = __float_as_uint(r2.w);
+        in[0] = it.a;
+        in[1] = hit_alpha(r1.w, crho2);
+        in[2] = c.x; in[3] = c.y; in[4] = c.z;
+    }
+
+    __device__ __forceinline__ bool step(const float *in, uint32_t, uint32_t, float, float *out)
+    {
+        const float a = in[0], w = T * a;
+        R.x -= w * in[2]; R.y -= w * in[3]; R.z -= w * in[4];
+        float dA = T * (gC.x * in[2] + gC.y * in[3] + gC.z * in[4]);
         const float om = 1.0f - a;
         if (om >= 1e-6f) {
             float behind = gC.x * R.x + gC.y * R.y + gC.z * R.z + gTf;
             dA -= behind / om;
         }
-        float terms[13];
-        hit_param_grads<false>(hg, r1, r2, r3, d, a, G, dA, 0.0f, make_float3(0.f, 0.f, 0.f), quat[p], r3.w, c.w,
-                               terms);
-        terms[10] = w * gC.x; terms[11] = w * gC.y; terms[12] = w * gC.z;
-        stage_add(stage, id, terms);
-        if constexpr (kOrigin) {
-            gmu.x += terms[0]; gmu.y += terms[1]; gmu.z += terms[2];
-        }
-
+        out[0] = w;
+        out[1] = dA;
         T = T * (1.0f - a);
-        Td = trans_step(Td, hit_alpha(op, crho2));
+        Td = trans_step(Td, in[1]);
         return Td < tcut;
     }
+
+    __device__ __forceinline__ void ray_terms(float *ray) const { ray[0] = gC.x; ray[1] = gC.y; ray[2] = gC.z; }
+
+    __device__ __forceinline__ void emit(const SceneDev &S, const Item &it, const float *out, const float *ray, float *ret)
+    {
+        const float w = out[0], dA = out[1];
+        float terms[13];
+        hit_param_grads<false>(it.hg, it.r1, it.r2, it.r3, it.d, it.a, it.G, dA, 0.0f, make_float3(0.f, 0.f, 0.f),
+                               S.quat[it.p], it.r3.w, it.sv, terms);
+        terms[10] = w * ray[0]; terms[11] = w * ray[1]; terms[12] = w * ray[2];
+        stage_add(stage, it.id, terms);
+        if constexpr (kOrigin) { ret[0] = terms[0]; ret[1] = terms[1]; ret[2] = terms[2]; }
+    }
+
+    __device__ __forceinline__ void collect(const float *x) { gmu.x += x[0]; gmu.y += x[1]; gmu.z += x[2]; }
 };
 
 using GradVisit = GradVisitT<false>;
@@ -334,22 +414,30 @@ using GradVisit = GradVisitT<false>;
 // and sum_k w_k e_k = 0 (every map is invariant to a common scale of the
 // weights), so the part of the loss behind hit k is -(e_1 w_1 + ... + e_k w_k).
 // The per-ray constants come from the forward's maps, W and |N| / W.
-struct GBufGradVisit {
-    const float4 *rec;
-    const float4 *col;
-    const float *albedo, *rough, *metal;  // per surfel id
+struct GBufGradVisit : VisitBase {
+    // alpha, canonical alpha, albedo, roughness, metallic, normal toward the camera, colour
+    static constexpr int kIn = 13;
+    static constexpr int kOut = 2;   // w, dL/dalpha
+    static constexpr int kRay = 12;  // kD, kR, kM, kA, kC, kN
+    struct Item {
+        HitGeo hg;
+        float4 r1, r2, r3;
+        float3 d;
+        float a, G, sv;
+        uint32_t p, id;
+    };
+    AttrTables t;
     float *ga_albedo, *ga_rough, *ga_metal;  // attribute gradients (NULL: skipped)
     float tcut;
-    GradPtrs g;
     WaveStage *stage = nullptr;
     float kD, kR, kM, e0;  // upstream gradients over W, and sum_f g_f F_f / W
     float3 kA, kC, kN;
     float T, Td, P;
 
     __device__ GBufGradVisit() {}
-    const float4 *quat;
-    __device__ GBufGradVisit(const SceneDev &S, float t_cut, const GradPtrs &gp)
-        : rec(S.rec), col(S.col), tcut(t_cut), g(gp), quat(S.quat) {}
+    __device__ explicit GBufGradVisit(float t_cut) : tcut(t_cut) {}
+
+    __device__ __forceinline__ AttrTables tables(int) const { return t; }
 
     __device__ __forceinline__ void reset()
     {
@@ -358,56 +446,92 @@ struct GBufGradVisit {
         P = 0.0f;
     }
 
-    __device__ __forceinline__ bool operator()(uint32_t p, uint32_t id, float tau, const float4 r0, const float4 r1,
-                                               const float4 r2, const float4 r3, float crho2, const float3 o,
-                                               const float3 d)
+    static __device__ __forceinline__ void item(const SceneDev &S, const AttrTables &t, uint32_t p, const float4 r0,
+                                                const float4 r1, const float4 r2, const float4 r3, float crho2,
+                                                const float3 o, const float3 d, Item &it, float *in)
     {
-        const float4 c = col[p];
-        const float op = r1.w;
-        HitGeo hg;
-        value_geo(r0, r1, r2, r3, o, d, hg);
-        const float G = expf(-0.5f * hg.rho2);
-        const float a = op * G;
-        const float w = T * a;
-        const float side = hg.den > 0.0f ? -1.0f : 1.0f;  // normal toward the camera
-        const size_t i = id;
-        const float3 al = make_float3(albedo[3 * i], albedo[3 * i + 1], albedo[3 * i + 2]);
-        const float e = kD * tau + kA.x * al.x + kA.y * al.y + kA.z * al.z + kR * rough[i] + kM * metal[i] +
-                        kC.x * c.x + kC.y * c.y + kC.z * c.z - e0 + side * (r1.x * kN.x + r1.y * kN.y + r1.z * kN.z);
+        const float4 c = S.col[p];
+        const size_t i = __float_as_uint(r2.w);
+        in[2] = t.albedo[3 * i]; in[3] = t.albedo[3 * i + 1]; in[4] = t.albedo[3 * i + 2];
+        in[5] = t.rough[i];
+        in[6] = t.metal[i];
+        value_geo(r0, r1, r2, r3, o, d, it.hg);
+        it.G = expf(-0.5f * it.hg.rho2);
+        it.a = r1.w * it.G;
+        it.r1 = r1; it.r2 = r2; it.r3 = r3;
+        it.d = d;
+        it.sv = c.w;
+        it.p = p;
+        it.id = __float_as_uint(r2.w);
+        in[0] = it.a;
+        in[1] = hit_alpha(r1.w, crho2);
+        const bool away = it.hg.den > 0.0f;  // normal toward the camera
+        in[7] = away ? -r1.x : r1.x; in[8] = away ? -r1.y : r1.y; in[9] = away ? -r1.z : r1.z;
+        in[10] = c.x; in[11] = c.y; in[12] = c.z;
+    }
+
+    __device__ __forceinline__ bool step(const float *in, uint32_t, uint32_t, float tau, float *out)
+    {
+        const float a = in[0], w = T * a;
+        const float e = kD * tau + kA.x * in[2] + kA.y * in[3] + kA.z * in[4] + kR * in[5] + kM * in[6] +
+                        kC.x * in[10] + kC.y * in[11] + kC.z * in[12] - e0 +
+                        (in[7] * kN.x + in[8] * kN.y + in[9] * kN.z);
         P += w * e;
         float dA = T * e;
         const float om = 1.0f - a;
         if (om >= 1e-6f) dA += P / om;
-        const float sw = side * w;
-        float terms[13];
-        hit_param_grads<true>(hg, r1, r2, r3, d, a, G, dA, w * kD, make_float3(sw * kN.x, sw * kN.y, sw * kN.z),
-                              quat[p], r3.w, c.w, terms);
-        terms[10] = w * kC.x; terms[11] = w * kC.y; terms[12] = w * kC.z;
-        stage_add(stage, id, terms);
-        if (ga_albedo) {
-            atomicAdd(ga_albedo + 3 * i, w * kA.x);
-            atomicAdd(ga_albedo + 3 * i + 1, w * kA.y);
-            atomicAdd(ga_albedo + 3 * i + 2, w * kA.z);
-        }
-        if (ga_rough) atomicAdd(ga_rough + i, w * kR);
-        if (ga_metal) atomicAdd(ga_metal + i, w * kM);
-
+        out[0] = w;
+        out[1] = dA;
         T = T * (1.0f - a);
-        Td = trans_step(Td, hit_alpha(op, crho2));
+        Td = trans_step(Td, in[1]);
         return Td < tcut;
+    }
+
+    __device__ __forceinline__ void ray_terms(float *ray) const
+    {
+        ray[0] = kD; ray[1] = kR; ray[2] = kM;
+        ray[3] = kA.x; ray[4] = kA.y; ray[5] = kA.z;
+        ray[6] = kC.x; ray[7] = kC.y; ray[8] = kC.z;
+        ray[9] = kN.x; ray[10] = kN.y; ray[11] = kN.z;
+    }
+
+    __device__ __forceinline__ void emit(const SceneDev &S, const Item &it, const float *out, const float *ray, float *)
+    {
+        const float w = out[0], dA = out[1], sw = it.hg.den > 0.0f ? -w : w;
+        const size_t i = it.id;
+        float terms[13];
+        hit_param_grads<true>(it.hg, it.r1, it.r2, it.r3, it.d, it.a, it.G, dA, w * ray[0],
+                              make_float3(sw * ray[9], sw * ray[10], sw * ray[11]), S.quat[it.p], it.r3.w, it.sv,
+                              terms);
+        terms[10] = w * ray[6]; terms[11] = w * ray[7]; terms[12] = w * ray[8];
+        stage_add(stage, it.id, terms);
+        if (ga_albedo) {
+            atomicAdd(ga_albedo + 3 * i, w * ray[3]);
+            atomicAdd(ga_albedo + 3 * i + 1, w * ray[4]);
+            atomicAdd(ga_albedo + 3 * i + 2, w * ray[5]);
+        }
+        if (ga_rough) atomicAdd(ga_rough + i, w * ray[1]);
+        if (ga_metal) atomicAdd(ga_metal + i, w * ray[2]);
     }
 };
 
-// Hand hit p of the visit's ray to `visit` (record loaded, canonical rho^2
-// computed here): for callers that hold only the record position.
+// Hand hit p of the lane's own ray to `visit`, all its parts: for callers that
+// hold the record positions of a ray's hits.
 template <class Visit>
-__device__ __forceinline__ bool visit_hit(Visit &visit, const float4 *rec, uint32_t p, float3 o, float3 d)
+__device__ __forceinline__ bool visit_hit(Visit &visit, const SceneDev &S, uint32_t p, float3 o, float3 d)
 {
-    const float4 *r = rec + 4 * (size_t)p;
+    const float4 *r = S.rec + 4 * (size_t)p;
     const float4 r0 = r[0], r1 = r[1], r2 = r[2], r3 = r[3];
     float den, tau, rho2;
     canon_geo(r0, r1, r2, r3, o, d, den, tau, rho2);
-    return visit(p, __float_as_uint(r2.w), tau, r0, r1, r2, r3, rho2, o, d);
+    typename Visit::Item item;
+    float in[Visit::kIn], out[Visit::kOut], ray[Visit::kRay], ret[Visit::kBack + 1];
+    Visit::item(S, visit.tables(0), p, r0, r1, r2, r3, rho2, o, d, item, in);
+    const bool stop = visit.step(in, p, __float_as_uint(r2.w), tau, out);
+    visit.ray_terms(ray);
+    visit.emit(S, item, out, ray, ret);
+    if constexpr (Visit::kBack > 0) visit.collect(ret);
+    return stop;
 }
 
 }  // namespace grt

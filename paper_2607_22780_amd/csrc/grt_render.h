@@ -503,8 +503,6 @@ struct ShadeTrace {
 
     __device__ __forceinline__ void bind(const RenderArgs &a, const SceneDev &S)
     {
-        v.rec = S.rec;
-        v.col = S.col;
         v.tcut = a.tcut;
         w.tmin = a.tmin;
         w.tmax = INFINITY;
@@ -564,14 +562,11 @@ struct ShadeTrace {
 template <int K, bool kPerRayArgs = false>
 struct RelightTrace {
     Walker<K, kPerRayArgs ? kWindow3 : kWindow4> w;
-    AttrVisit v;
+    AttrVisitT<kPerRayArgs> v;
 
     __device__ __forceinline__ void bind(const RenderArgs &a, const SceneDev &S)
     {
-        v.rec = S.rec;
-        v.albedo = a.sa_albedo;
-        v.rough = a.sa_rough;
-        v.metal = a.sa_metal;
+        v.t = {a.sa_albedo, a.sa_rough, a.sa_metal};
         v.tcut = a.tcut;
         w.tmin = a.tmin;
         w.tmax = INFINITY;

@@ -325,7 +325,7 @@ struct RelightJob {
 
     __device__ RelightJob(const RenderArgs &a_) : a(a_), S(a_.S), r(0) { t.bind(a, S); }
     __device__ __forceinline__ Walker<K> &walker() { return t.w; }
-    __device__ __forceinline__ AttrVisit &visit() { return t.v; }
+    __device__ __forceinline__ decltype(t.v) &visit() { return t.v; }
     __device__ __forceinline__ bool begin(int64_t g)
     {
         r = a.order ? a.order[g] : (uint32_t)g;
@@ -373,7 +373,7 @@ struct RenderBwdJob {
     int spp;
 
     __device__ RenderBwdJob(const RenderArgs &a_, WaveStage *t)
-        : a(a_), S(a_.S), v(a_.S, a_.tcut, a_.g), spp(a_.nc + a_.ng + a_.ne)
+        : a(a_), S(a_.S), v(a_.tcut), spp(a_.nc + a_.ng + a_.ne)
     {
         v.stage = t;
         stage_init(t);
@@ -465,7 +465,7 @@ __global__ void __launch_bounds__(256) k_render_bwd_stored(RenderArgs a)
     const int64_t r = g < nray ? (a.order ? (int64_t)a.order[g] : g) : 0;
     const uint32_t nh = g < nray && a.S.n > 0 ? a.hits[r] : 0u;
     const float4 r0 = nh ? a.rays[3 * r] : make_float4(0.f, 0.f, 0.f, 0.f);
-    GradVisitT<kOrigin> v(a.S, a.tcut, a.g);
+    GradVisitT<kOrigin> v(a.tcut);
     v.stage = stage;
     v.gmu = make_float3(0.f, 0.f, 0.f);
     uint32_t cnt = 0;
@@ -487,7 +487,7 @@ __global__ void __launch_bounds__(256) k_render_bwd_stored(RenderArgs a)
         }
     }
     for (uint32_t i = 0; __ballot(i < cnt); ++i) {
-        if (i < cnt) visit_hit(v, a.S.rec, list[i], x, d);
+        if (i < cnt) visit_hit(v, a.S, list[i], x, d);
         stage_sync(a.g.acc, stage, false);
     }
     stage_sync(a.g.acc, stage, true);

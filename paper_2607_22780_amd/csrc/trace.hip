@@ -41,7 +41,7 @@ struct TraceJob {
     Walker<K> w;
     CompositeVisit<false> v;
 
-    __device__ TraceJob(const TraceArgs &a_) : a(a_), S(a_.S), v(a_.S, a_.tcut) {}
+    __device__ TraceJob(const TraceArgs &a_) : a(a_), S(a_.S), v(a_.tcut) {}
     __device__ __forceinline__ Walker<K> &walker() { return w; }
     __device__ __forceinline__ CompositeVisit<false> &visit() { return v; }
 
@@ -84,7 +84,7 @@ struct TraceBwdJob {
     BwdWalker<K> w;
     GradVisit v;
 
-    __device__ TraceBwdJob(const TraceBwdArgs &a_, WaveStage *t) : a(a_), S(a_.f.S), v(a_.f.S, a_.f.tcut, a_.g)
+    __device__ TraceBwdJob(const TraceBwdArgs &a_, WaveStage *t) : a(a_), S(a_.f.S), v(a_.f.tcut)
     {
         v.stage = t;
         stage_init(t);
@@ -131,7 +131,7 @@ struct TraceAttrJob {
     AttrVisit v;
 
     __device__ TraceAttrJob(const TraceAttrArgs &a_)
-        : a(a_), S(a_.f.S), v(a_.f.S, a_.f.tcut, a_.albedo, a_.rough, a_.metal) {}
+        : a(a_), S(a_.f.S), v(a_.f.tcut, a_.albedo, a_.rough, a_.metal) {}
     __device__ __forceinline__ Walker<K> &walker() { return w; }
     __device__ __forceinline__ AttrVisit &visit() { return v; }
 
@@ -170,7 +170,7 @@ struct TraceGBufJob {
     GBufVisit v;
 
     __device__ TraceGBufJob(const TraceGBufArgs &a_)
-        : a(a_), S(a_.f.S), v(a_.f.S, a_.f.tcut, a_.albedo, a_.rough, a_.metal) {}
+        : a(a_), S(a_.f.S), v(a_.f.tcut, a_.albedo, a_.rough, a_.metal) {}
     __device__ __forceinline__ Walker<K, kWindow3> &walker() { return w; }
     __device__ __forceinline__ GBufVisit &visit() { return v; }
 
@@ -317,9 +317,9 @@ struct TraceGBufBwdJob {
     BwdWalker<K> w;
     GBufGradVisit v;
 
-    __device__ TraceGBufBwdJob(const TraceGBufBwdArgs &a_, WaveStage *t) : a(a_), S(a_.f.S), v(a_.f.S, a_.f.tcut, a_.g)
+    __device__ TraceGBufBwdJob(const TraceGBufBwdArgs &a_, WaveStage *t) : a(a_), S(a_.f.S), v(a_.f.tcut)
     {
-        v.albedo = a.albedo; v.rough = a.rough; v.metal = a.metal;
+        v.t = {a.albedo, a.rough, a.metal};
         v.ga_albedo = a.ga_albedo; v.ga_rough = a.ga_rough; v.ga_metal = a.ga_metal;
         v.stage = t;
         stage_init(t);
