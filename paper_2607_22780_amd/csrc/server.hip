@@ -258,8 +258,7 @@ template <int K>
 static hipError_t go_epoch(const ServeEpoch &e, const RenderArgs *one, int64_t r0, bool relight, int num_cu,
                            hipStream_t st)
 {
-    // (12: 16 hits fit the same registers and take fewer rounds)
-    if (relight) return go_relight_epoch<(K == 12 ? 16 : K)>(e, one, r0, num_cu, st);
+    if (relight) return go_relight_epoch<K>(e, one, r0, num_cu, st);
     if (one)
         return (!e.stop && e.nchunks <= 1) ? go_serve_one_as<K, ShadeTrace<K>, true>(*one, e, r0, num_cu, st)
                                            : go_serve_one_as<K, ShadeTrace<K>, false>(*one, e, r0, num_cu, st);
@@ -278,7 +277,7 @@ static hipError_t launch_epoch(const ServeEpoch &e, const RenderArgs *one, int64
     switch (k) {
     case 4: return go_epoch<4>(e, one, r0, relight, num_cu, st);
     case 8: return go_epoch<8>(e, one, r0, relight, num_cu, st);
-    case 12: return go_epoch<12>(e, one, r0, relight, num_cu, st);
+    case 12:  // as a render: 16 hits fit the same registers and take fewer rounds
     case 16: return go_epoch<16>(e, one, r0, relight, num_cu, st);
     default: return hipErrorInvalidValue;
     }
