@@ -90,7 +90,7 @@ typedef struct {
 } grt_surfels;
 
 /* Bytes of device workspace a scene of n surfels needs (records and stored
- * quaternions in LBVH order, bounding boxes, LBVH nodes, sort buffers, and 64
+ * quaternions in BVH order, bounding boxes, BVH nodes, sort buffers, and 64
  * bytes per surfel in which the backward passes sum gradients).  256-byte aligned pointer required. */
 size_t grt_scene_workspace_bytes(int64_t n);
 
@@ -103,8 +103,8 @@ int grt_scene_create(grt_ctx *ctx, const grt_surfels *surfels, float alpha_min, 
 
 /* Build the acceleration structure on `stream`: per-surfel frames and
  * 3-sigma bounding boxes (the paper's adaptive bounding proxy, Eq.
- * icosahedron_transform, as an axis-aligned box), then an LBVH (Morton codes
- * of box centres, LSD radix sort, Karras hierarchy, bottom-up refit) -- the
+ * icosahedron_transform, as an axis-aligned box), then a BVH (Morton codes of
+ * centres, LSD radix sort, locally-ordered clustering, at most 63 levels) -- the
  * BVH the paper builds over its proxies (Sec. 3.2).  Reads the surfel arrays;
  * call again after any parameter change. */
 int grt_scene_build(grt_scene *scene, void *stream);
@@ -117,7 +117,7 @@ int grt_scene_destroy(grt_scene *scene);
  * records [n,16] float (sorted order; word 11 holds the surfel id as bits,
  * word 15 the stored scale s_u), nodes [max(n-1,0),16] (child boxes lo/hi as
  * floats 0..11, children as int32 words 12,13: >= 0 internal node, < 0 leaf
- * -(pos+1)), order [n] int32 (sorted position -> surfel id). */
+ * -(pos+1); word 14 the number of leaves below; node 0 the root), order [n] int32 (sorted position -> surfel id). */
 typedef struct {
     int64_t n;
     const float *records;
@@ -126,7 +126,8 @@ typedef struct {
     const float *leaf_boxes; /* [n,6] lo.xyz, hi.xyz in sorted order */
     const float *colours;    /* [n,4] rgb and the stored scale s_v, sorted order */
     const float *quats;      /* [n,4] the stored quaternion (w first), sorted order */
-    /* The 4-wide hierarchy the traversal walks, collapsed from `nodes`:
+    /* The 4-wide hierarchy, collapsed from `nodes` (the traversal walks a
+     * copy with the child boxes rounded outward to 8 bits a plane):
      * nodes4 [max(n-1,0),32] (floats 0..23 the four child boxes as lo.x[4],
      * lo.y[4], lo.z[4], hi.x[4], hi.y[4], hi.z[4]; int32 words 24..27 the
      * children: >= 0 a 4-wide node, < 0 leaf -(pos+1), 0x7fffffff unused;
@@ -569,7 +570,7 @@ int grt_render_relight(const grt_scene *scene, const grt_env *env, const grt_sur
  *   verts [nv,3], tris [nf,3] int32 vertex indices (device, borrowed, not to
  *   change after grt_mesh_build; a triangle with an index outside [0, nv) is
  *   ignored).  0 <= nf <= 2^29.  Workspace: grt_mesh_workspace_bytes(nf),
- *   256-byte aligned (LBVH over the triangles' boxes). */
+ *   256-byte aligned (BVH over the triangles' boxes). */
 typedef struct {
     int64_t nv;
     const float *verts;

@@ -73,8 +73,8 @@ struct SceneDev {
 
 // Wavefronts per SIMD that a persistent kernel is held to (128 VGPRs at 4, 168
 // at 3), up to the largest buffer that fits; the windows of the stacks take
-// what LDS that leaves (20 entries at 4, 24 at 3).  Measured, room of 1M
-// surfels: the radiance forward at K = 16 runs 512 x 512 x 32 rays in 37.2 ms
+// what LDS that leaves (20 entries at 4, 24 at 3).  Measured in a room of 1M
+// surfels, with hits still composited a lane at a time: the radiance forward at K = 16 runs 512 x 512 x 32 rays in 37.2 ms
 // at 4 and 41.1 at 3, the relighting query 23.9 and 24.7; kernels that carry
 // more per lane keep 3: primary-ray maps 11.0 against 11.6 ms at 4 (200k
 // surfels, forward and backward), a server epoch of several requests 39.3

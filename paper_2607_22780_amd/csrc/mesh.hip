@@ -151,9 +151,11 @@ struct MeshStack {
 };
 
 // Closest hit of one ray: triangle id (0xffffffff: miss) and barycentrics.
-// Bound by the vector L1 like the surfel walk (one tag access per lane and 16
-// bytes of a divergent load): a 4-wide quantized node is four loads, as a
-// binary one was, for half the node steps.
+// Bound by VALU issue (84% of the peak, 26 of 64 lanes in an instruction) and
+// by the vector L1 (one tag access per lane and 16 bytes of a divergent load):
+// a 4-wide quantized node is four loads, as a binary one was, for half the node
+// steps.  (Lanes that take new rays as theirs end: 9.5 against 9.3 ms for a
+// relit frame of 33.5M rays, since results are then gathered by few lanes.)
 __device__ __forceinline__ void mesh_closest(const float4 *__restrict__ rec, const NodeQ *__restrict__ nodes, int nf,
                                              float3 o, float3 d, float tmin, float tmax, MeshStack &stack,
                                              uint32_t &bid, float &bu, float &bv)

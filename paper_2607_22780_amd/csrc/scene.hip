@@ -821,7 +821,7 @@ void launch_radix_sort(int n, int passes, uint32_t *k0, uint32_t *v0, uint32_t *
     }
 }
 
-// Pieces of the LBVH build shared with the triangle mesh: reset the centre
+// Pieces of the BVH build shared with the triangle mesh: reset the centre
 // bounds; Morton codes of centres [n,3] within the bounds and their sort
 // (sorted codes / original indices back in keys0 / vals0); the binary
 // hierarchy, from leaf boxes in sorted order.

@@ -16,7 +16,7 @@
 // CUs that the current epoch's tail leaves idle.
 // Every sample's random counter carries its request id and every pixel is
 // summed in sample order, so a request's image is the same alone or in any
-// mix.  Scene and LBVH stay resident; each epoch launch ends when its rays
+// mix.  Scene and BVH stay resident; each epoch launch ends when its rays
 // are done, so no kernel outlives the epoch.
 #include <string.h>
 

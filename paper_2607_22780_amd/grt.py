@@ -429,7 +429,7 @@ class Context:
 
 
 class Scene:
-    """A built LBVH over borrowed surfel tensors (kept alive here)."""
+    """A built BVH over borrowed surfel tensors (kept alive here)."""
 
     def __init__(self, ctx: Context, means, scales, quats, opacity, rgb, alpha_min: float = 1.0 / 255.0,
                  build: bool = True, stream=None):
@@ -455,7 +455,7 @@ class Scene:
 
     def arrays(self):
         """Torch views into the built scene: records [n,16], nodes [n-1,16]
-        (float32; children as int32 in words 12-13), leaf boxes [n,6], order [n],
+        (float32; children as int32 in words 12-13, leaves below in 14), leaf boxes [n,6], order [n],
         colours [n,4] (rgb, s_v) and stored quaternions [n,4], all in sorted order;
         nodes4 [n-1,32] (the 4-wide hierarchy: boxes as structure of arrays in
         words 0-23, children as int32 in words 24-27) and nodes4_count [1]."""
