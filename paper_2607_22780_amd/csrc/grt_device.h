@@ -294,8 +294,8 @@ __device__ __forceinline__ double key_max(double a, double b)
 // key.
 //
 // What bounds the walk is VALU issue: lanes of a wavefront take the node step
-// and the leaf test in turns (25 of 64 lanes active per VALU instruction), at
-// 88% of the issue peak.  So each of these blocks is kept short: pushes
+// and the leaf test in turns (29 of 64 lanes active per VALU instruction), at
+// 75% of the issue peak.  So each of these blocks is kept short: pushes
 // without branches into ring windows, one merged push for kept and deferred
 // children, keys moved by min and max.  Node step 430 to 230 VALU
 // instructions, insertion at K = 16 121 to 81; room of 1M surfels: forward
