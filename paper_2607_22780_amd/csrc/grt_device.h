@@ -26,6 +26,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "grt_nodeq.h"
+
 namespace grt {
 
 constexpr float kGrazing = 1e-6f; // |n . d| below this is no intersection
@@ -38,29 +40,12 @@ struct alignas(16) Node {
     int4 d;    // left, right, unused, unused
 };
 
-// Unused child slots of a 4-wide node hold this reference (and a zero box).
-constexpr int kNoChild = 0x7fffffff;
-
 struct alignas(16) Node4 {
     float4 lx, ly, lz;  // lower corners of the four child boxes
     float4 hx, hy, hz;  // upper corners
     int4 ch;            // child references (kNoChild: unused slot)
     int4 pad;
 };
-
-// The node a walk loads: child j spans org + scale * [lo_j, hi_j] on each
-// axis, with byte j of the axis' lo and hi words (conservative, see
-// quantize_node).  The vector L1 bounds the walk as much as VALU issue does (a
-// divergent load is one tag access per lane and 16 bytes: 97% of its cycles
-// were busy or stalled with the seven loads of a 128-byte node), so a node is
-// four loads.
-struct alignas(16) NodeQ {
-    float org[3];
-    float scale[3];
-    uint32_t lo[3], hi[3];
-    int4 ch;  // child references (kNoChild: unused slot)
-};
-static_assert(sizeof(NodeQ) == 64, "four 16-byte loads");
 
 struct SceneDev {
     const float4 *rec;
@@ -192,41 +177,6 @@ __device__ __forceinline__ float o2f(int i) { return __int_as_float(i >= 0 ? i :
 __device__ __forceinline__ float safe_inv(float d)
 {
     return 1.0f / (fabsf(d) > 1e-30f ? d : copysignf(1e-30f, d));
-}
-
-// The walk's inverse direction, formed at each node step rather than held (3
-// registers): the hardware reciprocal (1 ulp) is far inside the slab test's
-// slack and the boxes' padding, so the test still rejects no box the ray
-// enters.  Components below 1e-18 are taken as that, so that plane * inverse
-// stays finite; the sign is kept.
-__device__ __forceinline__ float fast_inv(float d)
-{
-    return __builtin_amdgcn_rcpf(fabsf(d) > 1e-18f ? d : copysignf(1e-18f, d));
-}
-
-// Byte j of a word as a float (one instruction).
-template <int j>
-__device__ __forceinline__ float byte_f(uint32_t w)
-{
-    return (float)((w >> (8 * j)) & 255u);
-}
-
-// Child j of a node from the words of its near and far planes (chosen by the
-// sign of the direction): the depth of plane q of an axis is q * step + start,
-// one fused multiply-add, with no min or max of the pair.  Rounding moves a
-// plane by less than the margin the node was quantized with, plus a relative
-// part that the comparison allows for; a NaN keeps the child.
-template <int j>
-__device__ __forceinline__ bool slab_q(uint32_t nx, uint32_t ny, uint32_t nz, uint32_t fx, uint32_t fy, uint32_t fz,
-                                       const float3 step, const float3 start, float t0, float &tnear)
-{
-    const float ax = fmaf(byte_f<j>(nx), step.x, start.x), bx = fmaf(byte_f<j>(fx), step.x, start.x);
-    const float ay = fmaf(byte_f<j>(ny), step.y, start.y), by = fmaf(byte_f<j>(fy), step.y, start.y);
-    const float az = fmaf(byte_f<j>(nz), step.z, start.z), bz = fmaf(byte_f<j>(fz), step.z, start.z);
-    const float tn = fmaxf(fmaxf(ax, ay), fmaxf(az, t0));
-    const float tf = fminf(fminf(bx, by), bz);
-    tnear = tn;
-    return !(tn > tf * 1.0000005f + 1e-30f);
 }
 
 // One exchange of a sorting network: (sa, ca) takes the nearer of two children.

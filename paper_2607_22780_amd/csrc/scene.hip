@@ -515,51 +515,6 @@ constexpr int kCollapseTop = 1024;   // threads of the first launch
 constexpr int kCollapseWide = 2048;  // level width handed to the second
 constexpr int kCollapseWaves = 4096;
 
-// The NodeQ of m child boxes (lo xyz, hi xyz).  Per axis, a grid of 256 planes
-// over the children's union; each child takes the grid planes just outside
-// its own, at least `margin` (2^-20 of the union's extent) away: the walk
-// computes a plane's depth with an error below 2^-22 of that extent when the
-// ray starts inside it, and below 2^-22 of the depth otherwise.  Checked
-// against the arithmetic of the walk, so rounding here cannot shrink a box.
-__device__ __forceinline__ NodeQ quantize_node(const float (&box)[4][6], const int (&ref)[4], int m)
-{
-    NodeQ q;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        float lo = box[0][a], hi = box[0][3 + a];
-#pragma unroll
-        for (int j = 1; j < 4; ++j)
-            if (j < m) {
-                lo = fminf(lo, box[j][a]);
-                hi = fmaxf(hi, box[j][3 + a]);
-            }
-        const float margin = (hi - lo) * 9.5367431640625e-07f;
-        const float org = lo - 2.0f * margin;
-        float scale = (hi + 2.0f * margin - org) * (1.0f / 255.0f) * 1.000001f;
-        if (fmaf(255.0f, scale, org) < hi + margin) scale *= 1.00001f;
-        q.org[a] = org;
-        q.scale[a] = scale;
-        uint32_t wl = 0, wh = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (j >= m) continue;
-            const float l = box[j][a] - margin, h = box[j][3 + a] + margin;
-            // (a NaN plane, of a surfel with NaN parameters, keeps the whole span)
-            int ql = (int)fminf(fmaxf(floorf((l - org) / scale), 0.0f), 255.0f);
-            int qh = (int)fminf(fmaxf(ceilf((h - org) / scale), 0.0f), 255.0f);
-            if (ql > 0 && !(fmaf((float)ql, scale, org) <= l)) --ql;
-            if (qh < 255 && !(fmaf((float)qh, scale, org) >= h)) ++qh;
-            if (!(scale > 0.0f && l <= h)) { ql = 0; qh = 255; }
-            wl |= (uint32_t)ql << (8 * j);
-            wh |= (uint32_t)qh << (8 * j);
-        }
-        q.lo[a] = wl;
-        q.hi[a] = wh;
-    }
-    q.ch = make_int4(ref[0], ref[1], ref[2], ref[3]);
-    return q;
-}
-
 struct Collapsed {
     float box[4][6];
     int ref[4];  // binary node >= 0, leaf -(pos+1)

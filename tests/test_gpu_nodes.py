@@ -79,3 +79,19 @@ def test_nan_surfels_are_no_hits(grt_ctx):
     g = np.random.default_rng(6)
     o, d = rays_at(g, 800, 1.0, 0.0)
     check(grt, ctx, s, o, d, keep)
+
+
+@pytest.mark.parametrize("size,at,dist", [(300.0, 0.0, 1.0), (1000.0, 0.0, 1.0), (1.0, 300.0, 2.0),
+                                          (0.2, -1000.0, 2.0), (1.0, 0.0, 1000.0)])
+def test_far_scenes(grt_ctx, size, at, dist):
+    """Coordinates and depths where the boxes' padding is below a unit in the
+    last place; rays aimed at the surfels from `dist` sizes away."""
+    grt, ctx = grt_ctx
+    g = np.random.default_rng(8)
+    target = g.uniform(-1.0, 1.0, (2000, 3)) * size + at
+    o = (target + W.random_unit_vectors(g, 2000) * size * dist * g.uniform(0.5, 1.0, (2000, 1))).astype(np.float32)
+    d = target - o
+    d = (d / np.linalg.norm(d, axis=1, keepdims=True)).astype(np.float32)
+    s = W.scene0(n=2000, seed=3)
+    check(grt, ctx, W.Surfels(np.float32(s.means * size + at), np.float32(s.scales * 4 * size), s.quats, s.opacity,
+                              s.rgb), o, d)
