@@ -27,9 +27,8 @@ struct alignas(16) NodeQ {
 static_assert(sizeof(NodeQ) == 64, "four 16-byte loads");
 
 // The walk's inverse direction, formed at each node step rather than held (3
-// registers): the hardware reciprocal (1 ulp) is far inside the slab test's
-// slack and the boxes' padding, so the test still rejects no box the ray
-// enters.  Components below 1e-18 are taken as that, so that plane * inverse
+// registers), by the hardware reciprocal (1 ulp, which the slab test's slack
+// counts).  Components below 1e-18 are taken as that, so that plane * inverse
 // stays finite; the sign is kept.
 __device__ __forceinline__ float fast_inv(float d)
 {
@@ -45,9 +44,13 @@ __device__ __forceinline__ float byte_f(uint32_t w)
 
 // Child j of a node from the words of its near and far planes (chosen by the
 // sign of the direction): the depth of plane q of an axis is q * step + start,
-// one fused multiply-add, with no min or max of the pair.  Rounding moves a
-// plane by less than the margin the node was quantized with, plus a relative
-// part that the comparison allows for; a NaN keeps the child.
+// one fused multiply-add, with no min or max of the pair.  Where start and step
+// cancel, rounding moves a plane by less than the margin the node was quantized
+// with.  The rest is relative to the depth: with u = 2^-24, 2 u of the
+// reciprocal and u each of the difference to the origin, its product and the
+// sum, so 5 u a plane; planes of two axes 10 u and the comparison's product 1,
+// for which it allows 16.  (With 8 u a ray through an edge of a box was lost
+// where all of them met.)  A NaN keeps the child.
 template <int j>
 __device__ __forceinline__ bool slab_q(uint32_t nx, uint32_t ny, uint32_t nz, uint32_t fx, uint32_t fy, uint32_t fz,
                                        const float3 step, const float3 start, float t0, float &tnear)
@@ -58,7 +61,7 @@ __device__ __forceinline__ bool slab_q(uint32_t nx, uint32_t ny, uint32_t nz, ui
     const float tn = fmaxf(fmaxf(ax, ay), fmaxf(az, t0));
     const float tf = fminf(fminf(bx, by), bz);
     tnear = tn;
-    return !(tn > tf * 1.0000005f + 1e-30f);
+    return !(tn > tf * 1.000001f + 1e-30f);
 }
 
 // The NodeQ of m child boxes (lo xyz, hi xyz).  Per axis, a grid of 256 planes

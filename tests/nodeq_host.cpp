@@ -1,12 +1,14 @@
 // The quantized node on the CPU: quantize_node and slab_q compiled for the
 // host, checked in extended precision.  argv[1] names the check.  Prints the
 // number of cases and of failures.
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <random>
+#include <vector>
 
 #define __device__
 #define __forceinline__ inline
@@ -93,8 +95,69 @@ static void planes()
     printf("planes %ld inside %ld wide %ld\n", n, inside, wide);
 }
 
+// A direction component whose reciprocal, within 1 ulp of the exact one, is
+// nearly that much above (side > 0) or below it.
+static float off_component(int side, float &inv)
+{
+    for (;;) {
+        const float d = (float)(0.5 * (1.0 - U(0, 0.004))), r = (float)(1.0 / (double)d);
+        inv = std::nextafterf(r, side > 0 ? 9.0f : 0.0f);
+        const double ulp = (double)std::nextafterf(r, 9.0f) - r, err = std::fabs((double)inv - 1.0 / (double)d) / ulp;
+        if (err <= 1.0 && err > 0.997) return d;
+    }
+}
+
+struct Plane {
+    long double depth;  // exact, of the single-precision ray
+    float o, org, scale;
+    int q;
+};
+
+// Near planes of x whose computed depth is nearly all the roundings together
+// too far, far planes of y as much too near, paired where the exact depths
+// meet within half a unit in the last place: the ray enters the box.
+static void slack()
+{
+    long n = 0, lost = 0, kept = 0;
+    for (int trial = 0; trial < 3; ++trial) {
+        float inv[2];
+        const float d[2] = {off_component(1, inv[0]), off_component(-1, inv[1])};
+        const double m = 1.08;  // depths just above a power of two
+        std::vector<Plane> v[2];
+        for (int a = 0; a < 2; ++a) {
+            for (long i = 0; i < 10000000; ++i) {
+                Plane c;
+                c.org = (float)U(-1e-4, 1e-4);
+                c.scale = (float)U(0.5e-6, 1e-6);
+                c.q = 1 + (int)(R() % 254);
+                c.o = (float)-(512 * m * (1 + U(0, 2e-4)) * d[a]);
+                const float t = fmaf((float)c.q, c.scale * inv[a], (c.org - c.o) * inv[a]);
+                c.depth = ((long double)c.org + (long double)c.q * c.scale - c.o) / d[a];
+                const long double err = (t - c.depth) / c.depth, lim = 0.972L * (2 + 3 / m) * kU;
+                if (a == 0 ? err > lim : err < -lim) v[a].push_back(c);
+            }
+            std::sort(v[a].begin(), v[a].end(), [](const Plane &x, const Plane &y) { return x.depth < y.depth; });
+        }
+        for (const Plane &x : v[0])
+            for (const Plane &y : v[1]) {
+                const long double gap = (y.depth - x.depth) / x.depth;
+                if (gap < 0) continue;
+                if (gap > 0.5L * kU) break;
+                const float3 step = {x.scale * inv[0], y.scale * inv[1], 0.0f};
+                float3 start = {(x.org - x.o) * inv[0], (y.org - y.o) * inv[1], NAN};  // no plane of z
+                float tn;
+                ++n;
+                lost += !slab_q<0>((uint32_t)x.q, 0u, 0u, 255u, (uint32_t)y.q, 0u, step, {start.x, start.y, start.z}, 0.0f, tn);
+                start.y *= 1.0f - 4e-6f;  // a far plane clearly before the near one
+                kept += slab_q<0>((uint32_t)x.q, 0u, 0u, 255u, (uint32_t)y.q, 0u, step, start, 0.0f, tn);
+            }
+    }
+    printf("pairs %ld lost %ld kept %ld\n", n, lost, kept);
+}
+
 int main(int argc, char **argv)
 {
     if (argc > 1 && !strcmp(argv[1], "planes")) planes();
+    if (argc > 1 && !strcmp(argv[1], "slack")) slack();
     return 0;
 }

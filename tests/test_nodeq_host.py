@@ -33,3 +33,11 @@ def test_planes_lie_outside_their_boxes(host):
     r = host("planes")
     assert r["planes"] > 300_000
     assert r["inside"] == 0 and r["wide"] == 0, r
+
+
+def test_slack_covers_the_roundings(host):
+    """Rays that meet a box's near plane of one axis and its far plane of
+    another at the same depth, with every rounding of the two against them."""
+    r = host("slack")
+    assert r["pairs"] > 100
+    assert r["lost"] == 0 and r["kept"] == 0, r
