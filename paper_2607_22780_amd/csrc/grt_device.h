@@ -291,6 +291,19 @@ __device__ __forceinline__ uint32_t lds_addr(const int *p) { return (uint32_t)(u
 __device__ __forceinline__ int lds_load(uint32_t a) { return *(const LdsInt *)(uintptr_t)a; }
 __device__ __forceinline__ void lds_store(uint32_t a, int x) { *(LdsInt *)(uintptr_t)a = x; }
 
+// What the lanes of a wavefront wrote, before others of them read it (all
+// lanes, wavefront-uniform point).  The barrier emits nothing: a fence alone
+// orders the accesses of one path, but the compiler may copy it into both arms
+// of a branch on the lane and run the readers' arm first.
+__device__ __forceinline__ void wave_sync(bool global = false)
+{
+    if (global) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    else __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (global) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    else __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // x of the lane at byte address 4 * lane (all lanes).
 __device__ __forceinline__ float lane_pull(int address, float x)
 {

@@ -640,13 +640,13 @@ __device__ __forceinline__ void reduce_pixels(int64_t npix, int spp, const float
             const int q = k * (64 / kReduceStep) + lane / kReduceStep, s = lane % kReduceStep;
             if (p0 + q < npix && s < m) v[q][s] = contrib[(p0 + q) * spp + j0 + s];
         }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        wave_sync();
         if (p < npix)
             for (int s = 0; s < m; ++s) {
                 const float4 c = v[lane][s];
                 x += c.x; y += c.y; z += c.z;
             }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        wave_sync();
     }
     if (p >= npix) return;
     const float inv = 1.0f / (float)spp;

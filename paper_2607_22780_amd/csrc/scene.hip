@@ -371,7 +371,7 @@ __global__ void __launch_bounds__(kClusterBlock) k_cluster(int n, int count, Clu
         const bool alone = m <= 64;
         if (alone && wave) break;
         const auto sync = [&]() {
-            if (alone) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (alone) wave_sync();
             else __syncthreads();
         };
         // number of the pairs and (upper half) of the merged clusters before
@@ -726,7 +726,7 @@ __global__ void __launch_bounds__(256) k_collapse_subtrees(const Node *__restric
         cur = make_int2(next, next + all);
         next += all;
         // the lanes' entries of the queue and the stack, before another lane reads them
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+        wave_sync(true);
     }
 }
 
