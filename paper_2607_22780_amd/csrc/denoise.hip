@@ -19,6 +19,8 @@
 // in the depth term; the normal term's logarithm is a short series near 1,
 // where sigma_n multiplies its error (two expf, a powf and a division per
 // weight took 3.5 times as long).
+#include <type_traits>
+
 #include "grt_internal.h"
 
 namespace grt {
@@ -29,21 +31,38 @@ constexpr int kDnSpan = kDnTile + 2 * kDenoiseMaxRadius;
 // log2 of the cosine between two unit normals (0 where it is not positive).
 // Near 1 the hardware logarithm's absolute error is about that of its result
 // at 2, and sigma_n multiplies it; there 2 atanh(s), s = (c - 1) / (c + 1),
-// with terms up to s^7 (|s| < 1/7: the next is below 2^-26 of the sum).
+// with terms up to s^7 (|s| <= 1/7: the next is below 2^-25 of the sum).
+// The hardware logarithm takes subnormal cosines for 0; kTiny scales them first.
+template <bool kTiny>
 __device__ __forceinline__ float log2_cos(float c)
 {
     const float s = (c - 1.0f) * __builtin_amdgcn_rcpf(c + 1.0f), s2 = s * s;
     const float near1 = s * fmaf(s2, fmaf(s2, fmaf(s2, 2.8853901f / 7.0f, 2.8853901f / 5.0f), 2.8853901f / 3.0f), 2.8853901f);
-    const float l = c >= 0.75f ? near1 : __builtin_amdgcn_logf(c);
+    float l;
+    if (kTiny) {
+        const bool sub = c < 1.17549435e-38f;
+        l = __builtin_amdgcn_logf(sub ? c * 4294967296.0f : c) - (sub ? 32.0f : 0.0f);
+    } else {
+        l = __builtin_amdgcn_logf(c);
+    }
+    l = c >= 0.75f ? near1 : l;
     return c > 0.0f ? l : 0.0f;
 }
+
+// A component that may make a cosine subnormal.  Where no unit normal of a
+// tile has one, the products of its normals are multiples of 2^-126 (two
+// components of 2^-40 and 24 bits), and so are their sums: a workgroup then
+// runs the weights without kTiny, which costs 5 instructions a weight (1024 x
+// 1024, radius 3: 59 us with it, 56 without).
+__device__ __forceinline__ bool tiny(float x) { return x != 0.0f && fabsf(x) < 9.0949470e-13f; }
 
 __global__ void __launch_bounds__(256) k_denoise(DenoiseArgs a)
 {
     __shared__ float4 lc[kDnSpan * kDnSpan];  // rgb, depth
-    __shared__ float4 ln[kDnSpan * kDnSpan];  // unit normal, valid (1/0)
+    __shared__ float4 ln[kDnSpan * kDnSpan];  // unit normal, valid (>= 1, or below)
     const int R = a.radius, span = kDnTile + 2 * R;
     const int x0 = blockIdx.x * kDnTile - R, y0 = blockIdx.y * kDnTile - R;
+    bool small = false;
     for (int i = threadIdx.x; i < span * span; i += blockDim.x) {
         const int ty = i / span, tx = i - ty * span;
         const int gx = x0 + tx, gy = y0 + ty;
@@ -56,26 +75,33 @@ __global__ void __launch_bounds__(256) k_denoise(DenoiseArgs a)
                 const float il = l > 0.0f ? 1.0f / l : 0.0f;
                 c = make_float4(a.rgb[3 * p], a.rgb[3 * p + 1], a.rgb[3 * p + 2], a.depth[p]);
                 n = make_float4(nx * il, ny * il, nz * il, 1.0f);
+                small |= tiny(n.x) | tiny(n.y) | tiny(n.z);
             }
         }
         lc[ty * span + tx] = c;
         ln[ty * span + tx] = n;
     }
     __syncthreads();
+    // (the flag is the lowest bit of a word that is there: one more word, and
+    // a compute unit takes four workgroups instead of five)
+    uint32_t *flag = reinterpret_cast<uint32_t *>(&ln[0].w);
+    if (small) atomicOr(flag, 1u);
+    __syncthreads();
+    const bool any_tiny = *flag & 1u;
     const int tx = threadIdx.x % kDnTile, ty = threadIdx.x / kDnTile;
     const int px = blockIdx.x * kDnTile + tx, py = blockIdx.y * kDnTile + ty;
     if (px >= a.W || py >= a.H) return;
     const int64_t p = (int64_t)py * a.W + px;
     const int lx = tx + R, ly = ty + R;
     const float4 cc = lc[ly * span + lx], cn = ln[ly * span + lx];
-    if (cn.w == 0.0f) {  // invalid: unchanged
+    if (cn.w < 1.0f) {  // invalid: unchanged
         a.out[3 * p] = a.rgb[3 * p]; a.out[3 * p + 1] = a.rgb[3 * p + 1]; a.out[3 * p + 2] = a.rgb[3 * p + 2];
         return;
     }
     // depth gradient (R >= 1, so the four neighbours are staged)
     auto grad = [&](int ox, int oy) {
         const float4 pc = lc[(ly + oy) * span + lx + ox], mc = lc[(ly - oy) * span + lx - ox];
-        const bool hp = ln[(ly + oy) * span + lx + ox].w != 0.0f, hm = ln[(ly - oy) * span + lx - ox].w != 0.0f;
+        const bool hp = ln[(ly + oy) * span + lx + ox].w >= 1.0f, hm = ln[(ly - oy) * span + lx - ox].w >= 1.0f;
         if (hp && hm) return (pc.w - mc.w) * 0.5f;
         if (hp) return pc.w - cc.w;
         if (hm) return cc.w - mc.w;
@@ -84,22 +110,27 @@ __global__ void __launch_bounds__(256) k_denoise(DenoiseArgs a)
     const float gx = grad(1, 0), gy = grad(0, 1);
     constexpr float kLog2e = 1.44269504f;
     const float inv2s2 = kLog2e / (2.0f * a.sigma_s * a.sigma_s);
+    const float sigma_n = fminf(a.sigma_n, 3.402823466e+38f);  // (infinity times log2 1 is no weight)
     float sr = 0.0f, sg = 0.0f, sb = 0.0f, sw = 0.0f;
-    for (int dy = -R; dy <= R; ++dy)
-        for (int dx = -R; dx <= R; ++dx) {
-            const int q = (ly + dy) * span + lx + dx;
-            const float4 qn = ln[q], qc = lc[q];
-            const float c = cn.x * qn.x + cn.y * qn.y + cn.z * qn.z;
-            // (kept above what the reciprocal can take)
-            const float scale = fmaxf(a.sigma_d * fabsf(gx * (float)dx + gy * (float)dy) + a.eps_d, 1e-37f);
-            float x = -(float)(dx * dx + dy * dy) * inv2s2;
-            x = fmaf(-kLog2e * fabsf(cc.w - qc.w), __builtin_amdgcn_rcpf(scale), x);
-            x = fmaf(a.sigma_n, log2_cos(c), x);
-            // (a zero base to the power 0 is 1)
-            const bool on = qn.w != 0.0f && (c > 0.0f || a.sigma_n == 0.0f);
-            const float B = on ? __builtin_amdgcn_exp2f(x) : 0.0f;
-            sr += B * qc.x; sg += B * qc.y; sb += B * qc.z; sw += B;
-        }
+    const auto sums = [&](auto tiny_cosines) {
+        for (int dy = -R; dy <= R; ++dy)
+            for (int dx = -R; dx <= R; ++dx) {
+                const int q = (ly + dy) * span + lx + dx;
+                const float4 qn = ln[q], qc = lc[q];
+                const float c = cn.x * qn.x + cn.y * qn.y + cn.z * qn.z;
+                // (kept above what the reciprocal can take)
+                const float scale = fmaxf(a.sigma_d * fabsf(gx * (float)dx + gy * (float)dy) + a.eps_d, 1e-37f);
+                float x = -(float)(dx * dx + dy * dy) * inv2s2;
+                x = fmaf(-kLog2e * fabsf(cc.w - qc.w), __builtin_amdgcn_rcpf(scale), x);
+                x = fmaf(sigma_n, log2_cos<decltype(tiny_cosines)::value>(c), x);
+                // (an invalid neighbour's normal is 0; a zero base to the power 0 is 1)
+                const bool on = (c > 0.0f) | ((sigma_n == 0.0f) & (qn.w >= 1.0f));
+                const float B = on ? __builtin_amdgcn_exp2f(x) : 0.0f;
+                sr += B * qc.x; sg += B * qc.y; sb += B * qc.z; sw += B;
+            }
+    };
+    if (any_tiny) sums(std::true_type{});
+    else sums(std::false_type{});
     const float inv = sw > 0.0f ? 1.0f / sw : 1.0f;
     a.out[3 * p] = sr * inv; a.out[3 * p + 1] = sg * inv; a.out[3 * p + 2] = sb * inv;
 }

@@ -76,3 +76,24 @@ def test_denoise_rejects_bad_arguments(grt_ctx):
         with pytest.raises(grt.GrtError) as e:
             grt.denoise(ctx, rgb, t(gb.depth), t(gb.n), t(gb.valid), gb.H, gb.W, **kw)
         assert e.value.code == grt.ERR_INVALID
+
+
+@pytest.mark.parametrize("sigma_n", [0.0, 0.01, 0.5, 128.0, np.inf])
+def test_denoise_vanishing_cosines(grt_ctx, sigma_n):
+    """Normals whose cosine is subnormal, 0 or negative, at exponents where
+    such a neighbour still counts (0, small ones) and where none does."""
+    grt, ctx = grt_ctx
+    gb = W.gbuffer1(12, 15, seed=2)
+    g = np.random.default_rng(3)
+    n = np.zeros((gb.npix, 3), np.float32)
+    kind = g.integers(0, 5, gb.npix)
+    n[kind == 0, 0] = 1.0
+    n[kind == 1, 1], n[kind == 1, 0] = 1.0, 1e-39
+    n[kind == 2, 1], n[kind == 2, 0] = 1.0, 1.4e-45
+    n[kind == 3, 1] = 1.0
+    n[kind == 4, 0] = -1.0
+    gb.n[:], gb.valid[:], gb.depth[:] = n, 1, 2.0
+    rgb = g.uniform(0, 2, (gb.npix, 3)).astype(np.float32)
+    got = run(grt, ctx, rgb, gb, radius=2, sigma_n=sigma_n)
+    ref = O.denoise(rgb, gb.depth, gb.n, gb.valid, gb.H, gb.W, radius=2, sigma_n=sigma_n)
+    np.testing.assert_allclose(got, ref, rtol=1e-4, atol=1e-5)
