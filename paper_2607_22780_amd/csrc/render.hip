@@ -277,15 +277,21 @@ hipError_t launch_dfg_lut(float *lut, hipStream_t st)
 
 // A wavefront draws one sample index of 64 neighbouring pixels, so that it
 // runs one proposal: with a pixel's samples side by side, every wavefront ran
-// all three in turns.  Bound by double-precision issue.
-__global__ void __launch_bounds__(256) k_render_gen(RenderArgs a)
+// all three in turns.  Bound by double-precision issue.  An image of at most
+// 32 pixels (probes with many samples) fills the lanes with 64 / 2^lp
+// consecutive samples of each of 2^lp pixels instead, which costs turns only
+// where a proposal begins (1 pixel x 65,536 samples: 163 us with one lane of
+// each wavefront, 11 so; 63 x 1,024: 11 either way).
+__global__ void __launch_bounds__(256) k_render_gen(RenderArgs a, int lp)
 {
-    const int spp = a.nc + a.ng + a.ne;
+    const int spp = a.nc + a.ng + a.ne, lane = threadIdx.x & 63;
     const int64_t npix = (int64_t)a.H * a.W;
+    const uint32_t runs = ((uint32_t)spp + (63u >> lp)) >> (6 - lp);  // of samples
     const uint32_t w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4u + (threadIdx.x >> 6));
-    const uint32_t group = w / (uint32_t)spp;
-    const int64_t p = 64 * (int64_t)group + (threadIdx.x & 63);
-    if (p < npix) gen_ray(a, p, (int)(w - group * (uint32_t)spp));
+    const uint32_t group = w / runs;
+    const int64_t p = ((int64_t)group << lp) + (lane & ((1 << lp) - 1));
+    const int j = (int)((w - group * runs) << (6 - lp)) + (lane >> lp);
+    if (p < npix && j < spp) gen_ray(a, p, j);
 }
 
 // ---------------------------------------------------------------------------
@@ -642,8 +648,12 @@ hipError_t launch_render_backward_stored(const RenderArgs &a, const RenderWS &w,
 hipError_t launch_render_gen(const RenderArgs &a, hipStream_t st)
 {
     // (fewer than 2^31 samples: at most 2^25 + 65536 wavefronts)
-    const int64_t waves = ((int64_t)a.H * a.W + 63) / 64 * (a.nc + a.ng + a.ne);
-    hipLaunchKernelGGL(k_render_gen, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, a);
+    const int64_t npix = (int64_t)a.H * a.W;
+    const int spp = a.nc + a.ng + a.ne;
+    int lp = 0;
+    while (lp < 6 && npix > (int64_t)1 << lp) ++lp;
+    const int64_t waves = ((npix + (1 << lp) - 1) >> lp) * ((spp + (63 >> lp)) >> (6 - lp));
+    hipLaunchKernelGGL(k_render_gen, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, a, lp);
     return hipGetLastError();
 }
 

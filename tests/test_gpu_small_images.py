@@ -1,0 +1,37 @@
+"""Images of a few pixels (probes) at the sizes where the split of generation
+over wavefronts changes: 2^k pixels and one beside, fewer samples than a
+wavefront takes of a pixel and a ragged number more.  Every sample's direction,
+pdf, weight and radiance, and the pixels, against the oracle."""
+import numpy as np
+import pytest
+
+from paper_2607_22780_amd import workloads as W
+from test_gpu_render import compare_samples, render_both
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def grt_ctx():
+    from paper_2607_22780_amd import grt
+    return grt, grt.Context(0)
+
+
+def probes(npix, seed=0):
+    """A 1 x npix strip of valid pixels."""
+    gb = W.gbuffer1(24, 24, seed=seed)
+    at = np.nonzero(gb.valid)[0][:npix]
+    assert len(at) == npix
+    return gb.subset(at)
+
+
+@pytest.mark.parametrize("npix", [1, 2, 3, 5, 16, 17, 31, 32, 33, 63, 64, 65])
+@pytest.mark.parametrize("split", [(3, 2, 2), (1, 0, 0), (40, 21, 10)])
+def test_small_images(grt_ctx, npix, split):
+    grt, ctx = grt_ctx
+    s = W.scene1(n=3000, seed=0, s_lo=0.02, s_hi=0.1)
+    gpu, ref = render_both(grt, ctx, s, probes(npix), W.envmap(16, 32, seed=1), split, 9)
+    edge = compare_samples(gpu["dump"], ref, max_excused=0.01)
+    ok = ~edge.any(axis=1)
+    assert ok.mean() > 0.5
+    np.testing.assert_allclose(gpu["rgb"][ok], ref["rgb"][ok], rtol=1e-4, atol=1e-5)
