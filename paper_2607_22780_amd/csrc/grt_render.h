@@ -617,38 +617,70 @@ __device__ __forceinline__ void bind_trace(RelightTrace<K, false> &t, const Rend
 // c_pbr = (1/N_r) sum_j contrib[p, j], summed in sample order, for the pixels
 // of a block of 256 threads (every thread calls it).  A pixel's samples are
 // consecutive, so a thread that read its own pixel's would touch a line per
-// lane; a wavefront instead loads 8 samples of its 64 pixels at a time, 128
-// bytes a pixel, and each lane adds its own from LDS (bound by memory: 1024 x
-// 1024 x 32 samples 450 us before).
-constexpr int kReduceStep = 8;
+// lane; a wavefront instead loads a tile of 64 >> kLog pixels and 8 << kLog
+// samples at a time, 16 bytes a lane and entry, and the pixels' lanes add
+// theirs from LDS.  The rule (reduce_shape; times with cold caches, us):
+//   64 x 8 tiles for many pixels, bound by memory: 1M x 16 samples 99 (by the
+//     pixels' own threads 244), 262,144 x 16 29 (40);
+//   16 x 32 up to 2^17 pixels, where too few wavefronts are in flight to hide
+//     a tile's latency and a longer one pays it less often: 63 x 1,024 134
+//     (64 x 8: 501; own threads 149), 65,535 x 32 18 (27; 17);
+//   own threads up to 16 samples and 98,304 pixels, which have no chain worth
+//     cutting: 16,384 x 16 8 (64 x 8: 14; 16 x 32: 9), 90,000 x 16 15 (17; 17),
+//     but 131,072 x 16 22 (19; 19).
+constexpr int kReduceOwn = -1;  // as kLog: by the pixels' own threads
+inline int reduce_shape(int64_t npix, int spp)
+{
+    if (spp <= 16) return npix <= 98304 ? kReduceOwn : 0;
+    return npix <= 1 << 17 ? 2 : 0;
+}
+template <int kLog>
+constexpr int kReducePixels = kLog < 0 ? 256 : 4 * (64 >> kLog);  // of a block
+
+template <int kLog>
 struct ReduceTile {
-    float4 v[4][64][kReduceStep + 1];
+    float4 v[4][64 >> kLog][(8 << kLog) + 1];
 };
+template <>
+struct ReduceTile<kReduceOwn> {};
+
+template <int kLog>
 __device__ __forceinline__ void reduce_pixels(int64_t npix, int spp, const float4 *__restrict__ contrib,
-                                              float *__restrict__ out, ReduceTile &tile)
+                                              float *__restrict__ out, ReduceTile<kLog> &tile)
 {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    float4(*v)[kReduceStep + 1] = tile.v[wave];
-    const int64_t p0 = (int64_t)blockIdx.x * 256 + wave * 64;
+    const int64_t p0 = (int64_t)blockIdx.x * kReducePixels<kLog> + wave * (kReducePixels<kLog> / 4);
     if (p0 >= npix) return;
     const int64_t p = p0 + lane;
     float x = 0.f, y = 0.f, z = 0.f;
-    for (int j0 = 0; j0 < spp; j0 += kReduceStep) {
-        const int m = spp - j0 < kReduceStep ? spp - j0 : kReduceStep;
-#pragma unroll
-        for (int k = 0; k < kReduceStep; ++k) {
-            const int q = k * (64 / kReduceStep) + lane / kReduceStep, s = lane % kReduceStep;
-            if (p0 + q < npix && s < m) v[q][s] = contrib[(p0 + q) * spp + j0 + s];
+    if constexpr (kLog == kReduceOwn) {
+        if (p >= npix) return;
+        const float4 *c = contrib + p * spp;
+        for (int j = 0; j < spp; ++j) {
+            const float4 v = c[j];
+            x += v.x; y += v.y; z += v.z;
         }
-        wave_sync();
-        if (p < npix)
-            for (int s = 0; s < m; ++s) {
-                const float4 c = v[lane][s];
-                x += c.x; y += c.y; z += c.z;
+    } else {
+        constexpr int kPix = 64 >> kLog, kStep = 8 << kLog;
+        auto v = tile.v[wave];
+        const bool own = lane < kPix && p < npix;
+        for (int j0 = 0; j0 < spp; j0 += kStep) {
+            const int m = spp - j0 < kStep ? spp - j0 : kStep;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int q = (k * 64 + lane) / kStep, s = (k * 64 + lane) % kStep;
+                if (p0 + q < npix && s < m) v[q][s] = contrib[(p0 + q) * spp + j0 + s];
             }
-        wave_sync();
+            wave_sync();
+            if (own)
+                for (int s = 0; s < m; ++s) {
+                    const float4 c = v[lane][s];
+                    x += c.x; y += c.y; z += c.z;
+                }
+            wave_sync();
+        }
+        if (!own) return;
     }
-    if (p >= npix) return;
     const float inv = 1.0f / (float)spp;
     out[3 * p] = x * inv;
     out[3 * p + 1] = y * inv;

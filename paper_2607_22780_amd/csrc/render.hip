@@ -570,11 +570,31 @@ hipError_t launch_render_shade_grad(const RenderArgs &a, const ShadeGradOut &o, 
     return hipGetLastError();
 }
 
+template <int kLog>
 __global__ void __launch_bounds__(256) k_render_reduce(int64_t npix, int spp, const float4 *__restrict__ contrib,
                                                        float *__restrict__ out)
 {
-    __shared__ ReduceTile tile;
-    reduce_pixels(npix, spp, contrib, out, tile);
+    __shared__ ReduceTile<kLog> tile;
+    reduce_pixels<kLog>(npix, spp, contrib, out, tile);
+}
+
+template <int kLog>
+static void go_reduce(int64_t npix, int spp, const RenderArgs &a, hipStream_t st)
+{
+    const unsigned nb = (unsigned)((npix + kReducePixels<kLog> - 1) / kReducePixels<kLog>);
+    hipLaunchKernelGGL(k_render_reduce<kLog>, dim3(nb), dim3(256), 0, st, npix, spp, a.contrib, a.out);
+}
+
+static hipError_t launch_reduce(const RenderArgs &a, hipStream_t st)
+{
+    const int64_t npix = (int64_t)a.H * a.W;
+    const int spp = a.nc + a.ng + a.ne;
+    switch (reduce_shape(npix, spp)) {
+    case 0: go_reduce<0>(npix, spp, a, st); break;
+    case 2: go_reduce<2>(npix, spp, a, st); break;
+    default: go_reduce<kReduceOwn>(npix, spp, a, st);
+    }
+    return hipGetLastError();
 }
 
 template <int K, bool kHitList>
@@ -749,9 +769,7 @@ hipError_t launch_render(const RenderArgs &a, const RenderWS &w, int k, int num_
     }
     if (e != hipSuccess) return e;
     if ((e = timer_mark(tm, true, st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_render_reduce, dim3((unsigned)((npix + 255) / 256)), dim3(256), 0, st, npix,
-                       a.nc + a.ng + a.ne, a.contrib, a.out);
-    return hipGetLastError();
+    return launch_reduce(a, st);
 }
 
 template <int K>
@@ -784,9 +802,7 @@ hipError_t launch_render_relight(const RenderArgs &a, const RenderWS &w, int k, 
     if (e != hipSuccess) return e;
     const int64_t total = npix * (a.nc + a.ng + a.ne);
     hipLaunchKernelGGL(k_relight_shade, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, a, total);
-    hipLaunchKernelGGL(k_render_reduce, dim3((unsigned)((npix + 255) / 256)), dim3(256), 0, st, npix,
-                       a.nc + a.ng + a.ne, a.contrib, a.out);
-    return hipGetLastError();
+    return launch_reduce(a, st);
 }
 
 hipError_t launch_relight_shade(const RenderArgs &a, hipStream_t st)
@@ -806,9 +822,7 @@ hipError_t launch_render_relight_mesh(const RenderArgs &a, const MeshTraceArgs &
     if ((e = launch_mesh_relight_query(a, m, st)) != hipSuccess) return e;
     const int64_t total = npix * (a.nc + a.ng + a.ne);
     hipLaunchKernelGGL(k_relight_shade, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, a, total);
-    hipLaunchKernelGGL(k_render_reduce, dim3((unsigned)((npix + 255) / 256)), dim3(256), 0, st, npix,
-                       a.nc + a.ng + a.ne, a.contrib, a.out);
-    return hipGetLastError();
+    return launch_reduce(a, st);
 }
 
 hipError_t launch_render_backward(const RenderArgs &a, const RenderWS &w, int k, int num_cu, hipStream_t st,

@@ -216,14 +216,35 @@ __global__ void __launch_bounds__(256) GRT_WAVES(K, 4)
 // counters/total: the claim counters of a preemptible epoch that held the
 // request's last rays; if the epoch was stopped before claiming them all, the
 // request is not complete and the reduction does nothing.
+template <int kLog>
 __global__ void __launch_bounds__(256) k_serve_reduce(const RenderArgs *a, int64_t npix,
                                                       const unsigned long long *counters, int64_t total)
 {
-    __shared__ ReduceTile tile;
+    __shared__ ReduceTile<kLog> tile;
     if (counters)
         for (int q = 0; q < kParts; ++q)
             if ((int64_t)counters[q] < part_begin(total, q + 1) - part_begin(total, q)) return;
-    reduce_pixels(npix, a->nc + a->ng + a->ne, a->contrib, a->out, tile);
+    reduce_pixels<kLog>(npix, a->nc + a->ng + a->ne, a->contrib, a->out, tile);
+}
+
+template <int kLog>
+static void go_serve_reduce(const RenderArgs *a, int64_t npix, const unsigned long long *counters, int64_t total,
+                            hipStream_t st)
+{
+    const unsigned nb = (unsigned)((npix + kReducePixels<kLog> - 1) / kReducePixels<kLog>);
+    hipLaunchKernelGGL(k_serve_reduce<kLog>, dim3(nb), dim3(256), 0, st, a, npix, counters, total);
+}
+
+// a: the request's arguments on the device, of npix pixels and spp samples
+static hipError_t launch_serve_reduce(const RenderArgs *a, int64_t npix, int spp, const unsigned long long *counters,
+                                      int64_t total, hipStream_t st)
+{
+    switch (reduce_shape(npix, spp)) {
+    case 0: go_serve_reduce<0>(a, npix, counters, total, st); break;
+    case 2: go_serve_reduce<2>(a, npix, counters, total, st); break;
+    default: go_serve_reduce<kReduceOwn>(a, npix, counters, total, st);
+    }
+    return hipGetLastError();
 }
 
 template <int K, class Trace, bool kStop>
@@ -919,9 +940,8 @@ static bool launch_cotrace(grt_server *s, grt::EpochSlot &E, grt::EpochSlot &oth
     for (ServerJob *j : mem) {
         if (err != hipSuccess) break;
         if (j->relight && (err = grt::launch_relight_shade(j->args, E.stream)) != hipSuccess) break;
-        hipLaunchKernelGGL(grt::k_serve_reduce, dim3((unsigned)((j->npix + 255) / 256)), dim3(256), 0, E.stream,
-                           E.d_jobs + j->slot, j->npix, nullptr, n);
-        err = hipGetLastError();
+        const int spp = j->args.nc + j->args.ng + j->args.ne;
+        err = grt::launch_serve_reduce(E.d_jobs + j->slot, j->npix, spp, nullptr, n, E.stream);
         if (err == hipSuccess)
             err = hipMemcpyAsync(j->spec.out_rgb, j->args.out, 12 * (size_t)j->npix,
                                  j->out_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, E.stream);
@@ -1059,9 +1079,9 @@ bool launch(grt_server *s, grt::EpochSlot &E, grt::EpochSlot &other, int64_t bud
         ServerJob &j = s->jobs[id];
         // relighting: the shading pass over the request's parked query results
         if (j.relight && (err = grt::launch_relight_shade(j.args, E.stream)) != hipSuccess) break;
-        hipLaunchKernelGGL(grt::k_serve_reduce, dim3((unsigned)((j.npix + 255) / 256)), dim3(256), 0, E.stream,
-                           E.d_jobs + j.slot, j.npix, E.preemptible ? E.counters : nullptr, off);
-        err = hipGetLastError();
+        const int spp = j.args.nc + j.args.ng + j.args.ne;
+        err = grt::launch_serve_reduce(E.d_jobs + j.slot, j.npix, spp, E.preemptible ? E.counters : nullptr, off,
+                                       E.stream);
         if (err == hipSuccess)
             err = hipMemcpyAsync(j.spec.out_rgb, j.args.out, 12 * (size_t)j.npix,
                                  j.out_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, E.stream);

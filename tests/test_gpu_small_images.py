@@ -35,3 +35,23 @@ def test_small_images(grt_ctx, npix, split):
     ok = ~edge.any(axis=1)
     assert ok.mean() > 0.5
     np.testing.assert_allclose(gpu["rgb"][ok], ref["rgb"][ok], rtol=1e-4, atol=1e-5)
+
+
+@pytest.mark.parametrize("spp,sizes", [(16, [70, 98304, 98305]), (17, [70, 131072, 131073]), (65, [70, 131073])])
+def test_pixel_sums_do_not_depend_on_the_split(grt_ctx, spp, sizes):
+    """The same pixels in images on both sides of each line where the split of
+    the per-pixel sums changes: sums are in sample order, so equal bit for bit."""
+    import torch
+    from gpu_util import scene_tensors, t
+    grt, ctx = grt_ctx
+    base = probes(70)
+    scene = grt.Scene(ctx, *scene_tensors(W.scene1(n=3000, seed=0, s_lo=0.02, s_hi=0.1)))
+    E = grt.Env(ctx, t(W.envmap(16, 32, seed=1)))
+    split = (spp - 8, 5, 3)
+    first = None
+    for n in sizes:
+        G = grt.GBuffer.from_numpy(base.subset(np.arange(n) % 70), torch.device("cuda", 0))
+        rgb = grt.render_mis(scene, E, G, split=split, seed=9)["rgb"][:70].cpu().numpy()
+        assert np.isfinite(rgb).all() and rgb.any()
+        first = rgb if first is None else first
+        np.testing.assert_array_equal(rgb.view(np.uint32), first.view(np.uint32), err_msg=str(n))
