@@ -158,7 +158,7 @@ typedef struct {
 
 /* k: k-nearest hit buffer size per traversal round, one of 1,2,4,8,12,16,32
  *    (results do not depend on k; some paths run a larger buffer than asked
- *    for where it fits the same registers).
+ *    for where it fits the same registers, or a smaller one where that does not).
  * t_cut: transmittance cutoff (1e-3 in the workloads).
  * sky: radiance of escaped rays, L = c_rt + T sky (when env is NULL).
  * env: optional built environment (grt_env_build); then L = c_rt + T L_env(d)

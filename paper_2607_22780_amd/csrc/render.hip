@@ -445,7 +445,7 @@ __global__ void __launch_bounds__(256) GRT_WAVES(K, 4) k_render_relight(RenderAr
 }
 
 template <int K, bool kOrigin>
-__global__ void __launch_bounds__(256) GRT_WAVES(K, 3) k_render_bwd(RenderArgs a)
+__global__ void __launch_bounds__(256) GRT_WAVES(K, kOrigin && K > 8 ? 2 : 3) k_render_bwd(RenderArgs a)
 {
     __shared__ WaveStage stages[4];
     RenderBwdJob<K, kOrigin> job(a, &stages[(threadIdx.x >> 6) & 3]);
@@ -621,10 +621,22 @@ static hipError_t go_render_bwd_as(const RenderArgs &a, int num_cu, hipStream_t 
     return hipGetLastError();
 }
 
+// With origin gradients (the shading state's) 8 hits are the most that 3
+// wavefronts per SIMD hold without spilling (164 VGPRs; 12 hits spill 9, 16
+// hits 94), so larger buffers run 8: re-traversal alone, 500k surfels of a
+// room, 320 x 320 x 16, 7.7 ms, with 12 hits 7.9, with 16 9.2 and with 16 at 2
+// wavefronts, which do not spill, 8.6.  The last are the better only where a
+// launch traces no more than the samples that overflowed long hit lists, so
+// that few rays with many hits set its time: lists of 64 4.8 against 5.1, lists
+// of 16 7.7 against 6.9.
+constexpr int kLongList = 32;
+
 template <int K>
 static hipError_t go_render_bwd(const RenderArgs &a, int num_cu, hipStream_t st)
 {
-    return a.gorig ? go_render_bwd_as<K, true>(a, num_cu, st) : go_render_bwd_as<K, false>(a, num_cu, st);
+    if (!a.gorig) return go_render_bwd_as<K, false>(a, num_cu, st);
+    if (K == 16 && !(a.hits && a.hcap >= kLongList)) return go_render_bwd_as<8, true>(a, num_cu, st);
+    return go_render_bwd_as<K, true>(a, num_cu, st);
 }
 
 static hipError_t timer_mark(const KernelTimer *tm, bool end, hipStream_t st)
@@ -656,7 +668,7 @@ hipError_t launch_render_backward_stored(const RenderArgs &a, const RenderWS &w,
     case 4: e = go_render_bwd<4>(b, num_cu, st); break;
     case 8: e = go_render_bwd<8>(b, num_cu, st); break;
     case 12:
-    case 13:  // as 16: 143.3 to 139.0 ms with the forward (1M, 1024 x 1024 x 16)
+    case 13:  // as 16, which fits the same registers: 143.3 to 139.0 ms with the forward (1M, 1024 x 1024 x 16)
     case 16: e = go_render_bwd<16>(b, num_cu, st); break;
     case 32: e = go_render_bwd<32>(b, num_cu, st); break;
     default: return hipErrorInvalidValue;
@@ -840,7 +852,7 @@ hipError_t launch_render_backward(const RenderArgs &a, const RenderWS &w, int k,
     case 4: e = go_render_bwd<4>(a, num_cu, st); break;
     case 8: e = go_render_bwd<8>(a, num_cu, st); break;
     case 12:
-    case 13:  // as 16: 143.3 to 139.0 ms with the forward (1M, 1024 x 1024 x 16)
+    case 13:  // as 16, which fits the same registers: 143.3 to 139.0 ms with the forward (1M, 1024 x 1024 x 16)
     case 16: e = go_render_bwd<16>(a, num_cu, st); break;
     case 32: e = go_render_bwd<32>(a, num_cu, st); break;
     default: return hipErrorInvalidValue;

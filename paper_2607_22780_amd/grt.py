@@ -1027,7 +1027,7 @@ class RenderMISShadedFn(torch.autograd.Function):
         gb = GBuffer(H, W, *(t.detach().contiguous() for t in (x, n, wo, albedo, rough, metal)), valid.contiguous())
         hits = make_hit_list(gb.npix, sum(split), hit_cap, gb.x.device) if hit_cap > 0 else None
         res = render_mis(scene, env, gb, split=split, seed=seed, k=k, save=True, hits=hits, hit_cap=hit_cap)
-        # the backward's k: at most 12 (its register budget)
+        # the backward's k: at most 12 (its kernels with origin gradients hold 8 hits)
         ctx_.scene, ctx_.env, ctx_.gb, ctx_.cfg = scene, env, gb, (split, seed, min(k, 12), hit_cap)
         ctx_.saved_state, ctx_.hits = res["saved"], hits
         return res["rgb"]
