@@ -318,7 +318,16 @@ struct Frontier {
     // divides D, and a window's oldest entry always sits at a multiple of it,
     // so the entries of a move are consecutive slots (immediate offsets).
     static constexpr int kSpill = D % 8 == 0 ? 8 : 4;
-    static_assert(D % kSpill == 0 && D >= kSpill + 5, "a move leaves room for what a step may add");
+    // Pushes between two calls of make_room, at most: 3 on the walk stack, 4 on
+    // the deferred list.  A node step defers up to 4 children, and the leaf
+    // test one hit more; but a node that yields a leaf has kept its nearest
+    // child (walk_node), so it defers 3 before that test.  One slot of the
+    // deferred window stays free beyond them, since push stores to it always.
+    static constexpr int kWalkPush = 3, kDeferPush = 4;
+    static constexpr int kWalkFull = D - kWalkPush, kDeferFull = D - kDeferPush - 1;  // most entries to leave
+    static_assert(D % kSpill == 0 && kSpill >= kWalkPush && kSpill >= kDeferPush,
+                  "a move out of a window makes the room of a step");
+    static_assert(kDeferFull >= 0 && kSpill + kWalkPush <= D, "a refilled window takes a step");
     uint32_t base;        // LDS address of this lane's slot 0 of window 0; window 1 follows
     uint32_t woff;        // the window that holds the walk: 0 or kWindow (the other one defers)
     uint32_t wtop, dtop;  // LDS address of the next free slot of the walk / deferred window
@@ -359,15 +368,14 @@ struct Frontier {
         old += kSpill;
     }
 
-    // Before a walking step, which pushes at most 3 items on the walk stack
-    // and 4 on the deferred list, and a leaf test after it that defers one
-    // more.  A deferred list too long is dropped (lost); while it is, what is
-    // pushed on it goes the same way.
+    // Before a walking step and the leaf test after it.  A deferred list too
+    // long is dropped (lost); while it is, what is pushed on it goes the same
+    // way.
     __device__ __forceinline__ void make_room(bool &lost)
     {
-        if (wn <= D - 3 && dn <= D - 5) return;
-        if (wn > D - 3) spill(wtop, wlo(), wn, wold, mem_of(woff));
-        if (dn > D - 5) {
+        if (wn <= kWalkFull && dn <= kDeferFull) return;
+        if (wn > kWalkFull) spill(wtop, wlo(), wn, wold, mem_of(woff));
+        if (dn > kDeferFull) {
             if (lost || dold + kSpill > kMaxDeferred - D) {
                 lost = true;
                 clear_def();
