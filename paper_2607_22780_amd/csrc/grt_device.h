@@ -37,7 +37,7 @@ struct alignas(16) Node {
     float4 a;  // L.lo.x L.lo.y L.lo.z L.hi.x
     float4 b;  // L.hi.y L.hi.z R.lo.x R.lo.y
     float4 c;  // R.lo.z R.hi.x R.hi.y R.hi.z
-    int4 d;    // left, right, unused, unused
+    int4 d;    // left, right, leaves below (the collapse places its queue by them), unused
 };
 
 struct alignas(16) Node4 {
@@ -151,21 +151,6 @@ __device__ __forceinline__ float trans_step(float T, float a)
     return T * (1.0f - a);
 }
 
-// ---------------------------------------------------------------------------
-// Slab test against one box, clipped to [t0, t1]; conservative by a few ulps.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ bool slab(float lx, float ly, float lz, float hx, float hy, float hz, const float3 o,
-                                     const float3 inv, float t0, float t1, float &tnear)
-{
-    float ax = (lx - o.x) * inv.x, bx = (hx - o.x) * inv.x;
-    float ay = (ly - o.y) * inv.y, by = (hy - o.y) * inv.y;
-    float az = (lz - o.z) * inv.z, bz = (hz - o.z) * inv.z;
-    float tn = fmaxf(fmaxf(fminf(ax, bx), fminf(ay, by)), fmaxf(fminf(az, bz), t0));
-    float tf = fminf(fminf(fmaxf(ax, bx), fmaxf(ay, by)), fminf(fmaxf(az, bz), t1));
-    tnear = tn;
-    return tn <= tf * 1.0000005f + 1e-30f;
-}
-
 // order-preserving float <-> int maps (atomic min/max of floats)
 __device__ __forceinline__ int f2o(float f)
 {
@@ -173,11 +158,6 @@ __device__ __forceinline__ int f2o(float f)
     return i >= 0 ? i : i ^ 0x7fffffff;
 }
 __device__ __forceinline__ float o2f(int i) { return __int_as_float(i >= 0 ? i : i ^ 0x7fffffff); }
-
-__device__ __forceinline__ float safe_inv(float d)
-{
-    return 1.0f / (fabsf(d) > 1e-30f ? d : copysignf(1e-30f, d));
-}
 
 // One exchange of a sorting network: (sa, ca) takes the nearer of two children.
 __device__ __forceinline__ void exchange(float &sa, int &ca, float &sb, int &cb)
