@@ -270,7 +270,11 @@ __global__ void __launch_bounds__(256) k_mesh_trace_attr(MeshTraceArgs a)
 // global sort and no scattered writes are paid for it.  (Relit frame of 1024 x
 // 1024 x 32 through 46k triangles: tiles of 1,024 11.0 ms, 2,048 11.3, 4,096
 // 11.8; 12 stack entries in LDS instead of 8, so fewer blocks, 12.0.)
-constexpr int kMeshTile = 1024;
+// Tiles of 1,024 give a thread four rays in turn, so they wait for launches
+// that fill the chip anyway: through 46k triangles 16 x 16 x 16 samples take 107
+// us in tiles of 256 and 270 in tiles of 1,024, 256 x 256 x 4 159 and 370, 512 x
+// 512 x 8 637 and 687, 512 x 512 x 16 1.29 ms both, 1024 x 1024 x 16 4.83 and 4.70.
+constexpr int64_t kMeshWide = 1 << 22;  // samples
 constexpr int kMeshBins = 257;  // 16 x 16 directions, then the untraced
 
 // octahedral direction bin, 16 x 16, along a Morton curve
@@ -290,6 +294,7 @@ __device__ __forceinline__ int dir_bin(float4 d)
     return spread(iu) | (spread(iv) << 1);
 }
 
+template <int kMeshTile>
 __global__ void __launch_bounds__(256) k_mesh_relight_query(RenderArgs a, MeshTraceArgs m, int64_t total)
 {
     __shared__ int2 top[kMeshLds][256];
@@ -362,8 +367,12 @@ hipError_t launch_mesh_relight_query(const RenderArgs &a, const MeshTraceArgs &m
 {
     const int64_t total = (int64_t)a.H * a.W * (a.nc + a.ng + a.ne);
     if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mesh_relight_query, dim3((unsigned)((total + kMeshTile - 1) / kMeshTile)), dim3(256), 0, st, a,
-                       m, total);
+    if (total >= kMeshWide)
+        hipLaunchKernelGGL(k_mesh_relight_query<1024>, dim3((unsigned)((total + 1023) / 1024)), dim3(256), 0, st, a, m,
+                           total);
+    else
+        hipLaunchKernelGGL(k_mesh_relight_query<256>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, a, m,
+                           total);
     return hipGetLastError();
 }
 

@@ -55,3 +55,23 @@ def test_pixel_sums_do_not_depend_on_the_split(grt_ctx, spp, sizes):
         assert np.isfinite(rgb).all() and rgb.any()
         first = rgb if first is None else first
         np.testing.assert_array_equal(rgb.view(np.uint32), first.view(np.uint32), err_msg=str(n))
+
+
+def test_mesh_frames_do_not_depend_on_the_tiles(grt_ctx):
+    """The same pixels relit through the mesh in frames on both sides of the
+    number of samples where the query's tiles change, with ragged last tiles."""
+    import torch
+    from gpu_util import t
+    grt, ctx = grt_ctx
+    base = W.gbuffer3(24, 24).subset(np.arange(200, 270))
+    m = W.mesh3(wall_res=8, segments=12)
+    mesh = grt.Mesh(ctx, t(m.verts), t(m.tris))
+    at = [t(a) for a in (m.albedo, m.rough, m.metal, m.normal)]
+    E = grt.Env(ctx, t(W.envmap(16, 32, seed=1))).prefilter()
+    first = None
+    for n in (70, 65535, 65536, 65537):
+        G = grt.GBuffer.from_numpy(base.subset(np.arange(n) % 70), torch.device("cuda", 0))
+        rgb = grt.render_relight_mesh(mesh, E, *at, G, split=(32, 16, 16), seed=4)["rgb"][:70].cpu().numpy()
+        assert np.isfinite(rgb).all() and rgb.any()
+        first = rgb if first is None else first
+        np.testing.assert_array_equal(rgb.view(np.uint32), first.view(np.uint32), err_msg=str(n))
