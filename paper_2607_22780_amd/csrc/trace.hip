@@ -114,8 +114,10 @@ struct TraceBwdJob {
     __device__ __forceinline__ void drain() { stage_sync(a.g.acc, v.stage, true); }
 };
 
+// (16 hits spill 7 registers at 4 wavefronts per SIMD: 1.2M rays through 500k
+// surfels of a room 5.43 ms, at 3 5.04; 32,768 through 4,096 287 us and 279)
 template <int K>
-__global__ void __launch_bounds__(256) GRT_WAVES(K, 4) k_trace(TraceArgs a)
+__global__ void __launch_bounds__(256) GRT_WAVES(K, K < 16 ? 4 : 3) k_trace(TraceArgs a)
 {
     TraceJob<K> job(a);
     run_persistent<K>(job, a.counters, a.n);

@@ -1,7 +1,7 @@
 """Registers of the kernels as built: the notes that the compiler wrote into
-libgrt.so's gfx950 code objects.  The re-traversing backwards run a persistent
-loop in which a spilled register is stored and loaded by every step: at most
-four, one 16-byte access."""
+libgrt.so's gfx950 code objects.  The traversals run a persistent loop in which
+a spilled register is stored and loaded by every step: at most four, one
+16-byte access."""
 import os
 import re
 import struct
@@ -41,6 +41,12 @@ def spills(tmp_path_factory):
             assert len(names) == len(counts)
             out.update(zip(names, map(int, counts)))
     return out
+
+
+def test_plain_traces_do_not_spill(spills):
+    trace = {n: c for n, c in spills.items() if re.match(r"_ZN3grt\d+k_traceI", n)}
+    assert len(trace) == 7
+    assert not {n: c for n, c in trace.items() if c > 4}
 
 
 def test_backward_kernels_do_not_spill(spills):
