@@ -108,8 +108,7 @@ int check_rays(const grt_rays *r)
     return GRT_OK;
 }
 
-// backward: the MIS backward also takes 13 (the size that fits its register
-// budget at 3 wavefronts per SIMD)
+// backward: the MIS backward also takes 13 (it runs as 16 does)
 static int check_k(int k, bool backward = false)
 {
     if (k == 1 || k == 2 || k == 4 || k == 8 || k == 12 || k == 16 || k == 32) return GRT_OK;

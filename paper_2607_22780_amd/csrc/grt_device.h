@@ -57,13 +57,16 @@ struct SceneDev {
 };
 
 // Wavefronts per SIMD that a persistent kernel is held to (128 VGPRs at 4, 168
-// at 3), up to the largest buffer that fits; the windows of the stacks take
-// what LDS that leaves (20 entries at 4, 24 at 3).  Measured in a room of 1M
-// surfels, with hits still composited a lane at a time: the radiance forward at K = 16 runs 512 x 512 x 32 rays in 37.2 ms
-// at 4 and 41.1 at 3, the relighting query 23.9 and 24.7; kernels that carry
-// more per lane keep 3: primary-ray maps 11.0 against 11.6 ms at 4 (200k
-// surfels, forward and backward), a server epoch of several requests 39.3
-// against 42.0, and the backwards, whose LDS also holds gradient lines.
+// at 3); the windows of the stacks take what LDS that leaves (20 entries at 4,
+// 24 at 3).  At K = 16 a kernel held to 4 spills a few registers, which may cost
+// less than the fourth wavefront gives.  Room of 1M surfels: the radiance
+// forward (2 spilled) runs 512 x 512 x 32 rays in 33.4 ms at 4 and 37.3 at 3, the
+// relighting query (8) 21.6 and 22.0; the attribute query (5) is the same at
+// both; the plain trace (7) is the faster at 3.  Kernels that carry more per
+// lane keep 3: primary-ray maps 11.0 against 11.6 ms at 4 (200k surfels, forward
+// and backward), a server epoch of several requests 39.3 against 42.0 (both with
+// hits still composited a lane at a time), and the backwards, whose LDS also
+// holds gradient lines.
 constexpr int kWindow4 = 20, kWindow3 = 24;
 constexpr int waves_for(int k, int waves) { return k <= 16 ? waves : 1; }
 #define GRT_WAVES(K, W) __attribute__((amdgpu_waves_per_eu(waves_for(K, W))))

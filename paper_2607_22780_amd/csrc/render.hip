@@ -17,8 +17,6 @@
 
 namespace grt {
 
-constexpr float kPi = 3.14159265358979323846f;
-
 // ---------------------------------------------------------------------------
 // Environment proposal tables: texel weight = luminance x sin(theta_centre);
 // cumulative sums in double, left to right, rounded to float at the end.

@@ -988,8 +988,8 @@ class RenderMISFn(torch.autograd.Function):
                 k_bwd=None, timers=None):
         """hit_cap > 0: store up to hit_cap hits per sample in the forward and
         differentiate from the stored lists; 0: re-traverse in the backward.
-        k_bwd: k-buffer size of the backward (default k, at most 16: the
-        backward's register budget; results do not depend on either).
+        k_bwd: k-buffer size of the backward (default k, at most 16, which fits
+        the backward's registers; results do not depend on either).
         timers: optional (forward, backward) Timer pair that records the
         trace kernels of the two passes."""
         scene = Scene(gctx, means.detach().contiguous(), scales.detach().contiguous(), quats.detach().contiguous(),
